@@ -184,7 +184,7 @@ struct ScanArgs {
   const uint32_t* read_order;  // chunk position -> read index, or null for identity
   uint64_t n_reads;
   uint32_t n_tiles;
-  uint32_t n_rchunks;          // read chunks (set by the launcher): a multiple of 8
+  uint32_t n_rchunks;          // read chunks (set by the launcher)
   uint32_t* mask_out;
   void* counts_out;
   uint32_t counts_bytes;

@@ -47,6 +47,13 @@ __device__ __forceinline__ void range_of(uint64_t n, uint32_t k, uint64_t* lo, u
   *hi = min(n, *lo + per);
 }
 
+// Launch position of the i-th read of parity f in a class that starts at
+// `base` and holds m reads of the rarer parity: the first m of each parity
+// alternate (position parity = read parity), the rest of the larger one follow.
+__device__ __forceinline__ uint32_t launch_position(uint32_t base, uint32_t m, uint32_t f, uint32_t i) {
+  return i < m ? base + 2u * i + (f ^ (base & 1u)) : base + 2u * m + (i - m);
+}
+
 // hist[k][key]: reads of range k with that key
 __global__ __launch_bounds__(256) void k_order_hist(const int64_t* offsets, uint64_t n, uint32_t q,
                                                    const DynSizes* dyn, uint32_t* hist) {
@@ -67,11 +74,19 @@ __global__ __launch_bounds__(256) void k_order_hist(const int64_t* offsets, uint
 __global__ __launch_bounds__(kKeys) void k_order_prefix(uint32_t* hist) {
   __shared__ uint32_t total[kKeys];
   const uint32_t key = threadIdx.x;
+  // 32 counts in flight at a time: one by one, each waiting for the store
+  // before it, the 1024 steps took 28 us
+  constexpr uint32_t kAhead = 32;
   uint32_t acc = 0;
-  for (uint32_t k = 0; k < kMaxRanges; ++k) {
-    const uint32_t c = hist[k * kKeys + key];
-    hist[k * kKeys + key] = acc;
-    acc += c;
+  for (uint32_t k0 = 0; k0 < kMaxRanges; k0 += kAhead) {
+    uint32_t c[kAhead];
+#pragma unroll
+    for (uint32_t j = 0; j < kAhead; ++j) c[j] = hist[(k0 + j) * kKeys + key];
+#pragma unroll
+    for (uint32_t j = 0; j < kAhead; ++j) {
+      hist[(k0 + j) * kKeys + key] = acc;
+      acc += c[j];
+    }
   }
   total[key] = acc;
   __syncthreads();
@@ -96,11 +111,37 @@ __global__ __launch_bounds__(256) void k_order_scatter(const int64_t* offsets, u
   for (uint64_t r = lo + threadIdx.x; r < hi; r += blockDim.x) {
     const uint32_t key = key_of(offsets, r, q), c = key >> 1, f = key & 1u;
     const uint32_t i = atomicAdd(&cur[key], 1u);
-    const uint32_t base = tab[2 * c], m = tab[2 * c + 1];
-    // the first m reads of each parity alternate (position parity = read
-    // parity); the rest of the larger parity follow them
-    const uint32_t pos = i < m ? base + 2u * i + (f ^ (base & 1u)) : base + 2u * m + (i - m);
-    order[pos] = (uint32_t)r;
+    order[launch_position(tab[2 * c], tab[2 * c + 1], f, i)] = (uint32_t)r;
+  }
+}
+
+// The same order for up to kOneGroup reads, by one workgroup in one launch:
+// LDS counters take the place of the per-range histograms and their prefix.
+constexpr uint64_t kOneGroup = 16384;
+__global__ __launch_bounds__(1024) void k_order_one(const int64_t* offsets, uint64_t n, uint32_t q,
+                                                   const DynSizes* dyn, uint32_t* order) {
+  __shared__ uint32_t cur[kKeys], total[kKeys], base_s[kBuckets];
+  const uint32_t t = threadIdx.x;
+  if (t < kKeys) cur[t] = total[t] = 0;
+  __syncthreads();
+  const uint64_t nn = dyn ? min(dyn->n_reads, n) : n;
+  for (uint64_t r = t; r < nn; r += 1024) atomicAdd(&total[key_of(offsets, r, q)], 1u);
+  __syncthreads();
+  if (t < kBuckets) {
+    // inclusive scan of the class sizes over the first wavefront
+    const uint32_t v = total[2 * t] + total[2 * t + 1];
+    uint32_t x = v;
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t y = (uint32_t)__shfl_up((int)x, d);
+      if ((int)t >= d) x += y;
+    }
+    base_s[t] = x - v;
+  }
+  __syncthreads();
+  for (uint64_t r = t; r < nn; r += 1024) {
+    const uint32_t key = key_of(offsets, r, q), c = key >> 1, f = key & 1u;
+    const uint32_t i = atomicAdd(&cur[key], 1u);
+    order[launch_position(base_s[c], min(total[2 * c], total[2 * c + 1]), f, i)] = (uint32_t)r;
   }
 }
 
@@ -111,6 +152,10 @@ uint64_t length_order_scratch_words() { return (uint64_t)kMaxRanges * kKeys + 2 
 hipError_t launch_length_order(const int64_t* offsets, uint64_t n, uint32_t q, const DynSizes* dyn, uint32_t* hist,
                                uint32_t* order, hipStream_t s) {
   if (n == 0) return hipSuccess;
+  if (n <= kOneGroup) {
+    hipLaunchKernelGGL(k_order_one, dim3(1), dim3(1024), 0, s, offsets, n, q, dyn, order);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_order_hist, dim3(kMaxRanges), dim3(256), 0, s, offsets, n, q, dyn, hist);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -19,10 +19,8 @@
 // streams its token list against the LDS rows: G = TW/LW lanes share a read,
 // each lane owns LW words (32*LW bins) and reads them with LW/4 16-byte LDS
 // loads per token. Tokens arrive pre-scaled to the LDS byte offset of their
-// row, so a row address costs one add per token. Workgroup ids are remapped
-// so the 32 CUs of one XCD work on the tiles of the same read chunk, whose
-// tokens then stay in that XCD's L2; chunks go round-robin to the XCDs, and
-// their number is a multiple of 8, so each XCD gets the same work.
+// row, so a row address costs one add per token. All CUs work on the tiles of
+// one read chunk at a time, whose tokens then stay in the XCDs' L2s.
 //
 // Full 32-token blocks go through the Harley-Seal tree, two blocks per step
 // so that only every other block's carry ripples through the upper planes;
@@ -37,6 +35,8 @@
 // 8 planes (counts up to 255); a wavefront holding a longer read switches to
 // 16 planes and covers its words in 2-word passes, which keeps that path
 // within the registers of the common one.
+
+#include <algorithm>
 
 #include "grim_internal.h"
 
@@ -364,6 +364,14 @@ __device__ __forceinline__ void scan_read(const ScanArgs& a, const char* lds_lan
   }
 }
 
+// 16 bytes per lane from global memory to LDS: lane l's go to dst + 16 l bytes
+// (dst is the same in all lanes). Complete after wait_vmem().
+__device__ __forceinline__ void lds_fill16(const uint4* src, uint32_t* dst) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(const void*)src,
+                                   (__attribute__((address_space(3))) void*)(void*)dst, 16, 0, 0);
+}
+__device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 template <int TW, int LW, int NT, bool COUNTS>
 __global__ __launch_bounds__(NT) void k_scan_allbins(ScanArgs a) {
   constexpr int G = TW / LW;       // lanes per read
@@ -372,39 +380,59 @@ __global__ __launch_bounds__(NT) void k_scan_allbins(ScanArgs a) {
   constexpr int kMaxRows = TW == 32 ? 1024 : (TW == 8 ? 4096 : 16384);
   __shared__ __attribute__((aligned(16))) uint32_t lds[(kMaxRows + 1) * TW];
 
-  // workgroup -> (read chunk, tile), XCD-aware: ids i and i+8 share an XCD
+  // Workgroup -> (read chunk, tile); ids i and i + 8 share an XCD. With chunks
+  // in eights each XCD walks the tiles of a chunk of its own, whose tokens then
+  // stay in its L2. With fewer, all XCDs walk the tiles of one chunk together,
+  // so that each still gets the same share (one chunk of 17 reads ran on a
+  // single XCD's 32 CUs: 555 us); then, in rounds of 8 * kAdj tiles, an XCD
+  // takes kAdj adjacent ones, 1 KB of each row of the index: tiles of less
+  // than a 128-byte line share their lines in its L2, and the tiles it reads at
+  // a time reach all of its L2 channels (with every eighth tile and a row
+  // length that steps 4 of the 16 channels, 12 of them idled: 194 MB in 78 us).
+  constexpr uint32_t kAdj = 256 / TW;
   const uint32_t id = blockIdx.x;
-  const uint32_t xcd = id & 7u, slot = id >> 3;
-  const uint32_t rc_local = slot / a.n_tiles;
-  const uint32_t tile = slot - rc_local * a.n_tiles;
-  const uint32_t rchunk = rc_local * 8u + xcd;
+  uint32_t rchunk, tile;
+  if (a.n_rchunks % 8u == 0) {
+    const uint32_t slot = id >> 3;
+    rchunk = slot / a.n_tiles;
+    tile = slot - rchunk * a.n_tiles;
+    rchunk = rchunk * 8u + (id & 7u);
+  } else {
+    rchunk = id / a.n_tiles;
+    tile = id - rchunk * a.n_tiles;
+    const uint32_t j = tile % (8u * kAdj);
+    if (tile - j + 8u * kAdj <= a.n_tiles) tile += (j % 8u) * kAdj + j / 8u - j;
+  }
   if (rchunk >= a.n_rchunks) return;
   const uint64_t n_reads = a.dyn ? min(a.dyn->n_reads, a.n_reads) : a.n_reads;
-  // The reads' workgroup iterations are dealt out evenly over the chunks
-  // (sizes differ by at most one iteration); with a chunk count that is a
-  // multiple of 8, every XCD gets the same share of the work.
-  constexpr uint32_t kIter = (uint32_t)(NW * RPW);
-  const uint64_t n_iter = (n_reads + kIter - 1) / kIter;
-  const uint64_t per = n_iter / a.n_rchunks, extra = n_iter % a.n_rchunks;
-  const uint64_t it0 = (uint64_t)rchunk * per + min((uint64_t)rchunk, extra);
-  const uint64_t its = per + (rchunk < extra ? 1 : 0);
-  const uint64_t r_begin = it0 * kIter;
-  uint64_t r_end = r_begin + its * kIter;
-  if (r_end > n_reads) r_end = n_reads;
-  if (r_begin >= r_end) return;
-  if (a.status && a.status[0] != 0) return;  // inputs were rejected: leave outputs untouched
+  // The reads come longest first, in groups of RPW (a wavefront's share of one
+  // step). Chunks that run side by side, `width` of them, take the groups of a
+  // stretch in turn, so that they hold the same mix of lengths and the XCDs the
+  // same work (with a run of reads each, the longest reads' chunk held its XCD
+  // up: 28000 mixed reads in 8 chunks 17.7 ms, 12.3 ms with equal shares).
+  const uint32_t width = a.n_rchunks % 8u == 0 ? 8u : a.n_rchunks;
+  const uint64_t n_all = (n_reads + RPW - 1) / RPW;
+  const uint64_t n_rows = (n_all + width - 1) / width, stretches = a.n_rchunks / width;
+  const uint64_t per = n_rows / stretches, extra = n_rows % stretches, mine = rchunk / width;
+  const uint64_t first = (mine * per + min(mine, extra)) * width + rchunk % width;
+  uint32_t n_groups = (uint32_t)(per + (mine < extra ? 1 : 0));
+  if (n_groups && first + (uint64_t)(n_groups - 1) * width >= n_all) --n_groups;
+  if (n_groups == 0) return;
+  const uint32_t rejected = a.status ? a.status[0] : 0u;
 
   // stage the tile: rows 0..R4-1 from HBM, row R4 = zeros
   const uint32_t R4 = a.R4;
   constexpr int V4 = TW / 4 > 0 ? TW / 4 : 1;
   if constexpr (TW >= 4) {
+    // straight to LDS, 16 bytes per lane: no registers hold the data, so a
+    // wavefront's loads are all in flight at once (one load per thread in
+    // flight moved 2.5 TB/s over the chip, a tile in 13 us)
     const uint4* src = reinterpret_cast<const uint4*>(a.tm);
-    uint4* dst = reinterpret_cast<uint4*>(lds);
     const uint64_t row4 = a.row_words / 4;
     const uint64_t col4 = (uint64_t)tile * TW / 4;
-    for (uint32_t i = threadIdx.x; i < R4 * V4; i += NT) {
-      const uint32_t row = i / V4, c = i % V4;
-      dst[i] = src[row * row4 + col4 + c];
+    for (uint32_t i0 = threadIdx.x & ~63u; i0 < R4 * V4; i0 += NT) {  // a wavefront's first 16 bytes
+      const uint32_t i = i0 + (threadIdx.x & 63u);
+      if (i < R4 * V4) lds_fill16(src + (i / V4) * row4 + col4 + i % V4, lds + 4 * i0);
     }
   } else {
     for (uint32_t i = threadIdx.x; i < R4 * TW; i += NT) {
@@ -418,21 +446,21 @@ __global__ __launch_bounds__(NT) void k_scan_allbins(ScanArgs a) {
   // when its last group ends rather than with its slowest wavefront's share
   __shared__ uint32_t next_group;
   if (threadIdx.x == 0) next_group = NW;
-  __syncthreads();
-
   const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
   const uint32_t g = lane / G, s = lane % G;
   const char* lds_lane = reinterpret_cast<const char*>(lds) + s * LW * 4;
   const uint64_t gw0 = (uint64_t)tile * TW + (uint64_t)s * LW;
 
-  const uint64_t n_groups = (r_end - r_begin + RPW - 1) / RPW;
+  wait_vmem();
+  __syncthreads();
+  if (rejected) return;  // inputs were rejected: leave outputs untouched
+
   for (uint32_t grp = wave; grp < n_groups;) {
-    const uint64_t base = r_begin + (uint64_t)grp * RPW;
-    const uint64_t k0 = base + g;
-    const bool active = k0 < r_end;
-    // a lane past the chunk's end takes the chunk's first read (always
-    // present) with no tokens of its own; it stores nothing
-    const uint64_t k = active ? k0 : r_begin;
+    const uint64_t k0 = (first + (uint64_t)grp * width) * RPW + g;
+    const bool active = k0 < n_reads;
+    // a lane past the last read takes the chunk's first read (always present)
+    // with no tokens of its own; it stores nothing
+    const uint64_t k = active ? k0 : first * RPW;
     const uint64_t rid = a.read_order ? a.read_order[k] : k;
     const uint32_t* tok;
     uint32_t* out_row;
@@ -468,19 +496,39 @@ __global__ __launch_bounds__(NT) void k_scan_allbins(ScanArgs a) {
   }
 }
 
+// Read chunks of a scan, of at most `most` groups of `reads` reads. Eight and
+// more come as a multiple of 8, one XCD each (49999 x 150 bp on 1480 tiles:
+// 19.6 ms, against 20.0 ms in 14 chunks shared by the XCDs). Fewer are chosen
+// for the smallest
+//   rounds of 256 workgroups x (staging a tile + the chunk's reads),
+// a staging being worth about 96 reads of 100-150 bp (6 us against 45-67 ns a
+// read and tile): the last round is then not nearly empty, and an index of few
+// tiles still fills the CUs (2000 reads on one tile ran as 8 workgroups).
+inline uint64_t chunk_count(uint64_t groups, uint64_t reads, uint64_t most, uint64_t tiles) {
+  constexpr uint64_t kCUs = 256, kStage = 96;
+  const uint64_t least = (groups + most - 1) / most;
+  if (least >= 8) return (least + 7) / 8 * 8;
+  const uint64_t last = std::min(groups, least + std::max<uint64_t>(8, kCUs / tiles));
+  uint64_t best = least, best_cost = ~0ull;
+  for (uint64_t c = least; c <= last; ++c) {
+    const uint64_t cost = (tiles * c + kCUs - 1) / kCUs * (kStage + (groups + c - 1) / c * reads);
+    if (cost < best_cost) {
+      best_cost = cost;
+      best = c;
+    }
+  }
+  return best;
+}
+
 template <int TW, int LW, int NT>
 hipError_t launch_t(ScanArgs a, uint64_t reads_per_chunk, hipStream_t s) {
-  // chunks of at most reads_per_chunk reads (whole workgroup iterations of
-  // NT / (TW / LW) reads), as many per XCD on each of the 8 XCDs
-  constexpr uint64_t kIter = (uint64_t)NT / (TW / LW);
-  const uint64_t n_iter = (a.n_reads + kIter - 1) / kIter;
-  const uint64_t it_per_chunk = reads_per_chunk / kIter > 0 ? reads_per_chunk / kIter : 1;
-  const uint64_t per_xcd = (n_iter + 8 * it_per_chunk - 1) / (8 * it_per_chunk);
-  if (per_xcd > 0x0FFFFFFFull) return hipErrorInvalidConfiguration;
-  a.n_rchunks = (uint32_t)(8 * per_xcd);
-  const uint64_t blocks = 8ull * per_xcd * a.n_tiles;
-  if (blocks == 0) return hipSuccess;
-  if (blocks > 0x7FFFFFFFull) return hipErrorInvalidConfiguration;
+  constexpr uint64_t kReads = 64 / (TW / LW);  // reads of one wavefront step
+  const uint64_t groups = (a.n_reads + kReads - 1) / kReads;
+  const uint64_t most = std::max<uint64_t>(1, reads_per_chunk / kReads);
+  const uint64_t chunks = chunk_count(groups, kReads, most, a.n_tiles);
+  if (chunks > 0x7FFFFFFFull / a.n_tiles) return hipErrorInvalidConfiguration;
+  a.n_rchunks = (uint32_t)chunks;
+  const uint64_t blocks = chunks * a.n_tiles;
   // the per-bin count output is compiled only into its own instance: without
   // it the kernel fits 126 registers with no spills (1.5% faster on the
   // human-scale scan, and 36 GB less of scratch traffic per launch)
