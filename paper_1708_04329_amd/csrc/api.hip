@@ -135,6 +135,7 @@ void free_workspace(grim_workspace& ws) {
   if (ws.vbucket_host) (void)hipHostFree(ws.vbucket_host);
   if (ws.vitem_pair) (void)hipFree(ws.vitem_pair);
   if (ws.vitem_read) (void)hipFree(ws.vitem_read);
+  if (ws.vitem_span) (void)hipFree(ws.vitem_span);
   if (ws.vread_sel) (void)hipFree(ws.vread_sel);
   if (ws.vchunk_sum) (void)hipFree(ws.vchunk_sum);
   ws = grim_workspace{};
@@ -187,11 +188,11 @@ int check_reads_args(const grim_index* idx, const grim_reads* rd) {
 
 // Tokenise + thresholds into the index workspace; leaves status zeroed first.
 int tokenize_reads(grim_index* idx, const grim_reads* rd, const ReadView& v, uint32_t max_tokens,
-                   uint32_t tok_shift, hipStream_t s, ProfSpan& ps) {
+                   uint32_t tok_shift, hipStream_t s, ProfSpan& ps, bool want_tokens = true) {
   grim_workspace& ws = idx->ws;
   int rc = ensure_status(ws);
   if (rc) return rc;
-  rc = grow(&ws.tokens, &ws.tokens_cap, token_capacity(rd->n_bases, rd->n_reads));
+  if (want_tokens) rc = grow(&ws.tokens, &ws.tokens_cap, token_capacity(rd->n_bases, rd->n_reads));
   if (rc) return rc;
   rc = grow(&ws.thr, &ws.thr_cap, rd->n_reads + 1);
   if (rc) return rc;
@@ -209,13 +210,13 @@ int tokenize_reads(grim_index* idx, const grim_reads* rd, const ReadView& v, uin
   a.flags = rd->flags;
   a.max_tokens = max_tokens;
   a.tok_shift = tok_shift;
-  // plain codes (no shift) serve the candidate and verification calls, which
-  // read a read's entries only up to its token count; the scans' shifted
-  // entries keep the padding their last block reads
+  // plain codes (no shift) serve the candidate calls, which read a read's
+  // entries only up to its token count; the scans' shifted entries keep the
+  // padding their last block reads
   a.short_pad = tok_shift == 0 ? 1u : 0u;
   // 128-byte tile rows: the all-bins scan reads tokens in pair order
   a.pair_order = tok_shift == 7 ? 1u : 0u;
-  a.tokens = ws.tokens;
+  a.tokens = want_tokens ? ws.tokens : nullptr;
   a.thr = ws.thr;
   a.status = ws.status;
   ps.start(s);
@@ -323,7 +324,7 @@ int fill_geometry(grim_index* idx, uint64_t G, uint32_t B, uint32_t O, uint32_t 
 int alloc_layouts(grim_index* idx) {
   if (idx->tm_bytes) GRIM_HIP_TRY(hipMalloc(&idx->tm, idx->tm_bytes));
   if (idx->bm_bytes) GRIM_HIP_TRY(hipMalloc(&idx->bm, idx->bm_bytes));
-  if (idx->ref_bytes) GRIM_HIP_TRY(hipMalloc(&idx->ref, idx->ref_bytes));
+  if (idx->ref_bytes) GRIM_HIP_TRY(hipMalloc(&idx->ref, idx->ref_bytes + kRefTail));
   return GRIM_OK;
 }
 
@@ -687,7 +688,7 @@ int verify_impl(const grim_index* cidx, const grim_reads* rd, const int64_t* can
   rc = stage_reads(idx, rd, s, &v);
   if (rc) return rc;
   ProfSpan pt(PROF_TOKENIZE);
-  rc = tokenize_reads(idx, rd, v, 65535u, 0u, s, pt);  // length checks and thresholds
+  rc = tokenize_reads(idx, rd, v, 65535u, 0u, s, pt, false);  // length checks and thresholds
   if (rc) return rc;
   grim_workspace& ws = idx->ws;
   if (!ws.vbucket) GRIM_HIP_TRY(hipMalloc(&ws.vbucket, kVerifyBuckets * sizeof(uint64_t)));
@@ -719,6 +720,7 @@ int verify_impl(const grim_index* cidx, const grim_reads* rd, const int64_t* can
   a.read_sel = ws.vread_sel;
   a.chunk_sum = ws.vchunk_sum;
   a.bounded = bounded ? 1u : 0u;
+  a.chunk = verify_chunk_reads(rd->n_reads);
   GRIM_HIP_TRY(launch_verify_count(a, s));
   // pairs per length class, and the status of the inputs
   uint64_t* counts = ws.vbucket_host;
@@ -739,14 +741,20 @@ int verify_impl(const grim_index* cidx, const grim_reads* rd, const int64_t* can
   if (rc) return rc;
   a.item_pair = ws.vitem_pair;
   a.item_read = ws.vitem_read;
+  if (bounded) {
+    rc = grow(&ws.vitem_span, &ws.vitem_span_cap, total);
+    if (rc) return rc;
+    a.item_span = ws.vitem_span;
+  }
   GRIM_HIP_TRY(launch_verify_scatter(a, s));
   ProfSpan pv(PROF_VERIFY);
   pv.start(s);
+  if (bounded) GRIM_HIP_TRY(launch_verify_sift(a, total, s));
   for (uint32_t w = 1; w < kVerifyBuckets; ++w) GRIM_HIP_TRY(launch_verify_align(a, w, first[w], counts[w], s));
   pv.stop(s);
-  rc = finish_status(idx, s);
+  GRIM_HIP_TRY(hipStreamSynchronize(s));  // the inputs' status is known: nothing after the count sets it
   pv.collect();
-  return rc;
+  return GRIM_OK;
 }
 
 }  // namespace

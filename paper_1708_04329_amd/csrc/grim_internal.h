@@ -99,7 +99,7 @@ struct TokArgs {
                         // checks read no further); 0: past the next multiple of 32 (scans)
   uint32_t pair_order;  // 1: order each read's tokens by the parity of their row (the
                         // all-bins scan with 128-byte tile rows; see launch_tokenize)
-  uint32_t* tokens;
+  uint32_t* tokens;     // null: checks and thresholds only
   int32_t* thr;
   uint32_t* status;
 };
@@ -124,7 +124,6 @@ hipError_t launch_ref_codes(const uint8_t* ref, uint64_t G, uint8_t* codes, hipS
 // of the read against the bases of the bin's extent.
 constexpr uint32_t kVerifyMaxLen = 512;   // bases per read: 16 words of 32 rows
 constexpr uint32_t kVerifyBuckets = 17;   // work lists by words per read, 1..16
-constexpr uint32_t kVerifyChunk = 2048;   // reads per workgroup of the list passes
 struct VerifyArgs {
   const uint8_t* ref;        // base codes, G bytes
   uint64_t G;
@@ -143,18 +142,25 @@ struct VerifyArgs {
   uint32_t* status;
   uint64_t* bucket;          // [kVerifyBuckets] pairs to align per class
   uint32_t* read_sel;        // [n_reads] pairs selected per read (first pass)
+  uint32_t chunk;            // reads per chunk: verify_chunk_reads(n_reads)
   uint64_t* chunk_sum;       // [chunks][kVerifyBuckets] pair counts, then first slots
   uint64_t* item_pair;       // work list: pair index
   uint32_t* item_read;       //            and its read
-  uint32_t bounded;          // 1: distances above E_r reported as E_r + 1 (Ukkonen's cutoff)
+  uint2* item_span;          // bounded: where an alignment within E_r may lie, per work item
+  uint32_t bounded;          // 1: distances above E_r reported as E_r + 1
 };
-// Chunks of reads of the list passes.
+// Reads per chunk of the list passes, and the chunks.
+uint32_t verify_chunk_reads(uint64_t n_reads);
 uint64_t verify_chunks(uint64_t n_reads);
 // Count the pairs to align per class into a.bucket and per chunk (and write
 // the outputs of skipped pairs); list positions follow classes in order.
 hipError_t launch_verify_count(const VerifyArgs& a, hipStream_t s);
 // Fill the work list from the counts and positions of launch_verify_count.
 hipError_t launch_verify_scatter(const VerifyArgs& a, hipStream_t s);
+// Bounded form: find the items (of all `count`) that can be within their budget
+// (item_span) and write the outputs of the others.
+hipError_t launch_verify_sift(const VerifyArgs& a, uint64_t count, hipStream_t s);
+constexpr uint64_t kRefTail = 64;  // bytes past the reference copy that the sift may read
 // Align work items [first, first + count), all of whose reads have `words`
 // 32-base words.
 hipError_t launch_verify_align(const VerifyArgs& a, uint32_t words, uint64_t first, uint64_t count,
@@ -302,6 +308,8 @@ struct grim_workspace {
   uint64_t* vitem_pair = nullptr;    // verification work list
   uint32_t* vitem_read = nullptr;
   uint64_t vitem_cap = 0, vitem_read_cap = 0;
+  uint2* vitem_span = nullptr;       // bounded verification: where to align
+  uint64_t vitem_span_cap = 0;
   uint32_t* vread_sel = nullptr;     // pairs selected per read
   uint64_t vread_sel_cap = 0;
   uint64_t* vchunk_sum = nullptr;    // per-chunk class counts / first slots

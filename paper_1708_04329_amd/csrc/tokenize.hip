@@ -40,6 +40,44 @@ __device__ __forceinline__ uint32_t lane_u32(uint32_t v, uint32_t k) {
   return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)k);
 }
 
+// Checks of read r, its budget and threshold (written to a.thr); flags what is
+// wrong in the status word and returns it. *ntok: its tokens.
+__device__ __forceinline__ uint32_t check_read(const TokArgs& a, uint64_t r, uint64_t n_bases, int64_t q, int64_t* start,
+                                               int64_t* tokens) {
+  const int64_t o0 = a.offsets[r], o1 = a.offsets[r + 1];
+  uint32_t err = 0;
+  int64_t L = o1 - o0;
+  if (o0 < 0 || o1 < o0 || (uint64_t)o1 > n_bases) { err |= ST_BAD_LENGTH; L = 0; }
+  if (L < q) err |= ST_BAD_LENGTH;
+  const int64_t ntok = L >= q ? L - q + 1 : 0;
+  if (ntok > 65535) err |= ST_TOO_LONG;
+  if (ntok > (int64_t)a.max_tokens) err |= ST_COUNT_U8;
+  uint64_t E;
+  if (a.max_edits) E = a.max_edits[r];
+  else {
+    const uint64_t e = a.err_pm ? a.err_pm[r] : a.err_pm_all;
+    E = ((uint64_t)L * e + 999u) / 1000u;
+  }
+  if (!(a.flags & GRIM_READS_ALLOW_SHORT_OVERLAP) && L + (int64_t)E - q > (int64_t)a.overlap)
+    err |= ST_OVERLAP;
+  int64_t T = (L - q + 1) - q * (int64_t)E;
+  if (T < -(1 << 30)) T = -(1 << 30);
+  a.thr[r] = (int32_t)T;
+  if (err) atomicOr(a.status, err);
+  *start = o0;
+  *tokens = ntok;
+  return err;
+}
+
+// The checks and thresholds alone, a thread per read.
+__global__ __launch_bounds__(256) void k_thresholds(TokArgs a) {
+  const uint64_t r = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const uint64_t n_reads = a.dyn ? min(a.dyn->n_reads, a.n_reads) : a.n_reads;
+  const uint64_t n_bases = a.dyn ? min(a.dyn->n_bases, a.n_bases) : a.n_bases;
+  int64_t o0, ntok;
+  if (r < n_reads) (void)check_read(a, r, n_bases, (int64_t)a.q, &o0, &ntok);
+}
+
 template <int Q>
 __global__ __launch_bounds__(256) void k_tokenize(TokArgs a) {
   const uint32_t lane = threadIdx.x & 63u;
@@ -53,26 +91,8 @@ __global__ __launch_bounds__(256) void k_tokenize(TokArgs a) {
   uint32_t ntok_read = 0, npad_read = 0;
   const uint64_t r = r0 + lane;
   if (lane < kTokReads && r < n_reads) {
-    const int64_t o0 = a.offsets[r], o1 = a.offsets[r + 1];
-    uint32_t err = 0;
-    int64_t L = o1 - o0;
-    if (o0 < 0 || o1 < o0 || (uint64_t)o1 > n_bases) { err |= ST_BAD_LENGTH; L = 0; }
-    if (L < (int64_t)Q) err |= ST_BAD_LENGTH;
-    const int64_t ntok = L >= (int64_t)Q ? L - Q + 1 : 0;
-    if (ntok > 65535) err |= ST_TOO_LONG;
-    if (ntok > (int64_t)a.max_tokens) err |= ST_COUNT_U8;
-    uint64_t E;
-    if (a.max_edits) E = a.max_edits[r];
-    else {
-      const uint64_t e = a.err_pm ? a.err_pm[r] : a.err_pm_all;
-      E = ((uint64_t)L * e + 999u) / 1000u;
-    }
-    if (!(a.flags & GRIM_READS_ALLOW_SHORT_OVERLAP) && L + (int64_t)E - (int64_t)Q > (int64_t)a.overlap)
-      err |= ST_OVERLAP;
-    int64_t T = (L - (int64_t)Q + 1) - (int64_t)Q * (int64_t)E;
-    if (T < -(1 << 30)) T = -(1 << 30);
-    a.thr[r] = (int32_t)T;
-    if (err) atomicOr(a.status, err);
+    int64_t o0, ntok;
+    const uint32_t err = check_read(a, r, n_bases, Q, &o0, &ntok);
     if (!(err & (ST_BAD_LENGTH | ST_TOO_LONG))) {
       o_read = (uint64_t)o0;
       ntok_read = (uint32_t)ntok;
@@ -201,6 +221,11 @@ __global__ __launch_bounds__(256) void k_pair_order(TokArgs a) {
 // With a.dyn set, a.n_reads / a.n_bases are the capacities the grid is sized for.
 hipError_t launch_tokenize(const TokArgs& a, hipStream_t s) {
   if (a.n_reads == 0) return hipSuccess;
+  if (!a.tokens) {
+    if (a.n_reads > 0x7FFFFFFFull * 256) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL(k_thresholds, dim3((unsigned)((a.n_reads + 255) / 256)), dim3(256), 0, s, a);
+    return hipGetLastError();
+  }
   // entries are written with 16-byte stores
   if (reinterpret_cast<uintptr_t>(a.tokens) & 15u) return hipErrorInvalidValue;
   const uint64_t reads_per_block = 4ull * kTokReads;
