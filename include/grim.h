@@ -13,6 +13,11 @@
  *     last failure on the calling thread.
  *   - The caller owns every input and output buffer. The library owns
  *     grim_index handles and frees them in grim_index_free.
+ *   - Device memory freed within 2 s of its allocation (a loop that builds, uses
+ *     and frees handles; a build's temporaries) is kept for the next handles, at
+ *     most 12 GiB per device; blocks idle for 10 s go back to the driver at the
+ *     next call that allocates or frees, all of them when an allocation of the
+ *     library fails or a server or batcher is created.
  *   - "device" buffers are HIP device memory on the device that holds the
  *     index; "host" buffers are ordinary process memory.
  *   - hip_stream is a hipStream_t passed as void* (NULL = the null stream).

@@ -106,38 +106,28 @@ int check_device(int dev) {
 template <typename T>
 int grow(T** p, uint64_t* cap, uint64_t need) {
   if (*cap >= need && *p) return GRIM_OK;
-  if (*p) (void)hipFree(*p);
+  pool_free(*p);  // calls wait for their work: the last one's is complete
   *p = nullptr;
   *cap = 0;
   uint64_t n = need + need / 4 + 256;
-  void* q = nullptr;
-  GRIM_HIP_TRY(hipMalloc(&q, n * sizeof(T)));
-  *p = static_cast<T*>(q);
+  GRIM_HIP_TRY(pool_alloc(p, n * sizeof(T)));
   *cap = n;
   return GRIM_OK;
 }
 
 int ensure_status(grim_workspace& ws) {
-  if (!ws.status) GRIM_HIP_TRY(hipMalloc(&ws.status, 8 * sizeof(uint32_t)));
+  if (!ws.status) GRIM_HIP_TRY(pool_alloc(&ws.status, 8 * sizeof(uint32_t)));
   if (!ws.status_host) GRIM_HIP_TRY(hipHostMalloc(&ws.status_host, 8 * sizeof(uint32_t), hipHostMallocDefault));
   return GRIM_OK;
 }
 
 void free_workspace(grim_workspace& ws) {
-  if (ws.tokens) (void)hipFree(ws.tokens);
-  if (ws.thr) (void)hipFree(ws.thr);
-  if (ws.status) (void)hipFree(ws.status);
+  for (void* p : {(void*)ws.tokens, (void*)ws.thr, (void*)ws.status, (void*)ws.staging, (void*)ws.order, (void*)ws.hist,
+                  (void*)ws.vbucket, (void*)ws.vitem_pair, (void*)ws.vitem_read, (void*)ws.vitem_span,
+                  (void*)ws.vread_sel, (void*)ws.vchunk_sum})
+    pool_free(p);
   if (ws.status_host) (void)hipHostFree(ws.status_host);
-  if (ws.staging) (void)hipFree(ws.staging);
-  if (ws.order) (void)hipFree(ws.order);
-  if (ws.hist) (void)hipFree(ws.hist);
-  if (ws.vbucket) (void)hipFree(ws.vbucket);
   if (ws.vbucket_host) (void)hipHostFree(ws.vbucket_host);
-  if (ws.vitem_pair) (void)hipFree(ws.vitem_pair);
-  if (ws.vitem_read) (void)hipFree(ws.vitem_read);
-  if (ws.vitem_span) (void)hipFree(ws.vitem_span);
-  if (ws.vread_sel) (void)hipFree(ws.vread_sel);
-  if (ws.vchunk_sum) (void)hipFree(ws.vchunk_sum);
   ws = grim_workspace{};
 }
 
@@ -322,18 +312,19 @@ int fill_geometry(grim_index* idx, uint64_t G, uint32_t B, uint32_t O, uint32_t 
 }
 
 int alloc_layouts(grim_index* idx) {
-  if (idx->tm_bytes) GRIM_HIP_TRY(hipMalloc(&idx->tm, idx->tm_bytes));
-  if (idx->bm_bytes) GRIM_HIP_TRY(hipMalloc(&idx->bm, idx->bm_bytes));
-  if (idx->ref_bytes) GRIM_HIP_TRY(hipMalloc(&idx->ref, idx->ref_bytes + kRefTail));
+  if (idx->tm_bytes) GRIM_HIP_TRY(pool_alloc(&idx->tm, idx->tm_bytes));
+  if (idx->bm_bytes) GRIM_HIP_TRY(pool_alloc(&idx->bm, idx->bm_bytes));
+  if (idx->ref_bytes) GRIM_HIP_TRY(pool_alloc(&idx->ref, idx->ref_bytes + kRefTail));
   return GRIM_OK;
 }
 
 void destroy(grim_index* idx) {
   if (!idx) return;
   DeviceGuard dg(idx->device);
-  if (idx->tm) (void)hipFree(idx->tm);
-  if (idx->bm) (void)hipFree(idx->bm);
-  if (idx->ref) (void)hipFree(idx->ref);
+  (void)hipDeviceSynchronize();  // the pool's blocks may go to any stream next
+  pool_free(idx->tm);
+  pool_free(idx->bm);
+  pool_free(idx->ref);
   free_workspace(idx->ws);
   delete idx;
 }
@@ -396,10 +387,11 @@ int grim_build_index(const uint8_t* ref, uint64_t ref_len, uint32_t ref_on_devic
   const uint8_t* dref = ref;
   void* staging = nullptr;
   if (!ref_on_device) {
-    GRIM_HIP_TRY(hipMalloc(&staging, ref_len));
+    GRIM_HIP_TRY(pool_alloc(&staging, ref_len));
     hipError_t e = hipMemcpyAsync(staging, ref, ref_len, hipMemcpyHostToDevice, s);
     if (e != hipSuccess) {
-      (void)hipFree(staging);
+      (void)hipDeviceSynchronize();
+      pool_free(staging);
       return set_error(GRIM_EDEVICE, "reference copy failed: %s", hipGetErrorString(e));
     }
     dref = static_cast<const uint8_t*>(staging);
@@ -426,7 +418,8 @@ int grim_build_index(const uint8_t* ref, uint64_t ref_len, uint32_t ref_on_devic
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     ps.collect();
   }
-  if (staging) (void)hipFree(staging);
+  if (e != hipSuccess) (void)hipDeviceSynchronize();
+  pool_free(staging);
   if (e != hipSuccess) return set_error(GRIM_EDEVICE, "index build failed: %s", hipGetErrorString(e));
   *out = idx.release();
   return GRIM_OK;
@@ -603,7 +596,7 @@ int grim_filter_scan(const grim_index* cidx, const grim_reads* rd, uint32_t* mas
   if (cfg.sort_by_length) {
     rc = grow(&idx->ws.order, &idx->ws.order_cap, rd->n_reads);
     if (rc) return rc;
-    if (!idx->ws.hist) GRIM_HIP_TRY(hipMalloc(&idx->ws.hist, length_order_scratch_words() * sizeof(uint32_t)));
+    if (!idx->ws.hist) GRIM_HIP_TRY(pool_alloc(&idx->ws.hist, length_order_scratch_words() * sizeof(uint32_t)));
     GRIM_HIP_TRY(launch_length_order(v.offsets, rd->n_reads, idx->q, nullptr, idx->ws.hist, idx->ws.order, s));
     a.read_order = idx->ws.order;
   }
@@ -691,7 +684,7 @@ int verify_impl(const grim_index* cidx, const grim_reads* rd, const int64_t* can
   rc = tokenize_reads(idx, rd, v, 65535u, 0u, s, pt, false);  // length checks and thresholds
   if (rc) return rc;
   grim_workspace& ws = idx->ws;
-  if (!ws.vbucket) GRIM_HIP_TRY(hipMalloc(&ws.vbucket, kVerifyBuckets * sizeof(uint64_t)));
+  if (!ws.vbucket) GRIM_HIP_TRY(pool_alloc(&ws.vbucket, kVerifyBuckets * sizeof(uint64_t)));
   if (!ws.vbucket_host)
     GRIM_HIP_TRY(hipHostMalloc(&ws.vbucket_host, 2 * kVerifyBuckets * sizeof(uint64_t), hipHostMallocDefault));
   rc = grow(&ws.vread_sel, &ws.vread_sel_cap, rd->n_reads);

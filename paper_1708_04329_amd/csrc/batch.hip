@@ -51,7 +51,10 @@ struct DevBuf {
   ~DevBuf() {
     if (p) (void)hipFree(p);
   }
-  hipError_t alloc(uint64_t n) { return hipMalloc(reinterpret_cast<void**>(&p), std::max<uint64_t>(n, 1) * sizeof(T)); }
+  hipError_t alloc(uint64_t n) {
+    pool_trim();
+    return hipMalloc(reinterpret_cast<void**>(&p), std::max<uint64_t>(n, 1) * sizeof(T));
+  }
 };
 
 // ------------------------------ tune cache --------------------------------
@@ -570,6 +573,7 @@ extern "C" int grim_batcher_create(const grim_index* idx, uint32_t mode, uint64_
   if (edits_kind > GRIM_BATCH_EDITS_ERR) return set_error(GRIM_EINVAL, "bad edits_kind");
   if (flags & ~GRIM_READS_ALLOW_SHORT_OVERLAP) return set_error(GRIM_EINVAL, "unknown flags");
   DeviceGuard dg(idx->device);
+  pool_trim();  // its buffers are the driver's: idle memory of this library is free memory
   auto* b = new grim_batcher;
   b->idx = idx;
   b->mode = mode;

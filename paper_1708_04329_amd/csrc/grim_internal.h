@@ -26,6 +26,16 @@ void clear_error();
                                "%s failed: %s", #expr, hipGetErrorString(_e));      \
   } while (0)
 
+// Device memory on the current device from and to the library's pool (pool.hip).
+// pool_free: after every use of the block on any stream is complete.
+hipError_t pool_alloc(void** out, size_t bytes);
+void pool_free(void* p);
+void pool_trim();  // idle blocks of the current device back to the driver
+template <typename T>
+hipError_t pool_alloc(T** out, size_t bytes) {
+  return pool_alloc(reinterpret_cast<void**>(out), bytes);
+}
+
 // Device status words written by kernels (status[0] holds error bits).
 enum : uint32_t {
   ST_BAD_LENGTH = 1u,      // L < q or offsets out of order / out of range

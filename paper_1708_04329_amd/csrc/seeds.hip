@@ -1066,13 +1066,11 @@ hipError_t launch_fill_word(uint32_t* p, uint32_t v, hipStream_t s) {
 template <typename T>
 int grow_dev(T** p, uint64_t* cap, uint64_t need) {
   if (*cap >= need && *p) return GRIM_OK;
-  if (*p) (void)hipFree(*p);
+  pool_free(*p);  // calls wait for their work: the last one's is complete
   *p = nullptr;
   *cap = 0;
   const uint64_t n = need + need / 8 + 64;
-  void* q = nullptr;
-  GRIM_HIP_TRY(hipMalloc(&q, n * sizeof(T)));
-  *p = static_cast<T*>(q);
+  GRIM_HIP_TRY(pool_alloc(p, n * sizeof(T)));
   *cap = n;
   return GRIM_OK;
 }
@@ -1080,10 +1078,11 @@ int grow_dev(T** p, uint64_t* cap, uint64_t need) {
 void free_seeds(grim_seeds* sd) {
   if (!sd) return;
   SeedGuard g(sd->device);
+  (void)hipDeviceSynchronize();  // the pool's blocks may go to any stream next
   for (void* p : {(void*)sd->start, (void*)sd->pos, (void*)sd->hits, (void*)sd->words, (void*)sd->tmp,
                   (void*)sd->toff, (void*)sd->outoff, (void*)sd->bsum, (void*)sd->cnt, (void*)sd->list,
                   (void*)sd->redo, (void*)sd->slab, (void*)sd->staging})
-    if (p) (void)hipFree(p);
+    pool_free(p);
   for (void* p : {(void*)sd->hits_host, (void*)sd->total_host, (void*)sd->toff_host, (void*)sd->list_host})
     if (p) (void)hipHostFree(p);
   delete sd;
@@ -1159,23 +1158,22 @@ int grim_seeds_build(const uint8_t* ref, uint64_t ref_len, uint32_t ref_on_devic
   uint32_t* counts = nullptr;
   void* tmp = nullptr;
   auto cleanup = [&]() {
-    if (staging) (void)hipFree(staging);
-    if (counts) (void)hipFree(counts);
-    if (tmp) (void)hipFree(tmp);
+    for (void* p : {(void*)staging, (void*)counts, tmp}) pool_free(p);
   };
   auto fail = [&](hipError_t e, const char* what) {
+    (void)hipDeviceSynchronize();  // some of the work may be on its way
     cleanup();
     return set_error(e == hipErrorOutOfMemory ? GRIM_ENOMEM : GRIM_EDEVICE, "%s: %s", what, hipGetErrorString(e));
   };
   hipError_t e;
   if (!ref_on_device) {
-    if ((e = hipMalloc(&staging, ref_len)) != hipSuccess) return fail(e, "reference staging");
+    if ((e = pool_alloc(&staging, ref_len)) != hipSuccess) return fail(e, "reference staging");
     if ((e = hipMemcpyAsync(staging, ref, ref_len, hipMemcpyHostToDevice, s)) != hipSuccess)
       return fail(e, "reference copy");
     dref = staging;
   }
-  if ((e = hipMalloc(&counts, (sd->nk + 1) * sizeof(uint32_t))) != hipSuccess) return fail(e, "k-mer counts");
-  if ((e = hipMalloc(&sd->start, (sd->nk + 1) * sizeof(uint64_t))) != hipSuccess) return fail(e, "k-mer starts");
+  if ((e = pool_alloc(&counts, (sd->nk + 1) * sizeof(uint32_t))) != hipSuccess) return fail(e, "k-mer counts");
+  if ((e = pool_alloc(&sd->start, (sd->nk + 1) * sizeof(uint64_t))) != hipSuccess) return fail(e, "k-mer starts");
   if ((e = launch_zero_words(counts, (uint32_t)(sd->nk + 1), s)) != hipSuccess) return fail(e, "zero counts");
   const uint64_t threads = (ref_len + kSpan - 1) / kSpan;
   const uint64_t blocks = (threads + 255) / 256;
@@ -1183,7 +1181,7 @@ int grim_seeds_build(const uint8_t* ref, uint64_t ref_len, uint32_t ref_on_devic
   hipLaunchKernelGGL(vec ? k_kmer_count<true> : k_kmer_count<false>, dim3((unsigned)blocks), dim3(256), 0, s, dref,
                      ref_len, k, counts);
   if ((e = hipGetLastError()) != hipSuccess) return fail(e, "k-mer count");
-  if ((e = hipMalloc(&tmp, (scan_blocks(sd->nk + 1) + 1) * sizeof(uint64_t))) != hipSuccess)
+  if ((e = pool_alloc(&tmp, (scan_blocks(sd->nk + 1) + 1) * sizeof(uint64_t))) != hipSuccess)
     return fail(e, "scan storage");
   if ((e = launch_scan(counts, sd->nk + 1, sd->start, static_cast<uint64_t*>(tmp), nullptr, nullptr, s)) !=
       hipSuccess)
@@ -1193,7 +1191,7 @@ int grim_seeds_build(const uint8_t* ref, uint64_t ref_len, uint32_t ref_on_devic
     return fail(e, "position count");
   if ((e = hipStreamSynchronize(s)) != hipSuccess) return fail(e, "position count");
   sd->n_pos = n_pos;
-  if ((e = hipMalloc(&sd->pos, std::max<uint64_t>(n_pos, 1) * sizeof(uint32_t))) != hipSuccess)
+  if ((e = pool_alloc(&sd->pos, std::max<uint64_t>(n_pos, 1) * sizeof(uint32_t))) != hipSuccess)
     return fail(e, "positions");
   hipLaunchKernelGGL(vec ? k_kmer_fill<true> : k_kmer_fill<false>, dim3((unsigned)blocks), dim3(256), 0, s, dref,
                      ref_len, k, sd->start, counts, sd->pos);
@@ -1261,7 +1259,7 @@ int grim_seed_candidates(const grim_seeds* csd, const grim_reads* rd, uint32_t b
     GRIM_HIP_TRY(hipHostMalloc(&sd->hits_host, sd->hits_cap * sizeof(uint64_t), hipHostMallocDefault));
     sd->hits_host_cap = sd->hits_cap;
   }
-  if (!sd->words) GRIM_HIP_TRY(hipMalloc(&sd->words, 8 * sizeof(uint64_t)));
+  if (!sd->words) GRIM_HIP_TRY(pool_alloc(&sd->words, 8 * sizeof(uint64_t)));
   uint32_t* bad = reinterpret_cast<uint32_t*>(sd->words + 2);
   uint32_t* n_redo = reinterpret_cast<uint32_t*>(sd->words + 3);
   GRIM_HIP_TRY(launch_zero_words(reinterpret_cast<uint32_t*>(sd->words), 16, s));  // base, bad, n_redo
@@ -1437,7 +1435,7 @@ int grim_reverse_complement(const uint8_t* bases, uint64_t n_bases, const int64_
   if (n_reads > (1ull << 36)) return set_error(GRIM_EINVAL, "too many reads");
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   uint32_t* bad = nullptr;  // set by the kernel when a read's offsets are out of order or out of range
-  GRIM_HIP_TRY(hipMalloc(&bad, sizeof(uint32_t)));
+  GRIM_HIP_TRY(pool_alloc(&bad, sizeof(uint32_t)));
   uint32_t bad_host = 0;
   hipError_t e = hipMemsetAsync(bad, 0, sizeof(uint32_t), s);
   if (e == hipSuccess) {
@@ -1447,7 +1445,8 @@ int grim_reverse_complement(const uint8_t* bases, uint64_t n_bases, const int64_
   }
   if (e == hipSuccess) e = hipMemcpyAsync(&bad_host, bad, sizeof(uint32_t), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
-  (void)hipFree(bad);
+  if (e != hipSuccess) (void)hipDeviceSynchronize();
+  pool_free(bad);
   GRIM_HIP_TRY(e);
   if (bad_host) return set_error(GRIM_EINVAL, "offsets out of order or outside [0, n_bases]; those reads were not written");
   return GRIM_OK;

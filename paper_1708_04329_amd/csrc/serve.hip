@@ -559,6 +559,7 @@ extern "C" int grim_serve_create(const grim_index* idx, const grim_serve_config*
     release_all(S.get());
     return set_error(code, "%s: %s", what, hipGetErrorString(e));
   };
+  pool_trim();  // idle memory of this library is free memory
   if (!c.arena_bytes) {
     size_t fr = 0, tot = 0;
     hipError_t e = hipMemGetInfo(&fr, &tot);
