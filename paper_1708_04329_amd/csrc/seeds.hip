@@ -4,9 +4,12 @@
 //
 // Seed table. Every reference position p whose k bases are A, C, G or T is
 // listed under the code of its k-mer: start[c] .. start[c + 1] index the
-// positions of code c in pos[]. Built with one counting pass (atomic adds on
-// the 4^k counters), an exclusive scan, and one filling pass that hands out
-// slots by counting down.
+// positions of code c in pos[]. Built by partitions of the codes (their high
+// bits): positions are written partition by partition, then each partition is
+// sorted by the rest of the code in one workgroup's LDS. Where the partitioned
+// copy does not fit in memory: one counting pass (atomic adds on the 4^k
+// counters), an exclusive scan, and one filling pass that hands out slots by
+// counting down.
 //
 // Candidates. A read's seeds are its non-overlapping k-mers at offsets 0, k,
 // 2k, ...; a seed at offset o found at p votes for bin max(p - o, 0) / B. The
@@ -115,13 +118,12 @@ __device__ __forceinline__ void for_kmers(const uint8_t* ref, uint64_t G, uint32
   }
 }
 
-// The same walk with the thread's bytes loaded up front: 80 bytes in five 16-byte loads (64
-// start positions plus up to 13 more bases for k <= 14), the bases then coded without
-// branches. Needs a 16-byte aligned reference; a thread whose 80 bytes run past the end takes
-// the byte-wise walk.
+// The same walk with the thread's bytes loaded up front, in 16-byte loads (64 start positions
+// plus up to 13 more bases for k <= 14), the bases then coded without branches. Needs a
+// 16-byte aligned reference; a thread whose bytes run past the end takes the byte-wise walk.
 template <typename F>
 __device__ __forceinline__ void for_kmers_vec(const uint8_t* ref, uint64_t G, uint32_t k, uint64_t p0, F f) {
-  constexpr uint32_t kBytes = 80;
+  constexpr uint32_t kBytes = kSpan + 16;
   if (p0 + kBytes > G) {
     for_kmers(ref, G, k, p0, f);
     return;
@@ -320,6 +322,266 @@ hipError_t launch_scan(const uint32_t* in, uint64_t n, uint64_t* out, uint64_t* 
   if (e != hipSuccess || !nblk) return e;
   hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nblk), dim3(kScanT), 0, s, in, n, bsum, out);
   return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// Table build by partitions. Random atomics and stores over the 4^k counters
+// and the positions took 115 + 181 ms for 3.1 Gbp, 3.7 + 5.4 ms for 100 Mbp (27 G
+// a second); here the random accesses are to LDS. The reference's tiles of 32768
+// positions are dealt in runs to up to 256 streams, a workgroup each:
+//   1. k_part_count: positions per (partition, stream);
+//   2. a scan makes them the streams' first slots, partition after partition;
+//   3. k_part_tile: a tile's positions sorted by partition in LDS, and each
+//      partition's run (8 positions) written by neighbouring lanes to the
+//      stream's next slots. For more partitions than its LDS holds (k = 13, 14):
+//      k_part_scatter, every position to its slot by itself;
+//   4. k_part_sort: per partition, LDS counts of the low bits, their scan (the
+//      table's starts), and the positions to their places, through LDS where
+//      the partition fits.
+// Bound by the partial lines of step 3's runs and, where a partition does not
+// fit in LDS, of step 4's stores. 100 Mbp: 0.11 + 0.62 + 0.40 ms (every position
+// to its slot by itself: 2.5 ms in step 3; slots reserved with an atomic per tile
+// and partition: 0.90).
+// ---------------------------------------------------------------------------
+constexpr uint32_t kTileT = 1024;  // threads per tile
+constexpr uint32_t kTileSpan = 32;
+constexpr uint64_t kTile = (uint64_t)kTileT * kTileSpan;  // reference positions per tile
+constexpr uint32_t kStreams = 256;                        // at most: a workgroup per CU
+constexpr uint64_t kPartMost = 1ull << 30;                // bytes of the partitioned copy
+
+// Partition bits: at most 2^14 LDS counters here and for the bits that are left.
+uint32_t part_bits(uint32_t k) { return std::min(2 * k, std::max(12u, k)); }
+
+// The tiles of stream w of n.
+__device__ __forceinline__ uint64_t stream_tile(uint64_t tiles, uint32_t w, uint32_t n) { return tiles * w / n; }
+
+// The k-mers that start at a thread's kTileSpan positions of a tile: code[i] is
+// the one that ends at base i of its 48, if bit i of the result is set.
+constexpr uint32_t kTileBases = kTileSpan + 16;
+template <bool VEC>
+__device__ __forceinline__ uint64_t tile_codes(const uint8_t* ref, uint64_t G, uint32_t k, uint64_t tile,
+                                               uint32_t (&code)[kTileBases]) {
+  const uint64_t p0 = tile * kTile + (uint64_t)threadIdx.x * kTileSpan;
+  uint32_t w[kTileBases / 4];
+  if (VEC && p0 + kTileBases <= G) {
+    const uint4* src = reinterpret_cast<const uint4*>(ref + p0);
+#pragma unroll
+    for (uint32_t j = 0; j < kTileBases / 16; ++j) {
+      const uint4 v = src[j];
+      w[4 * j] = v.x; w[4 * j + 1] = v.y; w[4 * j + 2] = v.z; w[4 * j + 3] = v.w;
+    }
+  } else {
+#pragma unroll
+    for (uint32_t j = 0; j < kTileBases / 4; ++j) {
+      w[j] = 0;  // no base
+#pragma unroll
+      for (uint32_t b = 0; b < 4; ++b)
+        if (p0 + 4 * j + b < G) w[j] |= (uint32_t)ref[p0 + 4 * j + b] << (8 * b);
+    }
+  }
+  const uint32_t mask = (1u << (2 * k)) - 1u;  // k <= 14
+  uint32_t c = 0, run = 0, valid[2] = {0, 0};
+#pragma unroll
+  for (uint32_t i = 0; i < kTileBases; ++i) {
+    const uint32_t d = (((w[i >> 2] >> (8 * (i & 3))) & 0xFFu) | 0x20u) - 0x60u;  // 'a' -> 1 ... 't' -> 20
+    const bool ok = d < 32u && ((0x0010008Au >> d) & 1u);                        // a, c, g, t
+    run = ok ? run + 1 : 0;
+    c = ((c << 2) | (((d >> 1) ^ (d >> 2)) & 3u)) & mask;  // a0 c1 g2 t3
+    code[i] = c;
+    valid[i / 32] |= (run >= k && i < kTileSpan + k - 1) ? 1u << (i % 32) : 0u;
+  }
+  return ((uint64_t)valid[1] << 32) | valid[0];
+}
+
+// counts[partition * streams + stream]
+template <bool VEC>
+__global__ __launch_bounds__(kTileT) void k_part_count(const uint8_t* ref, uint64_t G, uint32_t k, uint32_t pb,
+                                                       uint64_t tiles, uint32_t* counts) {
+  extern __shared__ uint32_t hist[];
+  const uint32_t np = 1u << pb, low = 2 * k - pb;
+  for (uint32_t i = threadIdx.x; i < np; i += kTileT) hist[i] = 0;
+  __syncthreads();
+  const uint64_t end = stream_tile(tiles, blockIdx.x + 1, gridDim.x);
+  for (uint64_t tile = stream_tile(tiles, blockIdx.x, gridDim.x); tile < end; ++tile) {
+    uint32_t code[kTileBases];
+    const uint64_t valid = tile_codes<VEC>(ref, G, k, tile, code);
+#pragma unroll
+    for (uint32_t i = 0; i < kTileBases; ++i)
+      if ((valid >> i) & 1u) atomicAdd(&hist[code[i] >> low], 1u);
+  }
+  __syncthreads();
+  for (uint32_t i = threadIdx.x; i < np; i += kTileT) counts[(uint64_t)i * gridDim.x + blockIdx.x] = hist[i];
+}
+
+// A position and its low code bits: one store, so a run of 8 is one 64-byte
+// piece (as a 4- and a 2-byte array, 0.70 ms for 100 Mbp).
+__device__ __forceinline__ uint64_t part_entry(uint32_t pos, uint32_t low) { return (uint64_t)low << 32 | pos; }
+
+// place[partition * streams + stream]: the stream's first slot. Slots are below
+// 2^32, as the positions are.
+template <bool VEC>
+__global__ __launch_bounds__(kTileT) void k_part_scatter(const uint8_t* ref, uint64_t G, uint32_t k, uint32_t pb,
+                                                         uint64_t tiles, const uint64_t* place, uint64_t* parts) {
+  extern __shared__ uint32_t cur[];
+  const uint32_t np = 1u << pb, low = 2 * k - pb;
+  for (uint32_t i = threadIdx.x; i < np; i += kTileT) cur[i] = (uint32_t)place[(uint64_t)i * gridDim.x + blockIdx.x];
+  __syncthreads();
+  const uint64_t end = stream_tile(tiles, blockIdx.x + 1, gridDim.x);
+  for (uint64_t tile = stream_tile(tiles, blockIdx.x, gridDim.x); tile < end; ++tile) {
+    uint32_t code[kTileBases];
+    const uint64_t valid = tile_codes<VEC>(ref, G, k, tile, code);
+    const uint32_t p0 = (uint32_t)(tile * kTile) + threadIdx.x * kTileSpan + 1 - k;
+#pragma unroll
+    for (uint32_t i = 0; i < kTileBases; ++i) {
+      if (!((valid >> i) & 1u)) continue;
+      parts[atomicAdd(&cur[code[i] >> low], 1u)] = part_entry(p0 + i, code[i] & ((1u << low) - 1u));
+    }
+  }
+}
+
+// k_part_scatter with the tile sorted in LDS first, for up to 2^kSortBits
+// partitions. An entry is the position within the tile and the low code bits.
+// One workgroup to a CU (152 KB of LDS).
+constexpr uint32_t kSortBits = 12;
+static_assert(kTile == 1u << 15, "position bits of an entry");
+template <bool VEC>
+__global__ __launch_bounds__(kTileT) void k_part_tile(const uint8_t* ref, uint64_t G, uint32_t k, uint32_t pb,
+                                                      uint64_t tiles, const uint64_t* place, uint64_t* parts,
+                                                      uint32_t* pos) {
+  __shared__ uint32_t ent[kTile];
+  __shared__ uint32_t cur[1u << kSortBits];          // counts, cursors, then slot - place in ent
+  __shared__ uint16_t first[(1u << kSortBits) + 1];  // place of a partition's run in ent
+  __shared__ uint32_t ws[kTileT / 64 + 1];
+  const uint32_t t = threadIdx.x, np = 1u << pb, low = 2 * k - pb;
+  // each thread's partitions are consecutive; it keeps their next slots
+  constexpr uint32_t kOwn = (1u << kSortBits) / kTileT;
+  const uint32_t per = (np + kTileT - 1) / kTileT;
+  uint32_t slot[kOwn];
+#pragma unroll
+  for (uint32_t j = 0; j < kOwn; ++j) {
+    const uint32_t p = t * per + j;
+    slot[j] = j < per && p < np ? (uint32_t)place[(uint64_t)p * gridDim.x + blockIdx.x] : 0u;
+  }
+  const uint64_t end = stream_tile(tiles, blockIdx.x + 1, gridDim.x);
+  for (uint64_t tile = stream_tile(tiles, blockIdx.x, gridDim.x); tile < end; ++tile) {
+    __syncthreads();  // the last tile's runs are written
+    for (uint32_t i = t; i < np; i += kTileT) cur[i] = 0;
+    __syncthreads();
+    uint32_t code[kTileBases];
+    const uint64_t valid = tile_codes<VEC>(ref, G, k, tile, code);
+#pragma unroll
+    for (uint32_t i = 0; i < kTileBases; ++i)
+      if ((valid >> i) & 1u) atomicAdd(&cur[code[i] >> low], 1u);
+    __syncthreads();
+    uint32_t n[kOwn], sum = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < kOwn; ++j) {
+      n[j] = j < per && t * per + j < np ? cur[t * per + j] : 0u;
+      sum += n[j];
+    }
+    uint32_t total;
+    uint32_t run = block_excl_scan<kTileT, uint32_t>(sum, ws, &total);
+#pragma unroll
+    for (uint32_t j = 0; j < kOwn; ++j) {
+      const uint32_t p = t * per + j;
+      if (j >= per || p >= np) continue;
+      first[p] = (uint16_t)run;
+      cur[p] = run;
+      run += n[j];
+    }
+    if (t == 0) first[np] = (uint16_t)total;  // 2^15 at most
+    __syncthreads();
+    const uint32_t o0 = t * kTileSpan + 1 - k;
+#pragma unroll
+    for (uint32_t i = 0; i < kTileBases; ++i)
+      if ((valid >> i) & 1u)
+        ent[atomicAdd(&cur[code[i] >> low], 1u)] = (o0 + i) | (code[i] & ((1u << low) - 1u)) << 15;
+    __syncthreads();
+#pragma unroll
+    for (uint32_t j = 0; j < kOwn; ++j) {
+      const uint32_t p = t * per + j;
+      if (j >= per || p >= np) continue;
+      cur[p] = slot[j] - first[p];
+      slot[j] += n[j];
+    }
+    __syncthreads();
+    // 8 lanes per run of about 8 entries, more where there are fewer partitions
+    const uint32_t lanes = np >= 4096 ? 8 : np >= 2048 ? 16 : np >= 1024 ? 32 : 64;
+    for (uint32_t p = t / lanes; p < np; p += kTileT / lanes) {
+      const uint32_t e = first[p + 1], to = cur[p];
+      for (uint32_t i = first[p] + t % lanes; i < e; i += lanes) {
+        const uint32_t v = ent[i];
+        const uint32_t p0 = (uint32_t)(tile * kTile) + (v & (uint32_t)(kTile - 1));
+        if (low) parts[to + i] = part_entry(p0, v >> 15);
+        else pos[to + i] = p0;
+      }
+    }
+  }
+}
+
+// One workgroup per partition; `low` > 0 code bits are left.
+// Dynamic LDS: the 2^low counters, then `room` positions.
+__global__ __launch_bounds__(1024) void k_part_sort(const uint64_t* place, uint32_t streams, const uint64_t* parts,
+                                                    uint32_t low, uint32_t room, uint64_t* start, uint32_t* pos) {
+  extern __shared__ uint32_t cur[];
+  uint32_t* const sorted = cur + (1u << low);
+  __shared__ uint32_t ws[1024 / 64 + 1];
+  const uint32_t t = threadIdx.x, nc = 1u << low;
+  const uint64_t part = blockIdx.x;
+  const uint64_t b = place[part * streams], e = place[(part + 1) * streams];
+  for (uint32_t i = t; i < nc; i += 1024) cur[i] = 0;
+  __syncthreads();
+  const bool fits = e - b <= room;
+  constexpr uint32_t kAhead = 8;  // loads of a thread in flight
+  for (uint64_t i0 = b + t; i0 < e; i0 += kAhead * 1024) {
+    uint32_t c[kAhead];
+#pragma unroll
+    for (uint32_t j = 0; j < kAhead; ++j) c[j] = i0 + j * 1024 < e ? (uint32_t)(parts[i0 + j * 1024] >> 32) : 0xFFFFFFFFu;
+#pragma unroll
+    for (uint32_t j = 0; j < kAhead; ++j)
+      if (c[j] != 0xFFFFFFFFu) atomicAdd(&cur[c[j]], 1u);
+  }
+  __syncthreads();
+  // each thread's counters are consecutive: their sum, a scan, the starts
+  const uint32_t per = (nc + 1023) / 1024, c0 = min(t * per, nc), c1 = min(c0 + per, nc);
+  uint32_t sum = 0;
+  for (uint32_t c = c0; c < c1; ++c) sum += cur[c];
+  uint32_t total;
+  uint32_t run = block_excl_scan<1024, uint32_t>(sum, ws, &total);
+  for (uint32_t c = c0; c < c1; ++c) {
+    const uint32_t n = cur[c];
+    start[(part << low) + c] = b + run;
+    cur[c] = run;
+    run += n;
+  }
+  __syncthreads();
+  for (uint64_t i0 = b + t; i0 < e; i0 += kAhead * 1024) {
+    uint32_t c[kAhead], p[kAhead];
+#pragma unroll
+    for (uint32_t j = 0; j < kAhead; ++j) {
+      const uint64_t v = i0 + j * 1024 < e ? parts[i0 + j * 1024] : ~0ull;
+      c[j] = (uint32_t)(v >> 32);
+      p[j] = (uint32_t)v;
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < kAhead; ++j) {
+      if (c[j] == 0xFFFFFFFFu) continue;
+      const uint32_t at = atomicAdd(&cur[c[j]], 1u);
+      if (fits) sorted[at] = p[j];
+      else pos[b + at] = p[j];
+    }
+  }
+  if (fits) {
+    __syncthreads();
+    for (uint32_t i = t; i < (uint32_t)(e - b); i += 1024) pos[b + i] = sorted[i];
+  }
+  if (part + 1 == gridDim.x && t == 0) start[(part + 1) << low] = e;
+}
+
+// The starts of a table whose partitions are the codes themselves.
+__global__ __launch_bounds__(256) void k_part_starts(const uint64_t* place, uint32_t streams, uint32_t np, uint64_t* start) {
+  const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+  if (i <= np) start[i] = place[(uint64_t)i * streams];
 }
 
 // ---------------------------------------------------------------------------
@@ -1157,8 +1419,9 @@ int grim_seeds_build(const uint8_t* ref, uint64_t ref_len, uint32_t ref_on_devic
   uint8_t* staging = nullptr;
   uint32_t* counts = nullptr;
   void* tmp = nullptr;
+  void* parts = nullptr;
   auto cleanup = [&]() {
-    for (void* p : {(void*)staging, (void*)counts, tmp}) pool_free(p);
+    for (void* p : {(void*)staging, (void*)counts, tmp, parts}) pool_free(p);
   };
   auto fail = [&](hipError_t e, const char* what) {
     (void)hipDeviceSynchronize();  // some of the work may be on its way
@@ -1172,30 +1435,88 @@ int grim_seeds_build(const uint8_t* ref, uint64_t ref_len, uint32_t ref_on_devic
       return fail(e, "reference copy");
     dref = staging;
   }
-  if ((e = pool_alloc(&counts, (sd->nk + 1) * sizeof(uint32_t))) != hipSuccess) return fail(e, "k-mer counts");
   if ((e = pool_alloc(&sd->start, (sd->nk + 1) * sizeof(uint64_t))) != hipSuccess) return fail(e, "k-mer starts");
-  if ((e = launch_zero_words(counts, (uint32_t)(sd->nk + 1), s)) != hipSuccess) return fail(e, "zero counts");
-  const uint64_t threads = (ref_len + kSpan - 1) / kSpan;
-  const uint64_t blocks = (threads + 255) / 256;
   const bool vec = ((uintptr_t)dref & 15u) == 0;
-  hipLaunchKernelGGL(vec ? k_kmer_count<true> : k_kmer_count<false>, dim3((unsigned)blocks), dim3(256), 0, s, dref,
-                     ref_len, k, counts);
+  // positions per partition and stream; the scanned counts are the streams' places
+  const uint32_t pb = part_bits(k), low = 2 * k - pb;
+  const uint64_t np = 1ull << pb, tiles = (ref_len + kTile - 1) / kTile;
+  const uint32_t streams = (uint32_t)std::min<uint64_t>(kStreams, tiles);
+  const uint64_t cells = np * streams;
+  const size_t part_lds = np * sizeof(uint32_t);
+  if ((e = pool_alloc(&counts, (cells + 1) * sizeof(uint32_t))) != hipSuccess) return fail(e, "partition counts");
+  if ((e = pool_alloc(&tmp, (cells + 1 + scan_blocks(cells + 1) + 1) * sizeof(uint64_t))) != hipSuccess)
+    return fail(e, "partition places");
+  uint64_t* place = static_cast<uint64_t*>(tmp);
+  if ((e = launch_zero_words(counts, (uint32_t)(cells + 1), s)) != hipSuccess) return fail(e, "zero counts");
+  hipLaunchKernelGGL(vec ? k_part_count<true> : k_part_count<false>, dim3(streams), dim3(kTileT), part_lds,
+                     s, dref, ref_len, k, pb, tiles, counts);
   if ((e = hipGetLastError()) != hipSuccess) return fail(e, "k-mer count");
-  if ((e = pool_alloc(&tmp, (scan_blocks(sd->nk + 1) + 1) * sizeof(uint64_t))) != hipSuccess)
-    return fail(e, "scan storage");
-  if ((e = launch_scan(counts, sd->nk + 1, sd->start, static_cast<uint64_t*>(tmp), nullptr, nullptr, s)) !=
-      hipSuccess)
-    return fail(e, "k-mer scan");
+  if ((e = launch_scan(counts, cells + 1, place, place + cells + 1, nullptr, nullptr, s)) != hipSuccess)
+    return fail(e, "partition scan");
   uint64_t n_pos = 0;
-  if ((e = hipMemcpyAsync(&n_pos, sd->start + sd->nk, sizeof n_pos, hipMemcpyDeviceToHost, s)) != hipSuccess)
+  if ((e = hipMemcpyAsync(&n_pos, place + cells, sizeof n_pos, hipMemcpyDeviceToHost, s)) != hipSuccess)
     return fail(e, "position count");
   if ((e = hipStreamSynchronize(s)) != hipSuccess) return fail(e, "position count");
   sd->n_pos = n_pos;
   if ((e = pool_alloc(&sd->pos, std::max<uint64_t>(n_pos, 1) * sizeof(uint32_t))) != hipSuccess)
     return fail(e, "positions");
-  hipLaunchKernelGGL(vec ? k_kmer_fill<true> : k_kmer_fill<false>, dim3((unsigned)blocks), dim3(256), 0, s, dref,
-                     ref_len, k, sd->start, counts, sd->pos);
-  if ((e = hipGetLastError()) != hipSuccess) return fail(e, "k-mer fill");
+  // the partitioned copy: 8 bytes of position and code each. Beyond kPartMost, or
+  // without the memory for it, the table is filled through its counters: 25 GB
+  // for 3.1 Gbp made the build 63 ms instead of 296, but hipFree then wiped them
+  // for 0.6 s, in which every other kernel ran 6% slower. (The switch is a test's.)
+  bool in_parts = true;
+  if (low) {
+    in_parts = n_pos * sizeof(uint64_t) <= kPartMost && !env_flag("GRIM_SEED_BUILD_COUNTERS") &&
+               pool_alloc(&parts, std::max<uint64_t>(n_pos, 1) * sizeof(uint64_t)) == hipSuccess;
+    if (!in_parts) {
+      parts = nullptr;
+      (void)hipGetLastError();  // the failed allocation is not an error of the build
+    }
+  }
+  if (in_parts) {
+    uint64_t* part = static_cast<uint64_t*>(parts);
+    if (pb <= kSortBits)
+      hipLaunchKernelGGL(vec ? k_part_tile<true> : k_part_tile<false>, dim3(streams), dim3(kTileT), 0, s, dref, ref_len,
+                         k, pb, tiles, place, part, sd->pos);
+    else
+      hipLaunchKernelGGL(vec ? k_part_scatter<true> : k_part_scatter<false>, dim3(streams), dim3(kTileT), part_lds, s, dref,
+                         ref_len, k, pb, tiles, place, part);
+    if ((e = hipGetLastError()) != hipSuccess) return fail(e, "k-mer partitions");
+    // LDS for a partition half as large again as the mean, if a CU holds that
+    // (two workgroups to a CU where they fit)
+    const uint64_t want = n_pos / np * 3 / 2 + 64, most = (152u << 10) / 4 - (1u << low);
+    const uint32_t room = want <= most ? (uint32_t)want : (n_pos / np < most * 9 / 10 ? (uint32_t)most : 0u);
+    const size_t sort_lds = ((1u << low) + room) * sizeof(uint32_t);
+    if (low && sort_lds > (64u << 10) &&
+        (e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_part_sort), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                 (int)sort_lds)) != hipSuccess)
+      return fail(e, "LDS of the partition sort");
+    if (low)
+      hipLaunchKernelGGL(k_part_sort, dim3((unsigned)np), dim3(1024), sort_lds, s, place, streams, part, low, room,
+                         sd->start, sd->pos);
+    else
+      hipLaunchKernelGGL(k_part_starts, dim3((unsigned)(np / 256 + 1)), dim3(256), 0, s, place, streams, (uint32_t)np,
+                         sd->start);
+    if ((e = hipGetLastError()) != hipSuccess) return fail(e, "k-mer sort");
+  } else {
+    for (void* p : {(void*)counts, tmp}) pool_free(p);  // the stream was waited for
+    counts = nullptr;
+    tmp = nullptr;
+    if ((e = pool_alloc(&counts, (sd->nk + 1) * sizeof(uint32_t))) != hipSuccess) return fail(e, "k-mer counts");
+    if ((e = pool_alloc(&tmp, (scan_blocks(sd->nk + 1) + 1) * sizeof(uint64_t))) != hipSuccess)
+      return fail(e, "scan storage");
+    if ((e = launch_zero_words(counts, (uint32_t)(sd->nk + 1), s)) != hipSuccess) return fail(e, "zero counts");
+    const uint64_t blocks = ((ref_len + kSpan - 1) / kSpan + 255) / 256;
+    hipLaunchKernelGGL(vec ? k_kmer_count<true> : k_kmer_count<false>, dim3((unsigned)blocks), dim3(256), 0, s, dref,
+                       ref_len, k, counts);
+    if ((e = hipGetLastError()) != hipSuccess) return fail(e, "k-mer count");
+    if ((e = launch_scan(counts, sd->nk + 1, sd->start, static_cast<uint64_t*>(tmp), nullptr, nullptr, s)) !=
+        hipSuccess)
+      return fail(e, "k-mer scan");
+    hipLaunchKernelGGL(vec ? k_kmer_fill<true> : k_kmer_fill<false>, dim3((unsigned)blocks), dim3(256), 0, s, dref,
+                       ref_len, k, sd->start, counts, sd->pos);
+    if ((e = hipGetLastError()) != hipSuccess) return fail(e, "k-mer fill");
+  }
   if ((e = hipStreamSynchronize(s)) != hipSuccess) return fail(e, "k-mer fill");
   cleanup();
   *out = sd.release();
