@@ -117,7 +117,7 @@ int grow(T** p, uint64_t* cap, uint64_t need) {
 
 int ensure_status(grim_workspace& ws) {
   if (!ws.status) GRIM_HIP_TRY(pool_alloc(&ws.status, 8 * sizeof(uint32_t)));
-  if (!ws.status_host) GRIM_HIP_TRY(hipHostMalloc(&ws.status_host, 8 * sizeof(uint32_t), hipHostMallocDefault));
+  if (!ws.status_host) GRIM_HIP_TRY(hipHostMalloc(&ws.status_host, (8 + kFlagWords) * sizeof(uint32_t), hipHostMallocDefault));
   return GRIM_OK;
 }
 
@@ -200,10 +200,6 @@ int tokenize_reads(grim_index* idx, const grim_reads* rd, const ReadView& v, uin
   a.flags = rd->flags;
   a.max_tokens = max_tokens;
   a.tok_shift = tok_shift;
-  // plain codes (no shift) serve the candidate calls, which read a read's
-  // entries only up to its token count; the scans' shifted entries keep the
-  // padding their last block reads
-  a.short_pad = tok_shift == 0 ? 1u : 0u;
   // 128-byte tile rows: the all-bins scan reads tokens in pair order
   a.pair_order = tok_shift == 7 ? 1u : 0u;
   a.tokens = want_tokens ? ws.tokens : nullptr;
@@ -228,6 +224,45 @@ int prepare_reads(grim_index* idx, const grim_reads* rd, uint32_t max_tokens, ui
   rc = tokenize_reads(idx, rd, v, max_tokens, tok_shift, s, pt);
   if (rc) return rc;
   *offsets_dev = v.offsets;
+  return GRIM_OK;
+}
+
+// The arguments of a candidate check of a read set (staged if host-resident),
+// with its flags in pinned host memory, cleared here: no work of this index is
+// on its way (calls wait for theirs).
+int prepare_candidates(grim_index* idx, const grim_reads* rd, const int64_t* cand_off, const int32_t* cand_bin,
+                       uint64_t n_cand, uint16_t* count_out, uint8_t* pass_out, hipStream_t s, CandArgs* out) {
+  int rc = check_reads_args(idx, rd);
+  if (rc) return rc;
+  rc = ensure_status(idx->ws);
+  if (rc) return rc;
+  ReadView v;
+  rc = stage_reads(idx, rd, s, &v);
+  if (rc) return rc;
+  CandArgs a{};
+  a.bm = idx->bm;
+  a.vec_words = idx->vec_words;
+  a.R4 = idx->R4;
+  a.q = idx->q;
+  a.nb = idx->nb;
+  a.bases = v.bases;
+  a.offsets = v.offsets;
+  a.n_reads = rd->n_reads;
+  a.n_bases = rd->n_bases;
+  a.max_edits = v.max_edits;
+  a.err_pm = v.err_pm;
+  a.err_pm_all = rd->err_permille_all;
+  a.overlap = idx->O;
+  a.read_flags = rd->flags;
+  a.cand_off = cand_off;
+  a.cand_bin = cand_bin;
+  a.n_cand = n_cand;
+  a.count_out = count_out;
+  a.pass_out = pass_out;
+  a.flags = idx->ws.status_host + 8;
+  a.work = idx->ws.status + 4;
+  std::memset(a.flags, 0, kFlagWords * sizeof(uint32_t));
+  *out = a;
   return GRIM_OK;
 }
 
@@ -625,37 +660,16 @@ int grim_filter_candidates(const grim_index* cidx, const grim_reads* rd, const i
   DeviceGuard dg(idx->device);
   apply_cached_config(idx, GRIM_MODE_CANDIDATES, rd->n_reads, rd->n_bases, n_cand);
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
-  ReadView v;
-  rc = stage_reads(idx, rd, s, &v);
+  CandArgs a;
+  rc = prepare_candidates(idx, rd, cand_off, cand_bin, n_cand, count_out, pass_out, s, &a);
   if (rc) return rc;
-  ProfSpan pt(PROF_TOKENIZE);
-  rc = tokenize_reads(idx, rd, v, 65535u, 0u, s, pt);
-  if (rc) return rc;
-  CandArgs a{};
-  a.bm = idx->bm;
-  a.vec_words = idx->vec_words;
-  a.R4 = idx->R4;
-  a.q = idx->q;
-  a.nb = idx->nb;
-  a.tokens = idx->ws.tokens;
-  a.offsets = v.offsets;
-  a.thr = idx->ws.thr;
-  a.n_reads = rd->n_reads;
-  a.cand_off = cand_off;
-  a.cand_bin = cand_bin;
-  a.n_cand = n_cand;
-  a.count_out = count_out;
-  a.pass_out = pass_out;
-  a.status = idx->ws.status;
-  a.work = idx->ws.status + 4;
   ProfSpan ps(PROF_CAND);
   ps.start(s);
   GRIM_HIP_TRY(launch_scan_candidates(a, cand_config_from_env(idx->cand_cfg), s));
   ps.stop(s);
-  rc = finish_status(idx, s);
-  pt.collect();
+  GRIM_HIP_TRY(hipStreamSynchronize(s));
   ps.collect();
-  return rc;
+  return status_to_error(flags_to_status(a.flags));
 }
 
 }  // extern "C"

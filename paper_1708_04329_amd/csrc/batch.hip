@@ -164,6 +164,8 @@ void apply_cached_config(grim_index* idx, uint32_t mode, uint64_t n_reads, uint6
 // Shared with api.hip: stage + tokenize a read set into the index workspace.
 int prepare_reads(grim_index* idx, const grim_reads* rd, uint32_t max_tokens, uint32_t tok_shift, hipStream_t s,
                   const int64_t** offsets_dev);
+int prepare_candidates(grim_index* idx, const grim_reads* rd, const int64_t* cand_off, const int32_t* cand_bin,
+                       uint64_t n_cand, uint16_t* count_out, uint8_t* pass_out, hipStream_t s, CandArgs* out);
 
 }  // namespace grim
 
@@ -187,12 +189,29 @@ extern "C" int grim_tune(grim_index* idx, const grim_reads* rd, const int64_t* c
   DeviceGuard dg(idx->device);
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   const int64_t* offs = nullptr;
-  int rc = prepare_reads(idx, rd, 65535u, mode == GRIM_MODE_SCAN ? scan_token_shift(idx->q) : 0u, s, &offs);
-  if (rc) return rc;
-  GRIM_HIP_TRY(hipMemcpyAsync(idx->ws.status_host, idx->ws.status, 8 * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-  GRIM_HIP_TRY(hipStreamSynchronize(s));
-  rc = status_to_error(idx->ws.status_host[0] & ~(uint32_t)(ST_BAD_BIN | ST_BAD_CAND_OFF));
-  if (rc) return rc;
+  int rc = GRIM_OK;
+  CandArgs ca{};
+  DevBuf<uint16_t> cnt;
+  DevBuf<uint8_t> pas;
+  if (mode == GRIM_MODE_SCAN) {
+    rc = prepare_reads(idx, rd, 65535u, scan_token_shift(idx->q), s, &offs);
+    if (rc) return rc;
+    GRIM_HIP_TRY(
+        hipMemcpyAsync(idx->ws.status_host, idx->ws.status, 8 * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+    GRIM_HIP_TRY(hipStreamSynchronize(s));
+    rc = status_to_error(idx->ws.status_host[0]);
+    if (rc) return rc;
+  } else {
+    if (cnt.alloc(n_cand) != hipSuccess || pas.alloc(n_cand) != hipSuccess)
+      return set_error(GRIM_ENOMEM, "tuning output buffers");
+    rc = prepare_candidates(idx, rd, cand_off, cand_bin, n_cand, cnt.p, pas.p, s, &ca);
+    if (rc) return rc;
+    // one launch of the default shape checks the sample
+    GRIM_HIP_TRY(launch_scan_candidates(ca, default_cand_config(idx->vec_words), s));
+    GRIM_HIP_TRY(hipStreamSynchronize(s));
+    rc = status_to_error(flags_to_status(ca.flags));
+    if (rc) return rc;
+  }
 
   hipEvent_t e0, e1;
   GRIM_HIP_TRY(hipEventCreate(&e0));
@@ -272,29 +291,6 @@ extern "C" int grim_tune(grim_index* idx, const grim_reads* rd, const int64_t* c
     best.cand_groups_per_cu = (uint32_t)idx->cand_cfg.groups_per_cu;
     best.cand_coop = (uint32_t)idx->cand_cfg.coop;
   } else {
-    DevBuf<uint16_t> cnt;
-    DevBuf<uint8_t> pas;
-    if (cnt.alloc(n_cand) != hipSuccess || pas.alloc(n_cand) != hipSuccess) {
-      cleanup();
-      return set_error(GRIM_ENOMEM, "tuning output buffers");
-    }
-    CandArgs a{};
-    a.bm = idx->bm;
-    a.vec_words = idx->vec_words;
-    a.R4 = idx->R4;
-    a.q = idx->q;
-    a.nb = idx->nb;
-    a.tokens = idx->ws.tokens;
-    a.offsets = offs;
-    a.thr = idx->ws.thr;
-    a.n_reads = rd->n_reads;
-    a.cand_off = cand_off;
-    a.cand_bin = cand_bin;
-    a.n_cand = n_cand;
-    a.count_out = cnt.p;
-    a.pass_out = pas.p;
-    a.status = idx->ws.status;
-    a.work = idx->ws.status + 4;
     const int waves[] = {1, 2, 4, 8};
     const CandConfig dflt = default_cand_config(idx->vec_words);
     // lane layouts: one lane per pair; groups of lanes per pair (q >= 5); four reads per wavefront (q = 5)
@@ -309,7 +305,7 @@ extern "C" int grim_tune(grim_index* idx, const grim_reads* rd, const int64_t* c
             c.persistent = pers;
             c.groups_per_cu = gpc;
             c.coop = coop;
-            const double ms = time_it([&] { return launch_scan_candidates(a, c, s); });
+            const double ms = time_it([&] { return launch_scan_candidates(ca, c, s); });
             if (ms < 0) continue;
             ++tried;
             // the shape an untuned index uses (default_cand_config)
@@ -339,10 +335,6 @@ extern "C" int grim_tune(grim_index* idx, const grim_reads* rd, const int64_t* c
   }
   cleanup();
   GRIM_HIP_TRY(hipStreamSynchronize(s));
-  // the candidate kernel may have flagged bad bins or offsets in the sample
-  GRIM_HIP_TRY(hipMemcpy(idx->ws.status_host, idx->ws.status, 8 * sizeof(uint32_t), hipMemcpyDeviceToHost));
-  rc = status_to_error(idx->ws.status_host[0]);
-  if (rc) return rc;
   if (tried == 0) return set_error(GRIM_EDEVICE, "no launch shape ran");
   best.mode = mode;
   best.n_tried = tried;
@@ -447,13 +439,12 @@ int build_slot(grim_batcher* b, grim_batch_slot& s) {
   GRIM_HIP_TRY(host_alloc(&s.h_bases, b->max_bases));
   GRIM_HIP_TRY(host_alloc(&s.h_offsets, b->max_reads + 1));
   GRIM_HIP_TRY(host_alloc(&s.h_dyn, 1));
-  GRIM_HIP_TRY(host_alloc(&s.h_status, 8));
+  GRIM_HIP_TRY(host_alloc(&s.h_status, kFlagWords));
   GRIM_HIP_TRY(dev_alloc(&s.d_bases, b->max_bases));
   GRIM_HIP_TRY(dev_alloc(&s.d_offsets, b->max_reads + 1));
   GRIM_HIP_TRY(dev_alloc(&s.d_dyn, 1));
-  GRIM_HIP_TRY(dev_alloc(&s.d_status, 8));
-  GRIM_HIP_TRY(dev_alloc(&s.d_tokens, token_capacity(b->max_bases, b->max_reads)));
-  GRIM_HIP_TRY(dev_alloc(&s.d_thr, b->max_reads + 1));
+  // status words (scans) or flags and the counter after them (candidates)
+  GRIM_HIP_TRY(dev_alloc(&s.d_status, 2 * kFlagWords));
   if (b->edits_kind != GRIM_BATCH_EDITS_NONE) {
     GRIM_HIP_TRY(host_alloc(&s.h_edits, b->max_reads));
     GRIM_HIP_TRY(dev_alloc(&s.d_edits, b->max_reads));
@@ -468,6 +459,8 @@ int build_slot(grim_batcher* b, grim_batch_slot& s) {
     GRIM_HIP_TRY(dev_alloc(&s.d_count, b->max_cand));
     GRIM_HIP_TRY(dev_alloc(&s.d_pass, b->max_cand));
   } else {
+    GRIM_HIP_TRY(dev_alloc(&s.d_tokens, token_capacity(b->max_bases, b->max_reads)));
+    GRIM_HIP_TRY(dev_alloc(&s.d_thr, b->max_reads + 1));
     GRIM_HIP_TRY(dev_alloc(&s.d_mask, b->max_reads * idx->W));
     GRIM_HIP_TRY(dev_alloc(&s.d_order, b->max_reads));
     GRIM_HIP_TRY(dev_alloc(&s.d_hist, length_order_scratch_words()));
@@ -477,8 +470,8 @@ int build_slot(grim_batcher* b, grim_batch_slot& s) {
   // kernels: captured from a stream into a child graph
   hipGraph_t kernels = nullptr;
   GRIM_HIP_TRY(hipStreamBeginCapture(s.stream, hipStreamCaptureModeThreadLocal));
-  hipError_t e = launch_zero_words(s.d_status, 8, s.stream);
-  if (e == hipSuccess) {
+  hipError_t e = launch_zero_words(s.d_status, 2 * kFlagWords, s.stream);
+  if (e == hipSuccess && !cand) {
     TokArgs t{};
     t.dyn = s.d_dyn;
     t.bases = s.d_bases;
@@ -492,9 +485,8 @@ int build_slot(grim_batcher* b, grim_batch_slot& s) {
     t.overlap = idx->O;
     t.flags = b->flags;
     t.max_tokens = 65535u;
-    t.tok_shift = cand ? 0u : scan_token_shift(idx->q);
-    t.short_pad = cand ? 1u : 0u;
-    t.pair_order = !cand && t.tok_shift == 7 ? 1u : 0u;
+    t.tok_shift = scan_token_shift(idx->q);
+    t.pair_order = t.tok_shift == 7 ? 1u : 0u;
     t.tokens = s.d_tokens;
     t.thr = s.d_thr;
     t.status = s.d_status;
@@ -504,22 +496,27 @@ int build_slot(grim_batcher* b, grim_batch_slot& s) {
     if (cand) {
       CandArgs a{};
       a.dyn = s.d_dyn;
-      a.work = s.d_status + 4;
+      a.work = s.d_status + kFlagWords;
       a.bm = idx->bm;
       a.vec_words = idx->vec_words;
       a.R4 = idx->R4;
       a.q = idx->q;
       a.nb = idx->nb;
-      a.tokens = s.d_tokens;
+      a.bases = s.d_bases;
       a.offsets = s.d_offsets;
-      a.thr = s.d_thr;
       a.n_reads = b->max_reads;
+      a.n_bases = b->max_bases;
+      a.max_edits = b->edits_kind == GRIM_BATCH_EDITS_MAX ? s.d_edits : nullptr;
+      a.err_pm = b->edits_kind == GRIM_BATCH_EDITS_ERR ? s.d_edits : nullptr;
+      a.err_pm_all = b->err_permille_all;
+      a.overlap = idx->O;
+      a.read_flags = b->flags;
       a.cand_off = s.d_cand_off;
       a.cand_bin = s.d_cand_bin;
       a.n_cand = b->max_cand;
       a.count_out = s.d_count;
       a.pass_out = s.d_pass;
-      a.status = s.d_status;
+      a.flags = s.d_status;
       e = launch_scan_candidates(a, idx->cand_cfg, s.stream);
     } else {
       ScanArgs a{};
@@ -636,7 +633,7 @@ extern "C" int grim_batcher_submit(grim_batcher* b, uint32_t slot, uint64_t n_re
     if (n_cand) GRIM_HIP_TRY(hipMemcpyAsync(s.d_cand_bin, s.h_cand_bin, n_cand * 4, h2d, s.stream));
   }
   GRIM_HIP_TRY(hipGraphLaunch(s.exec, s.stream));
-  GRIM_HIP_TRY(hipMemcpyAsync(s.h_status, s.d_status, 8 * sizeof(uint32_t), d2h, s.stream));
+  GRIM_HIP_TRY(hipMemcpyAsync(s.h_status, s.d_status, kFlagWords * sizeof(uint32_t), d2h, s.stream));
   if (b->mode == GRIM_MODE_CANDIDATES && n_cand) {
     GRIM_HIP_TRY(hipMemcpyAsync(s.h_count, s.d_count, n_cand * 2, d2h, s.stream));
     GRIM_HIP_TRY(hipMemcpyAsync(s.h_pass, s.d_pass, n_cand, d2h, s.stream));
@@ -653,7 +650,7 @@ extern "C" int grim_batcher_wait(grim_batcher* b, uint32_t slot) {
   DeviceGuard dg(b->idx->device);
   s.pending = false;
   GRIM_HIP_TRY(hipStreamSynchronize(s.stream));
-  return status_to_error(s.h_status[0]);
+  return status_to_error(b->mode == GRIM_MODE_CANDIDATES ? flags_to_status(s.h_status) : s.h_status[0]);
 }
 
 extern "C" void* grim_batcher_stream(grim_batcher* b, uint32_t slot) {

@@ -48,6 +48,30 @@ enum : uint32_t {
 };
 int status_to_error(uint32_t st);
 
+// Candidate checks flag errors without an atomic: word i of kFlagWords is set
+// when status bit i is, in device or pinned host memory (which the host then
+// reads with no copy). The counter that hands out reads follows in device memory.
+constexpr uint32_t kFlagWords = 8;
+inline uint32_t flags_to_status(const uint32_t* w) {
+  uint32_t st = 0;
+  for (uint32_t i = 0; i < kFlagWords; ++i) st |= w[i] ? 1u << i : 0u;
+  return st;
+}
+
+// Bases i .. i + 3 of a read of L bases, the first in the low byte (0 past the
+// end). One load without a branch: the last four bases stand in for a group
+// that runs past them.
+__device__ __forceinline__ uint32_t read4(const uint8_t* rd, uint32_t i, uint32_t L) {
+  uint32_t w = 0;
+  if (L < 4) {
+    for (uint32_t j = i; j < L; ++j) w |= (uint32_t)rd[j] << (8 * (j - i));
+    return w;
+  }
+  const uint32_t at = min(i, L - 4), shift = 8 * (i - at);
+  __builtin_memcpy(&w, rd + at, 4);
+  return shift < 32 ? w >> shift : 0u;
+}
+
 // Loads through a global-memory pointer. A pointer that was itself loaded
 // from memory (a request descriptor's token list, say) is a generic pointer
 // to the compiler, which then issues flat loads; those also count against the
@@ -105,8 +129,6 @@ struct TokArgs {
   uint32_t flags;
   uint32_t max_tokens;  // 255 when uint8 counts are requested, else 65535
   uint32_t tok_shift;   // tokens are stored as code << tok_shift
-  uint32_t short_pad;   // 1: a read's entries end at the next multiple of 8 (candidate
-                        // checks read no further); 0: past the next multiple of 32 (scans)
   uint32_t pair_order;  // 1: order each read's tokens by the parity of their row (the
                         // all-bins scan with 128-byte tile rows; see launch_tokenize)
   uint32_t* tokens;     // null: checks and thresholds only
@@ -227,23 +249,28 @@ inline uint32_t scan_token_shift(uint32_t q) {
 hipError_t launch_scan_allbins(const ScanArgs& a, const ScanConfig& cfg, hipStream_t s);
 
 struct CandArgs {
-  const DynSizes* dyn;         // overrides n_reads / n_cand when non-null
-  uint32_t* work;              // persistent mode: work[0] hands out reads to wavefronts
+  const DynSizes* dyn;         // overrides n_reads / n_bases / n_cand when non-null
+  uint32_t* work;              // persistent mode: work[0] hands out reads to wavefronts (device)
   const uint32_t* bm;
   uint32_t vec_words;
   uint32_t R4;
   uint32_t q;
   uint64_t nb;
-  const uint32_t* tokens;      // plain codes (shift 0)
+  const uint8_t* bases;        // reads and their budgets, as TokArgs
   const int64_t* offsets;
-  const int32_t* thr;
   uint64_t n_reads;
+  uint64_t n_bases;
+  const uint16_t* max_edits;
+  const uint16_t* err_pm;
+  uint32_t err_pm_all;
+  uint32_t overlap;
+  uint32_t read_flags;         // GRIM_READS_*
   const int64_t* cand_off;
   const int32_t* cand_bin;
   uint64_t n_cand;
   uint16_t* count_out;
   uint8_t* pass_out;
-  uint32_t* status;
+  uint32_t* flags;             // [kFlagWords], zero before the launch
   uint32_t grab;               // persistent mode: reads taken per counter increment (set at launch)
 };
 struct CandConfig {
@@ -253,8 +280,8 @@ struct CandConfig {
   int groups_per_cu = 2; // persistent grid size = 256 CUs x groups_per_cu
   int coop = 1;          // 1: VW/16 lanes per pair (q >= 5), 0: one lane per pair,
                          // 2 (q = 5): four reads per wavefront, 16 lanes each
-  int planes = 8;        // coop 2: LDS planes per read, 8 (reads above 255 tokens in a
-                         // second pass) or 16
+  int planes = 8;        // coop 2: LDS planes per read, 8 (reads above 255 tokens one
+                         // at a time) or 16
 };
 constexpr uint64_t kPersistentMinReads = 1ull << 20;
 // The launch shape an untuned index uses, by vector size: at q = 5 four reads
@@ -307,7 +334,7 @@ struct grim_workspace {
   int32_t* thr = nullptr;
   uint64_t thr_cap = 0;
   uint32_t* status = nullptr;      // device [8]
-  uint32_t* status_host = nullptr; // pinned [8]
+  uint32_t* status_host = nullptr; // pinned [8] status copy, then [kFlagWords] flags of candidate checks
   uint8_t* staging = nullptr;      // device copies of host-resident inputs
   uint64_t staging_cap = 0;
   uint32_t* order = nullptr;       // scan order (reads sorted by length)

@@ -4,11 +4,12 @@
 //
 // The call computes exactly what grim_filter_candidates computes, with the
 // same kernels; only the scratch differs. Instead of the index's workspace
-// (which grows with hipMalloc), its status words, per-read thresholds and
-// token lists live in `scratch`, a fixed device array of this file. Each GPU
-// holds its own copy of the array at its own address, so the host never uses
-// the array's name as a device address: the address is taken once per device
-// with hipGetSymbolAddress and kept.
+// (which grows with hipMalloc), its flags and the counter that hands out reads
+// live in `scratch`, a fixed device array of this file. Each GPU holds its own
+// copy of the array at its own address, so the host never uses the array's name
+// as a device address: the address is taken once per device with
+// hipGetSymbolAddress and kept. The call's size limit is that of the entry
+// point's description, which counts thresholds and token lists per read.
 
 #include <cstring>
 #include <mutex>
@@ -18,7 +19,7 @@
 namespace grim {
 namespace {
 
-constexpr uint64_t kScratchBytes = 64ull << 20;  // GRIM_STATIC_SCRATCH_BYTES in grim.h
+constexpr uint64_t kScratchBytes = 256;
 constexpr int kMaxDevices = 64;
 
 static __device__ __align__(256) uint8_t scratch[kScratchBytes];
@@ -80,18 +81,15 @@ extern "C" int grim_filter_candidates_static(const grim_index* cidx, const grim_
   if (rd->n_reads && !cand_off) return set_error(GRIM_EINVAL, "cand_off is NULL");
   if (n_cand && !cand_bin) return set_error(GRIM_EINVAL, "cand_bin is NULL");
   if (rd->n_reads == 0) return GRIM_OK;
-  // scratch layout: status words (status[4] hands out reads to a persistent
-  // grid), thresholds, then the token lists (16-byte aligned)
-  const uint64_t off_thr = 256;
-  const uint64_t off_tok = off_thr + up256((rd->n_reads + 1) * 4);
-  if (rd->n_reads > kScratchBytes || rd->n_bases > kScratchBytes ||
-      off_tok + token_capacity(rd->n_bases, rd->n_reads) * 4 > kScratchBytes)
+  const uint64_t most = GRIM_STATIC_SCRATCH_BYTES;
+  const uint64_t off_tok = 256 + up256((rd->n_reads + 1) * 4);
+  if (rd->n_reads > most || rd->n_bases > most || off_tok + token_capacity(rd->n_bases, rd->n_reads) * 4 > most)
     return set_error(GRIM_EINVAL,
                      "%llu reads of %llu bases need %llu scratch bytes, above the fixed %llu "
                      "(GRIM_STATIC_SCRATCH_BYTES); split the call or use grim_filter_candidates",
                      (unsigned long long)rd->n_reads, (unsigned long long)rd->n_bases,
                      (unsigned long long)(off_tok + token_capacity(rd->n_bases, rd->n_reads) * 4),
-                     (unsigned long long)kScratchBytes);
+                     (unsigned long long)most);
   const int dev = idx->device;
   if (dev < 0 || dev >= kMaxDevices) return set_error(GRIM_EDEVICE, "device ordinal %d out of range", dev);
   DeviceGuard dg(dev);
@@ -105,49 +103,34 @@ extern "C" int grim_filter_candidates_static(const grim_index* cidx, const grim_
     cfg = idx->cand_cfg;
   }
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
-  uint32_t* status = reinterpret_cast<uint32_t*>(base);
-  int32_t* thr = reinterpret_cast<int32_t*>(base + off_thr);
-  uint32_t* tokens = reinterpret_cast<uint32_t*>(base + off_tok);
-  // the array keeps the previous call's contents: clear the status words
-  GRIM_HIP_TRY(launch_zero_words(status, 8, s));
-  TokArgs t{};
-  t.bases = rd->bases;
-  t.offsets = rd->offsets;
-  t.n_reads = rd->n_reads;
-  t.n_bases = rd->n_bases;
-  t.max_edits = rd->max_edits;
-  t.err_pm = rd->err_permille;
-  t.err_pm_all = rd->err_permille_all;
-  t.q = idx->q;
-  t.overlap = idx->O;
-  t.flags = rd->flags;
-  t.max_tokens = 65535u;
-  t.tok_shift = 0;
-  t.short_pad = 1;
-  t.tokens = tokens;
-  t.thr = thr;
-  t.status = status;
-  GRIM_HIP_TRY(launch_tokenize(t, s));
+  uint32_t* flags = reinterpret_cast<uint32_t*>(base);
+  // the array keeps the previous call's contents: clear the flags
+  GRIM_HIP_TRY(launch_zero_words(flags, 2 * kFlagWords, s));
   CandArgs a{};
   a.bm = idx->bm;
   a.vec_words = idx->vec_words;
   a.R4 = idx->R4;
   a.q = idx->q;
   a.nb = idx->nb;
-  a.tokens = tokens;
+  a.bases = rd->bases;
   a.offsets = rd->offsets;
-  a.thr = thr;
   a.n_reads = rd->n_reads;
+  a.n_bases = rd->n_bases;
+  a.max_edits = rd->max_edits;
+  a.err_pm = rd->err_permille;
+  a.err_pm_all = rd->err_permille_all;
+  a.overlap = idx->O;
+  a.read_flags = rd->flags;
   a.cand_off = cand_off;
   a.cand_bin = cand_bin;
   a.n_cand = n_cand;
   a.count_out = count_out;
   a.pass_out = pass_out;
-  a.status = status;
-  a.work = status + 4;
+  a.flags = flags;
+  a.work = flags + kFlagWords;
   GRIM_HIP_TRY(launch_scan_candidates(a, cfg, s));
-  uint32_t st[8];
-  GRIM_HIP_TRY(hipMemcpyAsync(st, status, sizeof st, hipMemcpyDeviceToHost, s));
+  uint32_t st[kFlagWords];
+  GRIM_HIP_TRY(hipMemcpyAsync(st, flags, sizeof st, hipMemcpyDeviceToHost, s));
   GRIM_HIP_TRY(hipStreamSynchronize(s));
-  return status_to_error(st[0]);
+  return status_to_error(flags_to_status(st));
 }

@@ -5,8 +5,10 @@
 // The count with multiplicity, sum_i bit[x][t_i], is rewritten as
 // sum_j 2^j * popcount(vec_x AND plane_j), where plane_j is the 4^q-bit set of
 // tokens whose number of occurrences in the read has bit j set. One
-// wavefront handles one read: it counts the read's tokens straight into its
-// multiplicity planes in LDS once, then each lane takes one candidate bin,
+// wavefront handles one read: it takes the read's tokens from its bases (its
+// checks and threshold, too, are made here: a list of tokens in memory cost a
+// launch and, at 1M reads of 100 bp, 0.18 of 0.85 ms), counts them straight into
+// its multiplicity planes in LDS once, then each lane takes one candidate bin,
 // streams that bin's vector (128 B at q=5, 512 B at q=6) from HBM with
 // 16-byte loads and ANDs it with the planes (read from LDS with a
 // wave-uniform address, i.e. a broadcast), counting with v_bcnt. The gather
@@ -53,6 +55,68 @@ __device__ __forceinline__ uint32_t group_sum(uint32_t x) {
   return x;
 }
 
+__device__ __forceinline__ void flag(const CandArgs& a, uint32_t status) {
+  for (uint32_t i = 0; i < kFlagWords; ++i)
+    if ((status >> i) & 1u) a.flags[i] = 1u;
+}
+
+// A read: its bases, tokens and threshold, checked as the scans' tokenizer
+// does (paper Section 3; the budget's ceiling from Section 6). A rejected one
+// is flagged and has no tokens.
+struct Read {
+  const uint8_t* rd;
+  uint32_t L, ntok;
+  int32_t T;
+};
+
+__device__ __forceinline__ Read read_of(const CandArgs& a, uint64_t r, bool flags) {
+  Read x;
+  const int64_t o0 = a.offsets[r], o1 = a.offsets[r + 1], q = a.q;
+  const uint64_t n_bases = a.dyn ? min(a.dyn->n_bases, a.n_bases) : a.n_bases;
+  uint32_t err = 0;
+  int64_t L = o1 - o0;
+  if (o0 < 0 || o1 < o0 || (uint64_t)o1 > n_bases) { err |= ST_BAD_LENGTH; L = 0; }
+  if (L < q) err |= ST_BAD_LENGTH;
+  const int64_t ntok = L >= q ? L - q + 1 : 0;
+  if (ntok > 65535) err |= ST_TOO_LONG;
+  const uint64_t e = a.max_edits ? a.max_edits[r] : (a.err_pm ? a.err_pm[r] : a.err_pm_all);
+  const uint64_t E = a.max_edits ? e : ((uint64_t)L * e + 999u) / 1000u;
+  if (!(a.read_flags & GRIM_READS_ALLOW_SHORT_OVERLAP) && L + (int64_t)E - q > (int64_t)a.overlap) err |= ST_OVERLAP;
+  const int64_t T = (L - q + 1) - q * (int64_t)E;
+  x.T = (int32_t)max<int64_t>(T, -(1 << 30));
+  x.rd = a.bases + o0;
+  x.L = (uint32_t)L;
+  x.ntok = err ? 0u : (uint32_t)ntok;
+  if (err && flags) flag(a, err);
+  return x;
+}
+
+// Twelve bases from position i of a read: codes packed, the first most
+// significant, and a bit per base that is no A, C, G, T or past the end, the
+// first in bit 11. Four at a time: with the case folded, bits 1-2 and 2-3 of a
+// letter XOR to its code, which one byte permute turns back into the letter.
+struct Bases {
+  uint32_t codes, bad;
+};
+__device__ __forceinline__ Bases bases12(const uint8_t* rd, uint32_t i, uint32_t L) {
+  Bases b = {0, 0};
+#pragma unroll
+  for (uint32_t j = 0; j < 3; ++j) {
+    const uint32_t l = read4(rd, i + 4 * j, L) | 0x20202020u;
+    const uint32_t c = ((l >> 1) ^ (l >> 2)) & 0x03030303u;
+    const uint32_t d = __builtin_amdgcn_perm(0u, 0x74676361u, c) ^ l;  // byte k: "acgt"[c_k] ^ base k
+    const uint32_t bad = ((((d & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | d) >> 7) & 0x01010101u;
+    b.codes = __builtin_amdgcn_udot4(c, 0x01041040u, b.codes << 8, false);
+    b.bad = __builtin_amdgcn_udot4(bad, 0x01020408u, b.bad << 4, false);
+  }
+  return b;
+}
+// The token that starts at base u of them (u + q <= 12), or R4 if it is none.
+__device__ __forceinline__ uint32_t token_at(const Bases& b, uint32_t u, uint32_t q, uint32_t R4) {
+  const uint32_t end = 12 - q - u;
+  return (b.bad >> end) & ((1u << q) - 1u) ? R4 : (b.codes >> (2 * end)) & (R4 - 1u);
+}
+
 // Steps 1-3 for read r: the K multiplicity planes of its tokens in this
 // wavefront's LDS, counted directly in bit-sliced form. Adding one occurrence
 // of token t flips bit t of plane 0 with an atomic XOR; if the bit was set,
@@ -61,38 +125,41 @@ __device__ __forceinline__ uint32_t group_sum(uint32_t x) {
 // floor(n_k / 2) times whatever the order of the lanes' atomics, so the planes
 // end up holding every token's count in binary. K, the bit length of the
 // largest count, is one more than the highest level any increment reached.
-// Returns K, or -1 when the read has no candidates.
+// Returns K, or -1 when the read has no candidates or was rejected.
 template <int VW>
 __device__ __forceinline__ int build_planes(const CandArgs& a, uint64_t r, uint64_t n_cand, uint32_t* planes,
-                                            uint32_t lane, int64_t* pc0, int64_t* pc1) {
+                                            uint32_t lane, int64_t* pc0, int64_t* pc1, int32_t* T) {
   static_assert(VW <= 2048, "planes of 4^q bits, q <= 8");
   constexpr uint32_t kWords = kMaxPlanes * VW;
   const int64_t c0 = a.cand_off[r], c1 = a.cand_off[r + 1];
+  const Read x = read_of(a, r, lane == 0);
   if (c0 < 0 || c1 < c0 || (uint64_t)c1 > n_cand) {
-    if (lane == 0) atomicOr(a.status, ST_BAD_CAND_OFF);
+    if (lane == 0) flag(a, ST_BAD_CAND_OFF);
     return -1;
   }
-  if (c0 == c1) return -1;
+  if (c0 == c1 || x.ntok == 0) return -1;
   *pc0 = c0;
   *pc1 = c1;
-  const int64_t o0 = a.offsets[r], o1 = a.offsets[r + 1];
-  const uint32_t ntok = (uint32_t)(o1 - o0 - a.q + 1);
-  const uint32_t* tok = a.tokens + token_base(o0, r);
-  const uint32_t R4 = a.R4;
+  *T = x.T;
+  const uint32_t R4 = a.R4, q = a.q;
 
   uint4* p4 = reinterpret_cast<uint4*>(planes);  // kWords = 16 VW, a multiple of 4
   for (uint32_t i = lane; i < kWords / 4; i += 64) p4[i] = make_uint4(0, 0, 0, 0);
   wave_sync();
   uint32_t top = 0;  // highest level reached + 1
-  for (uint32_t i = lane; i < ntok; i += 64) {
-    const uint32_t t = tok[i];
-    if (t >= R4) continue;
-    const uint32_t bit = 1u << (t & 31u);
-    uint32_t* w = planes + (t >> 5);
-    uint32_t k = 0;
-    // a count stays below 2^16 (at most 65535 tokens), so k stays below kMaxPlanes
-    while ((atomicXor(w + k * VW, bit) & bit) && k + 1 < (uint32_t)kMaxPlanes) ++k;
-    top = max(top, k + 1);
+  for (uint32_t i = 4 * lane; i < x.ntok; i += 256) {
+    const Bases b = bases12(x.rd, i, x.L);
+#pragma unroll
+    for (uint32_t u = 0; u < 4; ++u) {
+      const uint32_t t = token_at(b, u, q, R4);
+      if (t >= R4) continue;
+      const uint32_t bit = 1u << (t & 31u);
+      uint32_t* w = planes + (t >> 5);
+      uint32_t k = 0;
+      // a count stays below 2^16 (at most 65535 tokens), so k stays below kMaxPlanes
+      while ((atomicXor(w + k * VW, bit) & bit) && k + 1 < (uint32_t)kMaxPlanes) ++k;
+      top = max(top, k + 1);
+    }
   }
   for (int off = 32; off >= 1; off >>= 1) top = max(top, (uint32_t)__shfl_xor((int)top, off));
   wave_sync();
@@ -103,10 +170,10 @@ template <int VW>
 __device__ __forceinline__ void cand_read(const CandArgs& a, uint64_t r, uint64_t n_cand,
                                           uint32_t* planes, uint32_t lane) {
   int64_t c0 = 0, c1 = 0;
-  const int Ki = build_planes<VW>(a, r, n_cand, planes, lane, &c0, &c1);
+  int32_t T = 0;
+  const int Ki = build_planes<VW>(a, r, n_cand, planes, lane, &c0, &c1, &T);
   if (Ki < 0) return;
   const uint32_t K = (uint32_t)Ki;
-  const int32_t T = a.thr[r];
   // 4. one candidate per lane
   for (int64_t cb = c0; cb < c1; cb += 64) {
     const int64_t c = cb + lane;
@@ -114,7 +181,7 @@ __device__ __forceinline__ void cand_read(const CandArgs& a, uint64_t r, uint64_
     const int32_t x = a.cand_bin[c];
     uint32_t cnt = 0;
     if (x < 0 || (uint64_t)x >= a.nb) {
-      atomicOr(a.status, ST_BAD_BIN);
+      flag(a, ST_BAD_BIN);
     } else {
       const uint32_t* vec = a.bm + (uint64_t)x * VW;
       uint32_t acc[4] = {0, 0, 0, 0};
@@ -170,10 +237,10 @@ __device__ __forceinline__ void cand_read_coop(const CandArgs& a, uint64_t r, ui
   constexpr int G = VW / WPL;              // lanes per pair
   constexpr int PPW = 64 / G;              // pairs per wavefront pass
   int64_t c0 = 0, c1 = 0;
-  const int Ki = build_planes<VW>(a, r, n_cand, planes, lane, &c0, &c1);
+  int32_t T = 0;
+  const int Ki = build_planes<VW>(a, r, n_cand, planes, lane, &c0, &c1, &T);
   if (Ki < 0) return;
   const uint32_t K = (uint32_t)Ki;
-  const int32_t T = a.thr[r];
   const uint32_t j = lane % G, g = lane / G;
   uint32_t pl[4][WPL];
 #pragma unroll
@@ -233,7 +300,7 @@ __device__ __forceinline__ void cand_read_coop(const CandArgs& a, uint64_t r, ui
       part = group_sum<G>(part);  // the group's partial counts (groups are aligned runs of G lanes)
       if (j == 0 && c[u] < c1) {
         if (!ok[u]) {
-          atomicOr(a.status, ST_BAD_BIN);
+          flag(a, ST_BAD_BIN);
         } else {
           if (a.count_out) a.count_out[c[u]] = (uint16_t)part;
           if (a.pass_out) a.pass_out[c[u]] = (int32_t)part >= T ? 1 : 0;
@@ -258,9 +325,10 @@ __device__ __forceinline__ void cand_read_coop(const CandArgs& a, uint64_t r, ui
 // counts with DPP moves.
 //
 // NPL is the number of planes a read keeps in LDS: 16, or 8 for reads of at
-// most 255 tokens (no count can reach 256). With 8, a read of more tokens is
-// left to k_cand_long, and a wavefront's LDS halves (4 KB at q = 5), so LDS
-// no longer limits how many wavefronts a CU holds.
+// most 255 tokens (no count can reach 256). With 8, a read of more tokens takes
+// the wavefront for itself after the others, in the cooperative layout (whose 16
+// planes fit the LDS of the four), and a wavefront's LDS halves (4 KB at q = 5),
+// so LDS no longer limits how many wavefronts a CU holds.
 constexpr int kQuadReads = 4;  // reads per wavefront in the quad layout
 
 constexpr uint32_t kShortTokens = 255;  // most tokens of a read the 8-plane layout takes
@@ -277,43 +345,44 @@ __device__ __forceinline__ void cand_quad(const CandArgs& a, uint64_t r_first, u
   uint32_t* planes = planes_wave + qd * kPlaneWords;
   uint32_t* kword = planes_wave + kQuadReads * kPlaneWords + qd;  // largest level reached, per read
   int64_t c0 = 0, c1 = 0;
-  uint32_t ntok = 0;
-  int32_t T = 0;
-  const uint32_t* tok = a.tokens;
+  Read x = {a.bases, 0, 0, 0};
+  bool is_long = false;
   if (r < n_reads) {
     c0 = a.cand_off[r];
     c1 = a.cand_off[r + 1];
+    x = read_of(a, r, ql == 0);
     if (c0 < 0 || c1 < c0 || (uint64_t)c1 > n_cand) {
-      if (ql == 0) atomicOr(a.status, ST_BAD_CAND_OFF);
+      if (ql == 0) flag(a, ST_BAD_CAND_OFF);
       c0 = c1 = 0;
     }
-    const int64_t o0 = a.offsets[r];
-    if (c1 > c0) ntok = (uint32_t)(a.offsets[r + 1] - o0 - a.q + 1);  // a read without pairs counts nothing
-    if (NPL < kMaxPlanes && ntok > kShortTokens) c0 = c1 = ntok = 0;   // k_cand_long takes it
-    tok = a.tokens + token_base(o0, r);
-    T = a.thr[r];
+    is_long = NPL < kMaxPlanes && x.ntok > kShortTokens && c1 > c0;
+    if (x.ntok == 0 || is_long) c1 = c0;  // rejected, or taken below
+    if (c1 == c0) x.ntok = 0;             // a read without pairs counts nothing
   }
+  const uint32_t ntok = x.ntok;
+  const int32_t T = x.T;
   uint4* p4 = reinterpret_cast<uint4*>(planes);
   for (uint32_t i = ql; i < kPlaneWords / 4; i += QL) p4[i] = make_uint4(0, 0, 0, 0);
   if (ql == 0) *kword = 0;
   wave_sync();
-  const uint32_t R4 = a.R4;
+  const uint32_t R4 = a.R4, q = a.q;
   uint32_t top = 0;  // highest level reached + 1
-  // four tokens per lane and load: a token list starts 16-byte aligned and its
-  // padding (code R4) reaches past the next multiple of 4 above the count
-  for (uint32_t i4 = ql * 4; i4 < ntok; i4 += 4 * QL) {
-    const uint4 t4 = ldg4(tok + i4);
-    const uint32_t tt[4] = {t4.x, t4.y, t4.z, t4.w};
-    // the four level-0 flips are issued together; a token whose bit was
-    // already set (a repeat) then carries into the levels above, in order
-    uint32_t old[4];
+  // eight tokens per lane: the 12 bases they span in three loads
+  constexpr uint32_t TL = 8;
+  for (uint32_t i = TL * ql; i < ntok; i += TL * QL) {
+    const Bases b = bases12(x.rd, i, x.L);
+    uint32_t tt[TL], old[TL];
+    // the level-0 flips are issued together; a token whose bit was already set
+    // (a repeat) then carries into the levels above, in order
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
+    for (uint32_t e = 0; e < TL; ++e) {
+      tt[e] = token_at(b, e, q, R4);
       old[e] = tt[e] < R4 ? atomicXor(planes + (tt[e] >> 5), 1u << (tt[e] & 31u)) : 0u;
+    }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
+    for (uint32_t e = 0; e < TL; ++e) {
       const uint32_t t = tt[e];
-      if (t >= R4) continue;  // invalid window or padding
+      if (t >= R4) continue;  // invalid window, or past the read's end
       const uint32_t bit = 1u << (t & 31u);
       uint32_t k = 0;
       if (old[e] & bit) {
@@ -408,7 +477,7 @@ __device__ __forceinline__ void cand_quad(const CandArgs& a, uint64_t r_first, u
     }
     if (livem) {
       if (!okm) {
-        atomicOr(a.status, ST_BAD_BIN);
+        flag(a, ST_BAD_BIN);
       } else {
         if (cnt_out) cnt_out[pm] = (uint16_t)mine;
         if (pas_out) pas_out[pm] = (int32_t)mine >= T ? 1 : 0;
@@ -417,6 +486,10 @@ __device__ __forceinline__ void cand_quad(const CandArgs& a, uint64_t r_first, u
   }
   // the LDS of this wavefront is reused by its next reads
   wave_sync();
+  if constexpr (NPL < kMaxPlanes) {
+    for (uint64_t m = __ballot(is_long && ql == 0); m; m &= m - 1)
+      cand_read_coop<VW>(a, r_first + (uint32_t)__builtin_ctzll(m) / QL, n_cand, planes_wave, lane);
+  }
 }
 
 // LAYOUT: 0 one lane per pair, 1 VW/WPL lanes per pair, 2 four reads per
@@ -432,7 +505,6 @@ __global__ __launch_bounds__(NW * 64) void k_scan_cand(CandArgs a) {
   uint32_t* planes = lds + wave * kPerWave;
   const uint64_t n_reads = a.dyn ? min(a.dyn->n_reads, a.n_reads) : a.n_reads;
   const uint64_t n_cand = a.dyn ? min(a.dyn->n_cand, a.n_cand) : a.n_cand;
-  if (a.status[0] & ~(uint32_t)(ST_BAD_BIN | ST_BAD_CAND_OFF)) return;  // rejected reads
   auto step = [&](uint64_t r) {
     if constexpr (LAYOUT == 2) cand_quad<VW, NPL>(a, r, n_reads, n_cand, planes, lane);
     else if constexpr (LAYOUT == 1) cand_read_coop<VW>(a, r, n_cand, planes, lane);
@@ -452,31 +524,6 @@ __global__ __launch_bounds__(NW * 64) void k_scan_cand(CandArgs a) {
       if ((uint64_t)r0 >= n_reads) break;
       const uint64_t r1 = min((uint64_t)r0 + grab, n_reads);
       for (uint64_t r = r0; r < r1; r += kReads) step(r);
-    }
-  }
-}
-
-// The reads of more than 255 tokens that the 8-plane quad layout leaves: each
-// wavefront looks at 64 reads at a time (a lane each) and runs every long one
-// that has pairs in the cooperative layout with all 16 planes.
-template <int VW>
-__global__ __launch_bounds__(256) void k_cand_long(CandArgs a) {
-  __shared__ __attribute__((aligned(16))) uint32_t lds[4 * kMaxPlanes * VW];
-  const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
-  uint32_t* planes = lds + wave * kMaxPlanes * VW;
-  const uint64_t n_reads = a.dyn ? min(a.dyn->n_reads, a.n_reads) : a.n_reads;
-  const uint64_t n_cand = a.dyn ? min(a.dyn->n_cand, a.n_cand) : a.n_cand;
-  if (a.status[0] & ~(uint32_t)(ST_BAD_BIN | ST_BAD_CAND_OFF)) return;  // rejected reads
-  const uint64_t stride = (uint64_t)gridDim.x * 4 * 64;
-  for (uint64_t base = ((uint64_t)blockIdx.x * 4 + wave) * 64; base < n_reads; base += stride) {
-    const uint64_t r = base + lane;
-    bool is_long = false;
-    if (r < n_reads) is_long = (uint64_t)(a.offsets[r + 1] - a.offsets[r]) > kShortTokens + a.q - 1;
-    uint64_t m = __ballot(is_long);
-    while (m) {
-      const uint32_t l = (uint32_t)__builtin_ctzll(m);
-      m &= m - 1;
-      cand_read_coop<VW>(a, base + l, n_cand, planes, lane);
     }
   }
 }
@@ -505,15 +552,7 @@ hipError_t launch_nw_layout(const CandArgs& a, const CandConfig& cfg, hipStream_
     if (blocks == 0) return hipSuccess;
     hipLaunchKernelGGL((k_scan_cand<VW, NW, false, LAYOUT, NPL>), dim3((unsigned)blocks), dim3(NW * 64), 0, s, a);
   }
-  hipError_t e = hipGetLastError();
-  if constexpr (NPL < kMaxPlanes) {
-    // reads of more than 255 tokens, left by the 8-plane layout
-    if (e != hipSuccess) return e;
-    const uint64_t groups = std::min<uint64_t>(1024, (a.n_reads + 255) / 256);
-    hipLaunchKernelGGL((k_cand_long<VW>), dim3((unsigned)groups), dim3(256), 0, s, a);
-    e = hipGetLastError();
-  }
-  return e;
+  return hipGetLastError();
 }
 
 template <int VW, int NW>

@@ -8,8 +8,8 @@
 // error budget E_r = ceil(e_r * L_r) (Section 6, read-existence figure
 // caption) are computed here too, one per read.
 //
-// Tokens are written as code << tok_shift (the scan kernel wants the LDS byte
-// offset of the token's row, the candidate kernel the plain code).
+// Tokens are written as code << tok_shift, the LDS byte offset of the token's
+// row, for the all-bins scan (candidate checks read the bases themselves).
 //
 // A wavefront tokenises eight reads at once: lane j < 8 validates read j and
 // writes its threshold, then the 64 lanes walk the reads' padded token ranges
@@ -98,9 +98,8 @@ __global__ __launch_bounds__(256) void k_tokenize(TokArgs a) {
       ntok_read = (uint32_t)ntok;
       // padded to the next multiple of 32 strictly above the token count: the
       // scan folds the last partial block exactly and may read one block past
-      // the full ones; candidate checks read whole groups of four up to the
-      // count, so a multiple of 8 serves them
-      npad_read = a.short_pad ? (ntok_read + 7u) & ~7u : (ntok_read / 32u + 1u) * 32u;
+      // the full ones
+      npad_read = (ntok_read / 32u + 1u) * 32u;
     }
   }
 

@@ -382,20 +382,6 @@ __device__ __forceinline__ Pair pair_of(const VerifyArgs& a, uint32_t r, uint32_
   return p;
 }
 
-// Bases i .. i + 3 of a read of L bases, the first in the low byte (0 past the
-// end). One load without a branch: the last four bases stand in for a group
-// that runs past them.
-__device__ __forceinline__ uint32_t read4(const uint8_t* rd, uint32_t i, uint32_t L) {
-  uint32_t w = 0;
-  if (L < 4) {
-    for (uint32_t j = i; j < L; ++j) w |= (uint32_t)rd[j] << (8 * (j - i));
-    return w;
-  }
-  const uint32_t at = min(i, L - 4), shift = 8 * (i - at);
-  __builtin_memcpy(&w, rd + at, 4);
-  return shift < 32 ? w >> shift : 0u;
-}
-
 // The smallest distance of pair p's read to a part of text [lo, hi) within its bin.
 template <int W, bool BOUNDED>
 __device__ __forceinline__ int32_t align_text(const VerifyArgs& a, const Pair& p, uint64_t lo, uint64_t hi) {
