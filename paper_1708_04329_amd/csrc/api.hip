@@ -756,8 +756,12 @@ int verify_impl(const grim_index* cidx, const grim_reads* rd, const int64_t* can
   GRIM_HIP_TRY(launch_verify_scatter(a, s));
   ProfSpan pv(PROF_VERIFY);
   pv.start(s);
-  if (bounded) GRIM_HIP_TRY(launch_verify_sift(a, total, s));
-  for (uint32_t w = 1; w < kVerifyBuckets; ++w) GRIM_HIP_TRY(launch_verify_align(a, w, first[w], counts[w], s));
+  if (bounded) {
+    GRIM_HIP_TRY(launch_verify_sift(a, total, s));
+    GRIM_HIP_TRY(launch_verify_left(a, first, counts, s));
+  } else {
+    for (uint32_t w = 1; w < kVerifyBuckets; ++w) GRIM_HIP_TRY(launch_verify_align(a, w, first[w], counts[w], s));
+  }
   pv.stop(s);
   GRIM_HIP_TRY(hipStreamSynchronize(s));  // the inputs' status is known: nothing after the count sets it
   pv.collect();

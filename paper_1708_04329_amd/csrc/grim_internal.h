@@ -193,8 +193,11 @@ hipError_t launch_verify_scatter(const VerifyArgs& a, hipStream_t s);
 // (item_span) and write the outputs of the others.
 hipError_t launch_verify_sift(const VerifyArgs& a, uint64_t count, hipStream_t s);
 constexpr uint64_t kRefTail = 64;  // bytes past the reference copy that the sift may read
-// Align work items [first, first + count), all of whose reads have `words`
-// 32-base words.
+// Bounded form: align what the sift left; reads of w words are the items
+// [first[w], first[w] + count[w]), w = 1 .. kVerifyBuckets - 1.
+hipError_t launch_verify_left(const VerifyArgs& a, const uint64_t* first, const uint64_t* count, hipStream_t s);
+// Exact form: align work items [first, first + count), all of whose reads have
+// `words` 32-base words.
 hipError_t launch_verify_align(const VerifyArgs& a, uint32_t words, uint64_t first, uint64_t count,
                                hipStream_t s);
 

@@ -486,7 +486,7 @@ __global__ __launch_bounds__(256) void k_verify_align(VerifyArgs a, uint64_t fir
 // number of pieces (comparing each window with every code took 190), against
 // 12 per 32 rows and base in the alignment. Bound by the bins' bytes, each read
 // for one pair: 752065 pairs of the 3.1 Gbp reference (100003 reads of 100-250
-// bp) take 0.62 ms, 2.8 TB/s, and the alignments of what is left 1.5 ms; without
+// bp) take 0.61 ms, 2.8 TB/s, and the alignments of what is left 0.94 ms; without
 // the sift the alignments took 5.1 ms.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kMinPiece = 13;
@@ -709,21 +709,34 @@ __global__ __launch_bounds__(256) void k_verify_sift(VerifyArgs a, uint64_t coun
 // length, so that a wavefront's lanes end together, and aligns them a lane
 // each. (With whole texts in list order a wavefront ran to its longest of 64
 // lanes, five times the mean, and a whole bin of 2.3 kbp alone took 0.5 ms.)
+// Bound by the chain of a lane's columns, so every class of read lengths is in
+// one launch, that as many workgroups as fit are there to hide it: for 752065
+// listed pairs of 100-250 bp reads, launches by class (512, 512 and 358
+// workgroups one after the other) took 1.47 ms, one 1.07 with 1024 workgroups and
+// parts of 384 columns, 0.94 with 2048 and 192 (96 columns 0.96, 4096 workgroups
+// 0.96: more columns before the parts, fewer parts to order).
 constexpr uint32_t kMostLeft = 2048;
 constexpr uint32_t kMostParts = 4096;
-constexpr uint32_t kPart = 384;
+constexpr uint32_t kPart = 192;
+constexpr uint64_t kLeftBlocks = 2048;
 
+struct LeftLds {
+  uint32_t part[kMostParts];  // item | part << 11
+  uint32_t best_of[kMostLeft];
+  uint32_t cur[64];
+  uint32_t n_parts;
+};
+static_assert(kMostLeft == 1u << 11, "item bits of a part");
+
+// Items [t0, t0 + n), reads of W words, by one workgroup.
 template <int W, bool BOUNDED>
-__global__ __launch_bounds__(256) void k_verify_left(VerifyArgs a, uint64_t first, uint64_t count, uint32_t per) {
-  __shared__ uint32_t part[kMostParts];  // item | part << 11
-  __shared__ uint32_t best_of[kMostLeft];
-  __shared__ uint32_t cur[64];
-  __shared__ uint32_t n_parts;
-  static_assert(kMostLeft == 1u << 11, "item bits of a part");
+__device__ __forceinline__ void left_items(const VerifyArgs& a, uint64_t t0, uint32_t n, LeftLds& lds) {
+  uint32_t* const part = lds.part;
+  uint32_t* const best_of = lds.best_of;
+  uint32_t* const cur = lds.cur;
+  uint32_t& n_parts = lds.n_parts;
   const uint32_t t = threadIdx.x;
   if (t < 64) cur[t] = 0;
-  const uint64_t t0 = first + (uint64_t)blockIdx.x * per;
-  const uint32_t n = (uint32_t)min<uint64_t>(per, first + count - t0);
   for (uint32_t i = t; i < n; i += 256) best_of[i] = 0xFFFFFFFFu;
   // parts of a text: all but the last end kPart columns after the one before. A
   // text is cut where that saves its length by half; whole bins that the sift
@@ -800,19 +813,63 @@ __global__ __launch_bounds__(256) void k_verify_left(VerifyArgs a, uint64_t firs
   }
 }
 
+// The classes of reads of W0 .. W0 + 7 words in one launch: block[c] .. block[c + 1]
+// are the workgroups of words W0 + 7 - c (the longest alignments start first).
+struct LeftPlan {
+  uint32_t block[9];
+  uint32_t per;
+  uint64_t first[8], count[8];
+};
+
+// the cutoff pays off for reads of up to 6 words (measured: 1.3x at 4 and 5
+// words, 0.86x at 8, where lanes diverge over more words); longer reads run
+// the full column and cap the distance
+template <int W0>
+__global__ __launch_bounds__(256) void k_verify_left(VerifyArgs a, LeftPlan plan) {
+  __shared__ LeftLds lds;
+  uint32_t c = 0;
+  while (blockIdx.x >= plan.block[c + 1]) ++c;
+  const uint64_t at = (uint64_t)(blockIdx.x - plan.block[c]) * plan.per, t0 = plan.first[c] + at;
+  const uint32_t n = (uint32_t)min<uint64_t>(plan.per, plan.count[c] - at);
+  switch (c) {
+    case 0: left_items<W0 + 7, (W0 + 7 <= 6)>(a, t0, n, lds); break;
+    case 1: left_items<W0 + 6, (W0 + 6 <= 6)>(a, t0, n, lds); break;
+    case 2: left_items<W0 + 5, (W0 + 5 <= 6)>(a, t0, n, lds); break;
+    case 3: left_items<W0 + 4, (W0 + 4 <= 6)>(a, t0, n, lds); break;
+    case 4: left_items<W0 + 3, (W0 + 3 <= 6)>(a, t0, n, lds); break;
+    case 5: left_items<W0 + 2, (W0 + 2 <= 6)>(a, t0, n, lds); break;
+    case 6: left_items<W0 + 1, (W0 + 1 <= 6)>(a, t0, n, lds); break;
+    default: left_items<W0, (W0 <= 6)>(a, t0, n, lds); break;
+  }
+}
+
+template <int W0>
+hipError_t launch_left(const VerifyArgs& a, const uint64_t* first, const uint64_t* count, hipStream_t s) {
+  uint64_t total = 0, blocks = 0;
+  for (int c = 0; c < 8; ++c) total += count[W0 + c];
+  if (total == 0) return hipSuccess;
+  LeftPlan plan;
+  // part of the pairs are left after the sift, so a workgroup takes several for
+  // each of its lanes, where that leaves some for every CU
+  plan.per = (uint32_t)std::min<uint64_t>(kMostLeft, std::max<uint64_t>(256, total / kLeftBlocks));
+  for (int c = 0; c < 8; ++c) {
+    const int w = W0 + 7 - c;
+    plan.block[c] = (uint32_t)blocks;
+    plan.first[c] = first[w];
+    plan.count[c] = count[w];
+    blocks += (count[w] + plan.per - 1) / plan.per;
+    if (blocks > 0x7FFFFFFFull) return hipErrorInvalidConfiguration;
+  }
+  plan.block[8] = (uint32_t)blocks;
+  hipLaunchKernelGGL((k_verify_left<W0>), dim3((unsigned)blocks), dim3(256), 0, s, a, plan);
+  return hipGetLastError();
+}
+
 template <int W>
 hipError_t launch_align_w(const VerifyArgs& a, uint64_t first, uint64_t count, hipStream_t s) {
-  // bounded: part of the pairs are left after the sift, so a workgroup takes
-  // several for each of its lanes, where that leaves one for every CU
-  const uint64_t per = a.bounded ? std::min<uint64_t>(kMostLeft, std::max<uint64_t>(256, count / 512)) : 256;
-  const uint64_t blocks = (count + per - 1) / per;
+  const uint64_t blocks = (count + 255) / 256;
   if (blocks > 0x7FFFFFFFull) return hipErrorInvalidConfiguration;
-  const dim3 g((unsigned)blocks);
-  // the cutoff pays off for reads of up to 6 words (measured: 1.3x at 4 and 5
-  // words, 0.86x at 8, where lanes diverge over more words); longer reads run
-  // the full column and cap the distance
-  if (!a.bounded) hipLaunchKernelGGL((k_verify_align<W>), g, dim3(256), 0, s, a, first, count);
-  else hipLaunchKernelGGL((k_verify_left<W, (W <= 6)>), g, dim3(256), 0, s, a, first, count, (uint32_t)per);
+  hipLaunchKernelGGL((k_verify_align<W>), dim3((unsigned)blocks), dim3(256), 0, s, a, first, count);
   return hipGetLastError();
 }
 
@@ -853,6 +910,11 @@ hipError_t launch_verify_sift(const VerifyArgs& a, uint64_t count, hipStream_t s
   if (blocks > 0x7FFFFFFFull) return hipErrorInvalidConfiguration;
   hipLaunchKernelGGL(k_verify_sift, dim3((unsigned)blocks), dim3(256), 0, s, a, count);
   return hipGetLastError();
+}
+
+hipError_t launch_verify_left(const VerifyArgs& a, const uint64_t* first, const uint64_t* count, hipStream_t s) {
+  const hipError_t e = launch_left<1>(a, first, count, s);
+  return e == hipSuccess ? launch_left<9>(a, first, count, s) : e;
 }
 
 hipError_t launch_verify_align(const VerifyArgs& a, uint32_t words, uint64_t first, uint64_t count,
