@@ -15,18 +15,20 @@
 // 2k, ...; a seed at offset o found at p votes for bin max(p - o, 0) / B. The
 // read's candidates are its bins ranked by votes (more first), then by bin
 // (smaller first), the first `cap` kept, listed by increasing bin. On the GPU:
-//   1. hits per read (a thread per read: table lookups of its seeds);
+//   1. hits per read (a lane per seed: table lookups);
 //   2. reads are cut into batches whose staging (min(hits, cap) slots per
-//      read) is bounded, and sorted by hit count into four table sizes;
-//   3. a workgroup per read counts its bins' votes in an LDS hash table,
-//      picks the kept bins (vote threshold from a histogram, ties by a radix
-//      select on the bin) and writes them sorted to its staging slots;
-//   4. the few reads a table cannot describe exactly take a slower path in
-//      device memory (sort, runs, exact selection);
+//      read) is bounded, and grouped by hit count into launch shapes;
+//   3. a workgroup per read sorts its hits into buckets of bins in LDS, counts
+//      votes and places there, and writes the kept bins in order to its staging
+//      slots; reads of more hits than fit are thinned out first;
+//   4. the reads that does not suit take LDS hash tables, and the few a table
+//      cannot describe exactly a slower path in device memory (sort, runs, exact
+//      selection);
 //   5. a scan of the kept counts gives the CSR offsets, and the lists move
 //      from staging to their place.
 
 #include <algorithm>
+#include <cstddef>
 #include <cstdlib>
 #include <cstring>
 #include <memory>
@@ -48,6 +50,8 @@ struct grim_seeds {
   uint64_t* hits = nullptr;       // [n_reads] hits per read
   uint64_t* hits_host = nullptr;  // pinned copy
   uint64_t hits_cap = 0, hits_host_cap = 0;
+  uint2* found = nullptr;         // [n_bases / k + 1] seeds' table entries
+  uint64_t found_cap = 0;
   uint64_t* words = nullptr;      // [8]: CSR total so far (two words, by batch parity), bad offsets, fallback count
   uint32_t* tmp = nullptr;        // staging: kept bins per read
   uint64_t tmp_cap = 0;
@@ -63,6 +67,8 @@ struct grim_seeds {
   uint64_t list_cap = 0;
   uint32_t* redo = nullptr;       // [batch reads] reads for the fallback
   uint64_t redo_cap = 0;
+  uint32_t* hash = nullptr;       // [batch reads] reads for the hash tables
+  uint64_t hash_cap = 0;
   uint32_t* slab = nullptr;       // fallback work space
   uint64_t slab_cap = 0;
   uint64_t* toff_host = nullptr;  // pinned
@@ -193,27 +199,42 @@ __device__ __forceinline__ int64_t seed_code(const uint8_t* s, uint32_t k) {
   return ok ? (int64_t)code : -1;
 }
 
+// 16 lanes per read, a seed each at a time: first place in pos[] and hits of seed
+// j of a read that starts at base o to found[o / k + j] (seeds of different
+// reads share none of these), and the read's hits. Bound by the dependent
+// loads (offsets, bases, table): a thread per read, seed after seed, took 96 us
+// for 20011 reads of 100-250 bp, the lanes take 27.
 // A read whose offsets are out of order or outside [0, n_bases] gets no hits
 // and sets *bad; the call then fails before any later pass reads its bases.
 __global__ __launch_bounds__(256) void k_seed_hits(const uint64_t* start, uint32_t k, const uint8_t* bases,
                                                    uint64_t n_bases, const int64_t* offsets, uint64_t n,
-                                                   uint64_t* hits, uint32_t* bad) {
-  const uint64_t r = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+                                                   uint2* found, uint64_t* hits, uint32_t* bad) {
+  const uint64_t r = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 4;
+  const uint32_t j = threadIdx.x & 15u;
   if (r >= n) return;
   const int64_t o0 = offsets[r], o1 = offsets[r + 1];
   if (o0 < 0 || o1 < o0 || (uint64_t)o1 > n_bases) {
-    hits[r] = 0;
-    atomicOr(bad, 1u);
+    if (j == 0) {
+      hits[r] = 0;
+      atomicOr(bad, 1u);
+    }
     return;
   }
-  const uint8_t* rd = bases + o0;
-  const int64_t L = o1 - o0;
+  const uint64_t n_seeds = (uint64_t)(o1 - o0) / k, at = (uint64_t)o0 / k;
   uint64_t h = 0;
-  for (int64_t o = 0; o + (int64_t)k <= L; o += k) {
-    const int64_t c = seed_code(rd + o, k);
-    if (c >= 0) h += start[c + 1] - start[c];
+  for (uint64_t i = j; i < n_seeds; i += 16) {
+    const int64_t c = seed_code(bases + o0 + i * k, k);
+    uint2 f = make_uint2(0, 0);
+    if (c >= 0) {
+      const uint64_t b = start[c];
+      f = make_uint2((uint32_t)b, (uint32_t)(start[c + 1] - b));
+    }
+    found[at + i] = f;
+    h += f.y;
   }
-  hits[r] = h;
+  for (int d = 1; d < 16; d <<= 1)
+    h += ((uint64_t)(uint32_t)__shfl_xor((int)(uint32_t)(h >> 32), d) << 32) + (uint32_t)__shfl_xor((int)(uint32_t)h, d);
+  if (j == 0) hits[r] = h;
 }
 
 // ---------------------------------------------------------------------------
@@ -585,7 +606,8 @@ __global__ __launch_bounds__(256) void k_part_starts(const uint64_t* place, uint
 }
 
 // ---------------------------------------------------------------------------
-// Candidate selection, one workgroup per read, in LDS.
+// Candidate selection by hash tables, one workgroup per read, in LDS: the reads that
+// k_seed_sort and k_seed_large pass on.
 //
 // Each hit's bin goes into an open-addressing hash table of packed entries
 // (bin << vb | votes, linear probing, atomic compare-and-swap to claim a
@@ -614,6 +636,7 @@ struct SelArgs {
   const uint64_t* start;
   const uint32_t* pos;
   uint32_t k;
+  const uint2* found;        // the seeds' first places in pos[] and hits (k_seed_hits)
   const uint8_t* bases;
   const int64_t* offsets;
   uint64_t r0;               // first read of the batch
@@ -623,8 +646,9 @@ struct SelArgs {
   uint32_t* cnt;             // [batch reads] bins kept
   uint32_t* redo;            // [batch reads] reads handed to the fallback
   uint32_t* n_redo;          // their number
-  const uint32_t* list;      // batch-relative reads of this launch
-  uint32_t n_list;
+  uint32_t* hash;            // [batch reads] reads for the hash tables
+  uint32_t* n_hash;          // their number
+  const uint32_t* list;      // batch-relative reads of a k_seed_sort launch, a workgroup each
   uint32_t cap;
   uint32_t nbins;            // bins are below nbins
   uint32_t bin_bits;         // bits of nbins - 1
@@ -632,6 +656,7 @@ struct SelArgs {
   uint32_t dm, ds1, ds2;     // loc / B as (t + ((loc - t) >> ds1)) >> ds2, t = umulhi(dm, loc)
   uint32_t range_hits;       // hits per range for reads taken in ranges
   uint32_t force_ranges;     // take every read of the launch in ranges (tests)
+  uint32_t dbm;              // buckets / bins as a 32-bit fraction (k_seed_sort)
 };
 
 __device__ __forceinline__ uint32_t hit_bin(uint32_t p, uint64_t o, const SelArgs& a) {
@@ -724,8 +749,9 @@ __global__ __launch_bounds__(T) void k_seed_select(SelArgs a) {
   __shared__ uint32_t sh[9];
   const uint32_t t = threadIdx.x, lane = t & 63u;
   const uint32_t vmask = (1u << a.vb) - 1u;
-  for (uint32_t li = blockIdx.x; li < a.n_list; li += gridDim.x) {
-    const uint32_t i = a.list[li];
+  const uint32_t n_hash = *a.n_hash;
+  for (uint32_t li = blockIdx.x; li < n_hash; li += gridDim.x) {
+    const uint32_t i = a.hash[li];
     const uint64_t r = a.r0 + i;
     const uint64_t H = a.hits[r];
     if (t == 0) sh[2] = 0;  // read by no thread before the first clear()'s barrier
@@ -1156,6 +1182,456 @@ __global__ __launch_bounds__(T) void k_seed_select(SelArgs a) {
   }
 }
 
+// The same selection for reads of up to T * HPT hits, by buckets of bins in
+// ascending order. A hit's bucket hands it its rank there (one LDS atomic), a
+// scan of the buckets' sizes and one store group the hits by bucket, and a hit
+// counts its bin's votes and the smaller bins among the few hits of its bucket:
+// that is its place among the read's hits in order of bins. Kept bins are flagged
+// there, and the flags' prefix counts are their places in the list: no probe
+// chains, no radix select over the ties and no sort. Bound by instructions and the
+// dependent loads that start a read (a third of its 25 us), which the other
+// workgroups of a CU hide: 19241 reads of up to 24576 hits on the 3.1 Gbp reference
+// (77 M hits) take 0.57 ms, the hash tables took 1.7.
+// A read with more than kSeedBucket hits in one bucket, or more seeds than the
+// lists hold, goes on to the hash tables.
+constexpr uint32_t kSeedBucket = 255;
+
+template <int T, int HPT, int SPT>
+struct SortLds {
+  static constexpr uint32_t S = SPT * T, HMAX = HPT * T, kSeeds = T < 256 ? T : 256;
+  static_assert(SPT % 4 == 0 && HMAX % 32 == 0 && HMAX / 32 <= T && HMAX < 65536 && HMAX / 4 <= S, "shape");
+  uint32_t cnt[S + 4];             // a bucket's hits, then its first place; later a byte per place
+  uint32_t out[HMAX + 4];          // bins by bucket
+  uint32_t hist[kSeedBucket + 1];  // [v]: bins with v votes
+  uint32_t s_h0[kSeeds];           // a seed's first position in pos[]
+  uint32_t s_pre[kSeeds + 1];      // hits of the seeds before it
+  uint32_t ws[T / 64 + 1];
+  uint32_t sh[4];
+};
+
+// Takes the read's n_seeds <= kSeeds seeds; returns its hits. Clears hist and sh.
+template <int T, typename Lds>
+__device__ __forceinline__ uint32_t sort_seeds(const uint2* found, uint32_t n_seeds, Lds& m) {
+  const uint32_t t = threadIdx.x;
+  uint32_t h0 = 0, c = 0;
+  if (t < n_seeds) {
+    const uint2 f = found[t];
+    h0 = f.x;
+    c = f.y;
+  }
+  for (uint32_t v = t; v <= kSeedBucket; v += T) m.hist[v] = 0;
+  if (t < 4) m.sh[t] = 0;
+  uint32_t H;
+  const uint32_t ex = block_excl_scan<T, uint32_t>(c, m.ws, &H);
+  if (t < Lds::kSeeds) {
+    m.s_h0[t] = h0;
+    m.s_pre[t] = ex;  // threads past the seeds hold H
+  }
+  if (t == 0) m.s_pre[Lds::kSeeds] = H;
+  __syncthreads();
+  return H;
+}
+
+// Bins of hits f0 + h T, h < N, below H (the seed of the first is s or later);
+// the positions are all loaded before the first is used.
+template <int T, int N, typename Lds>
+__device__ __forceinline__ void hit_bins(const SelArgs& a, const Lds& m, uint32_t f0, uint32_t H, uint32_t& s,
+                                         uint32_t (&bin)[N]) {
+  uint32_t o[N];
+#pragma unroll
+  for (int h = 0; h < N; ++h) {
+    const uint32_t f = f0 + h * T;
+    bin[h] = 0;
+    o[h] = 0;
+    if (f < H) {
+      while (m.s_pre[s + 1] <= f) ++s;
+      bin[h] = a.pos[m.s_h0[s] + (f - m.s_pre[s])];
+      o[h] = s * a.k;
+    }
+  }
+#pragma unroll
+  for (int h = 0; h < N; ++h) bin[h] = hit_bin(bin[h], o[h], a);
+}
+
+// The value in a register of its own: what is computed from it is not kept for
+// later uses (twelve t + h T, kept over all phases of sort_select, spilled).
+__device__ __forceinline__ uint32_t afresh(uint32_t x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
+// Thread t's hits are those numbered t + h T < H. cnt and hist are zero. Writes
+// the kept bins and their number, or returns false with nothing written: a bucket
+// is too full, or the vote threshold is below `least` (0: none is).
+template <int T, int HPT, int SPT>
+__device__ __forceinline__ bool sort_select(const SelArgs& a, uint32_t i, uint32_t H, uint32_t (&bin)[HPT],
+                                            uint32_t least, SortLds<T, HPT, SPT>& m) {
+  constexpr uint32_t S = SPT * T, HMAX = HPT * T;
+  uint32_t* const cnt = m.cnt;
+  uint32_t* const out = m.out;
+  const uint32_t t = threadIdx.x, lane = t & 63u;
+  uint32_t rank[HPT];
+#pragma unroll
+  for (int h = 0; h < HPT; ++h)
+    if (t + h * T < H) rank[h] = atomicAdd(&cnt[__umulhi(bin[h], a.dbm)], 1u);
+  __syncthreads();
+  {
+    uint32_t v[SPT], sum = 0, most = 0;
+#pragma unroll
+    for (uint32_t u = 0; u < SPT; u += 4) {
+      const uint4 q = *reinterpret_cast<const uint4*>(cnt + SPT * t + u);
+      v[u] = q.x; v[u + 1] = q.y; v[u + 2] = q.z; v[u + 3] = q.w;
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < SPT; ++u) {
+      const uint32_t x = v[u];
+      most = max(most, x);
+      v[u] = sum;
+      sum += x;
+    }
+    if (most > kSeedBucket) m.sh[0] = 1;
+    uint32_t all;
+    const uint32_t at = block_excl_scan<T, uint32_t>(sum, m.ws, &all);
+#pragma unroll
+    for (uint32_t u = 0; u < SPT; u += 4)
+      *reinterpret_cast<uint4*>(cnt + SPT * t + u) = make_uint4(at + v[u], at + v[u + 1], at + v[u + 2], at + v[u + 3]);
+    if (t == 0) cnt[S] = H;
+  }
+  __syncthreads();
+  if (m.sh[0]) return false;
+#pragma unroll
+  for (int h = 0; h < HPT; ++h)
+    if (afresh(t) + h * T < H) out[cnt[__umulhi(bin[h], a.dbm)] + rank[h]] = bin[h];
+  if (t < 4) out[H + t] = kEmpty;  // after the last: larger than any bin
+  __syncthreads();
+  // of the hit at place p: its bin's votes, and its place by bin and then p; only
+  // the first hit of a bin goes on (0 otherwise)
+  uint32_t(&info)[HPT] = rank;  // place | votes << 16
+  uint32_t n1 = 0, n2 = 0;
+  constexpr int N = 2;  // hits a thread has in flight
+  static_assert(HPT % N == 0, "groups of hits");
+#pragma unroll
+  for (int h0 = 0; h0 < HPT; h0 += N) {
+    // the hits before its bucket are of smaller bins, those after of larger ones,
+    // so whole groups of four places do; backwards, the last match is the bin's first hit
+    const uint32_t first = afresh(t) + h0 * T;
+    uint32_t j0[N], j1[N];
+    uint32_t own[N];
+    uint4 q0[N];
+#pragma unroll
+    for (int g = 0; g < N; ++g) own[g] = out[min(first + g * T, HMAX - 1)];
+#pragma unroll
+    for (int g = 0; g < N; ++g) {
+      j0[g] = j1[g] = 0;
+      if (first + g * T < H) {
+        const uint32_t b = __umulhi(own[g], a.dbm);
+        j0[g] = cnt[b] & ~3u;
+        j1[g] = (cnt[b + 1] + 3u) & ~3u;
+      }
+    }
+#pragma unroll
+    for (int g = 0; g < N; ++g) q0[g] = *reinterpret_cast<const uint4*>(out + j0[g]);
+#pragma unroll
+    for (int g = 0; g < N; ++g) {
+      const uint32_t p = first + g * T, mine = own[g];
+      uint32_t place = j0[g], head = p, votes = 0;
+      auto look = [&](uint32_t j, const uint4& q) {
+        const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+        for (int u = 3; u >= 0; --u) {
+          place += w[u] < mine;
+          votes += w[u] == mine;
+          head = w[u] == mine ? j + (uint32_t)u : head;
+        }
+      };
+      for (uint32_t j = j1[g]; j > j0[g] + 4;) {
+        j -= 4;
+        look(j, *reinterpret_cast<const uint4*>(out + j));
+      }
+      look(j0[g], q0[g]);
+      if (head != p || p >= H) votes = 0;
+      rank[h0 + g] = afresh(place | votes << 16);
+      n1 += (uint32_t)__popcll(__ballot(votes == 1u));
+      n2 += (uint32_t)__popcll(__ballot(votes == 2u));
+      if (votes > 2u) atomicAdd(&m.hist[votes], 1u);
+    }
+  }
+  if (lane == 0) {
+    if (n1) atomicAdd(&m.hist[1], n1);
+    if (n2) atomicAdd(&m.hist[2], n2);
+  }
+  __syncthreads();
+  // the vote threshold (wavefront 0; lane l holds votes 4l .. 4l + 3); cnt becomes the flags
+  for (uint32_t w = t; w < HMAX / 4; w += T) cnt[w] = 0;
+  if (t < 64) {
+    uint32_t hv[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) hv[j] = m.hist[4 * lane + j];
+    const uint32_t mine = hv[0] + hv[1] + hv[2] + hv[3];
+    const uint32_t incl = wave_incl_scan(mine, lane);
+    const uint32_t all = (uint32_t)__shfl((int)incl, 63);
+    uint32_t vt = 0, over = 0, run = all - incl;  // bins with more votes
+    for (int j = 3; j >= 0; --j) {
+      const uint32_t v = 4 * lane + (uint32_t)j;
+      if (!vt && v >= 1 && run + hv[j] >= a.cap) {
+        vt = v;
+        over = run;
+      }
+      run += hv[j];
+    }
+    const uint64_t found = __ballot(vt != 0);
+    if (lane == 0 && all <= a.cap) {  // every bin
+      m.sh[1] = 0;
+      m.sh[2] = 0;
+      m.sh[3] = all;
+    } else if (all > a.cap && lane == 63u - (uint32_t)__clzll(found)) {  // the largest vt
+      m.sh[1] = vt;
+      m.sh[2] = a.cap - over;
+      m.sh[3] = a.cap;
+    }
+  }
+  __syncthreads();
+  const uint32_t vt = m.sh[1], need = m.sh[2];
+  if (vt < least) return false;
+  uint8_t* const flag = reinterpret_cast<uint8_t*>(cnt);  // by place: 1 more than vt votes, 2 as many
+#pragma unroll
+  for (int h = 0; h < HPT; ++h) {
+    const uint32_t v = info[h] >> 16, p = info[h] & 0xFFFFu;
+    if (v && v >= vt) flag[p] = v > vt ? 1 : 2;
+  }
+  __syncthreads();
+  // the flags as bitmaps, and their counts before every 32 places
+  uint32_t up = 0, eq = 0;
+  if (t < HMAX / 32) {
+#pragma unroll
+    for (uint32_t u = 0; u < 2; ++u) {
+      const uint4 q = *reinterpret_cast<const uint4*>(cnt + 8 * t + 4 * u);
+      const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+      for (uint32_t j = 0; j < 4; ++j) {
+        up |= __builtin_amdgcn_udot4(w[j] & 0x01010101u, 0x08040201u, 0u, false) << (16 * u + 4 * j);
+        eq |= __builtin_amdgcn_udot4((w[j] >> 1) & 0x01010101u, 0x08040201u, 0u, false) << (16 * u + 4 * j);
+      }
+    }
+  }
+  uint32_t all;
+  const uint32_t pc = block_excl_scan<T, uint32_t>((uint32_t)__popc(up) | (uint32_t)__popc(eq) << 16, m.ws, &all);
+  uint32_t* const above = cnt;  // every flag has been read
+  uint32_t* const ties = cnt + HMAX / 32;
+  uint32_t* const pre = cnt + 2 * (HMAX / 32);
+  if (t < HMAX / 32) {
+    above[t] = up;
+    ties[t] = eq;
+    pre[t] = pc;
+  }
+  __syncthreads();
+  const uint64_t out0 = a.tmp_off[i];
+#pragma unroll
+  for (int h = 0; h < HPT; ++h) {
+    const uint32_t v = info[h] >> 16, p = info[h] & 0xFFFFu;
+    if (!v || v < vt) continue;
+    const uint32_t below = (1u << (p & 31u)) - 1u, w = pre[p >> 5];
+    const uint32_t na = (w & 0xFFFFu) + (uint32_t)__popc(above[p >> 5] & below);
+    const uint32_t nt = (w >> 16) + (uint32_t)__popc(ties[p >> 5] & below);
+    if (v > vt || nt < need) a.tmp[out0 + na + min(nt, need)] = out[afresh(t) + h * T];
+  }
+  if (t == 0) a.cnt[i] = m.sh[3];
+  return true;
+}
+
+__device__ __forceinline__ void to_hash(const SelArgs& a, uint32_t i) {
+  if (threadIdx.x == 0) a.hash[atomicAdd(a.n_hash, 1u)] = i;
+}
+
+template <int T, int HPT, int SPT>
+__global__ __launch_bounds__(T) void k_seed_sort(SelArgs a) {
+  __shared__ __attribute__((aligned(16))) SortLds<T, HPT, SPT> m;
+  const uint32_t t = threadIdx.x;
+  constexpr int N = 6;
+  const uint32_t i = a.list[blockIdx.x];
+  const int64_t o0 = a.offsets[a.r0 + i];
+  const uint64_t n_seeds = (uint64_t)(a.offsets[a.r0 + i + 1] - o0) / a.k;
+  if (n_seeds > m.kSeeds) {
+    to_hash(a, i);
+    return;
+  }
+#pragma unroll
+  for (uint32_t u = 0; u < SPT; u += 4) *reinterpret_cast<uint4*>(m.cnt + SPT * t + u) = make_uint4(0, 0, 0, 0);
+  // H <= HMAX: the host chose T by the same counts
+  const uint32_t H = sort_seeds<T>(a.found + (uint64_t)o0 / a.k, (uint32_t)n_seeds, m);
+  uint32_t bin[HPT], s = 0;
+#pragma unroll
+  for (int h0 = 0; h0 < HPT; h0 += N) {
+    uint32_t some[N];
+    hit_bins<T, N>(a, m, afresh(t) + h0 * T, H, s, some);
+#pragma unroll
+    for (int h = 0; h < N; ++h) bin[h0 + h] = some[h];
+  }
+  if (!sort_select<T, HPT, SPT>(a, i, H, bin, 0, m)) to_hash(a, i);
+}
+
+// Reads of more hits than that: the hits are first counted by cell, the bins
+// dealt to kCells of them. A bin has no more votes than its cell, so of the hits
+// only those in cells of at least `least` are selected from, `least` being the
+// smallest number from 2 on that leaves as many as fit. Where 2 leaves too many,
+// those of cells of 2 or more are dealt anew, to other cells, first. The selection
+// is exact if the vote threshold comes out no lower than `least`, as it does where
+// a read has more than cap bins of several votes (a read in a repeat: the
+// 770 reads of 24577-80448 hits among 20011 on the 3.1 Gbp reference at cap
+// 1024); else the read goes on to the hash tables. Two or three walks over the
+// hits (40 k: 160 KB each, from the caches after the first) and no table of bins:
+// the hash tables, which fill at such sizes and are taken in ranges of bins, took
+// 1.29 ms for those 770 reads.
+constexpr uint32_t kCells = 1u << 16;
+using CellLds = SortLds<1024, 24, 8>;
+
+// The hits to select from to out, their number to sh[2]; returns `least`, or 0 where
+// the cells cannot tell.
+__device__ __forceinline__ uint32_t cells_of(const SelArgs& a, uint32_t H, uint32_t cell_f, CellLds& m,
+                                             uint32_t (&many)[2][kCells / 32]) {
+  constexpr uint32_t T = 1024, SPT = 8, kWords = kCells / 2, kPer = kWords / 4 / T;
+  uint32_t* const cells = m.cnt;  // two to a word, over cnt and out
+  static_assert(offsetof(CellLds, out) == sizeof m.cnt && sizeof m.cnt + sizeof m.out >= 4 * kWords, "cells");
+  const uint32_t t = threadIdx.x, lane = t & 63u;
+  constexpr int N = 8;  // hits a thread has in flight
+  // its cell in a round: runs of consecutive bins, then the top bits of a product
+  auto cell = [&](uint32_t bin, uint32_t round) {
+    return round == 0 ? __umulhi(bin, cell_f) : (bin * 0x9E3779B1u) >> 16;
+  };
+  auto listed = [&](uint32_t bin, uint32_t round) {
+    const uint32_t c = cell(bin, round);
+    return (many[round][c >> 5] >> (c & 31u)) & 1u;
+  };
+  auto each = [&](const uint4& q, auto f) {
+    const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+    for (uint32_t j = 0; j < 8; ++j) f(j, (w[j >> 1] >> (16 * (j & 1u))) & 0xFFFFu);
+  };
+  uint32_t least = 0, round = 0;
+  for (;; ++round) {
+#pragma unroll
+    for (uint32_t u = 0; u < kPer; ++u) reinterpret_cast<uint4*>(cells)[u * T + t] = make_uint4(0, 0, 0, 0);
+    for (uint32_t w = t; w <= kSeedBucket; w += T) m.hist[w] = 0;
+    if (t == 0) m.sh[1] = 0;
+    __syncthreads();
+    for (uint32_t f0 = t, s = 0; f0 < H; f0 += N * T) {
+      uint32_t bin[N];
+      hit_bins<T, N>(a, m, f0, H, s, bin);
+#pragma unroll
+      for (int h = 0; h < N; ++h)
+        if (f0 + h * T < H && (round == 0 || listed(bin[h], 0))) {
+          const uint32_t c = cell(bin[h], round), shift = 16 * (c & 1u);
+          if (((atomicAdd(&cells[c >> 1], 1u << shift) >> shift) & 0xFFFFu) == 0xFFFFu) m.sh[0] = 1;
+        }
+    }
+    __syncthreads();
+    if (m.sh[0]) return 0;  // a cell's count ran over
+    // hits by the count of their cell, 255 or more together
+    uint4 v[kPer];
+    uint32_t n2 = 0;
+#pragma unroll
+    for (uint32_t u = 0; u < kPer; ++u) {
+      v[u] = reinterpret_cast<const uint4*>(cells)[u * T + t];
+      each(v[u], [&](uint32_t, uint32_t n) {
+        n2 += n == 2 ? 2u : 0u;
+        if (n > 2) atomicAdd(&m.hist[min(n, 255u)], n);
+      });
+    }
+    for (int d = 1; d < 64; d <<= 1) n2 += (uint32_t)__shfl_xor((int)n2, d);
+    if (lane == 0) atomicAdd(&m.hist[2], n2);
+    __syncthreads();
+    if (t < 64) {
+      uint32_t hv[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) hv[j] = m.hist[4 * lane + j];
+      const uint32_t incl = wave_incl_scan(hv[0] + hv[1] + hv[2] + hv[3], lane);
+      uint32_t run = (uint32_t)__shfl((int)incl, 63) - incl, fit = 0;
+      for (int j = 3; j >= 0; --j) {
+        const uint32_t n = 4 * lane + (uint32_t)j;
+        run += hv[j];  // hits in cells of n or more
+        if (n >= 2 && run <= m.HMAX) fit = n;
+      }
+      const uint64_t found = __ballot(fit != 0);
+      if (found && lane == (uint32_t)__builtin_ctzll(found)) m.sh[1] = fit;
+    }
+    __syncthreads();
+    least = m.sh[1];
+    const bool last = least == 2 || round == 1;
+    if (last && least == 0) return 0;  // more than fit in cells of 255 or more
+    const uint32_t from = last ? least : 2u;
+#pragma unroll
+    for (uint32_t u = 0; u < kPer; ++u) {
+      uint32_t bits = 0;
+      each(v[u], [&](uint32_t j, uint32_t n) { bits |= n >= from ? 1u << j : 0u; });
+      reinterpret_cast<uint8_t*>(many[round])[u * T + t] = (uint8_t)bits;
+    }
+    if (last) break;
+    __syncthreads();
+  }
+#pragma unroll
+  for (uint32_t u = 0; u < SPT; u += 4) *reinterpret_cast<uint4*>(m.cnt + SPT * t + u) = make_uint4(0, 0, 0, 0);
+  __syncthreads();  // the threshold has been read from hist
+  for (uint32_t w = t; w <= kSeedBucket; w += T) m.hist[w] = 0;
+  // the hits in those cells, in any order, to out
+  for (uint32_t b0 = 0, s = 0; b0 < H; b0 += N * T) {
+    uint32_t bin[N];
+    hit_bins<T, N>(a, m, b0 + t, H, s, bin);
+#pragma unroll
+    for (int h = 0; h < N; ++h) {
+      const bool in = b0 + t + h * T < H && listed(bin[h], 0) && (round == 0 || listed(bin[h], 1));
+      const uint64_t who = __ballot(in);
+      uint32_t at = 0;
+      if (lane == 0 && who) at = atomicAdd(&m.sh[2], (uint32_t)__popcll(who));
+      at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+      if (in) m.out[at + (uint32_t)__popcll(who & ((1ull << lane) - 1ull))] = bin[h];
+    }
+  }
+  __syncthreads();
+  return least;
+}
+
+// Reads of the two largest classes, a workgroup to a CU each, from the list's end:
+// its last n_cells by cells, the others as they are (in one launch: 770 of the
+// former are three rounds of 256 CUs and two more).
+__global__ __launch_bounds__(1024) void k_seed_large(SelArgs a, uint32_t n_cells, uint32_t cell_f) {
+  constexpr int T = 1024, HPT = 24, SPT = 8, N = 8;
+  __shared__ __attribute__((aligned(16))) CellLds m;
+  __shared__ uint32_t many[2][kCells / 32];  // a bit per cell of a round: its hits go on
+  const uint32_t t = threadIdx.x;
+  const uint32_t i = a.list[gridDim.x - 1 - blockIdx.x];
+  const int64_t o0 = a.offsets[a.r0 + i];
+  const uint64_t n_seeds = (uint64_t)(a.offsets[a.r0 + i + 1] - o0) / a.k;
+  if (n_seeds > CellLds::kSeeds) {
+    to_hash(a, i);
+    return;
+  }
+#pragma unroll
+  for (uint32_t u = 0; u < SPT; u += 4) *reinterpret_cast<uint4*>(m.cnt + SPT * t + u) = make_uint4(0, 0, 0, 0);
+  const uint32_t H = sort_seeds<T>(a.found + (uint64_t)o0 / a.k, (uint32_t)n_seeds, m);
+  uint32_t bin[HPT], left = H, least = 0;
+  if (blockIdx.x < n_cells) {
+    least = cells_of(a, H, cell_f, m, many);
+    if (least == 0) {
+      to_hash(a, i);
+      return;
+    }
+    left = m.sh[2];
+#pragma unroll
+    for (int h = 0; h < HPT; ++h) bin[h] = t + h * T < left ? m.out[t + h * T] : 0u;
+    __syncthreads();
+  } else {
+    uint32_t s = 0;
+#pragma unroll
+    for (int h0 = 0; h0 < HPT; h0 += N) {
+      uint32_t some[N];
+      hit_bins<T, N>(a, m, afresh(t) + h0 * T, H, s, some);
+#pragma unroll
+      for (int h = 0; h < N; ++h) bin[h0 + h] = some[h];
+    }
+  }
+  if (!sort_select<T, HPT, SPT>(a, i, left, bin, least, m)) to_hash(a, i);
+}
+
 // ---------------------------------------------------------------------------
 // Fallback, one wavefront per read: every hit's bin into the wavefront's slab
 // of device memory, a bitonic sort there, runs of equal bins become (bin,
@@ -1341,9 +1817,9 @@ void free_seeds(grim_seeds* sd) {
   if (!sd) return;
   SeedGuard g(sd->device);
   (void)hipDeviceSynchronize();  // the pool's blocks may go to any stream next
-  for (void* p : {(void*)sd->start, (void*)sd->pos, (void*)sd->hits, (void*)sd->words, (void*)sd->tmp,
+  for (void* p : {(void*)sd->start, (void*)sd->pos, (void*)sd->hits, (void*)sd->found, (void*)sd->words, (void*)sd->tmp,
                   (void*)sd->toff, (void*)sd->outoff, (void*)sd->bsum, (void*)sd->cnt, (void*)sd->list,
-                  (void*)sd->redo, (void*)sd->slab, (void*)sd->staging})
+                  (void*)sd->redo, (void*)sd->hash, (void*)sd->slab, (void*)sd->staging})
     pool_free(p);
   for (void* p : {(void*)sd->hits_host, (void*)sd->total_host, (void*)sd->toff_host, (void*)sd->list_host})
     if (p) (void)hipHostFree(p);
@@ -1367,12 +1843,23 @@ int env_int(const char* name, int dflt) {
 }
 bool env_flag(const char* name) { return env_int(name, 0) != 0; }
 
-// Table size class of a read with h hits (h <= the class's 3/4-full table).
-// Table sizes (threads, entries): a class's table holds its reads' hits at
-// most 3/4 full; smaller tables leave room for more workgroups per CU.
-constexpr uint32_t kSeedClasses = 6;
-uint32_t seed_class(uint64_t h) {
-  return h <= 768 ? 0u : h <= 1536 ? 1u : h <= 3072 ? 2u : h <= 6144 ? 3u : h <= 12288 ? 4u : 5u;
+// The kernel of a read with h hits: k_seed_sort of the fewest threads and LDS that
+// hold them, which leaves room for more workgroups per CU; k_seed_cells beyond. The
+// hash tables take what these pass on.
+constexpr uint32_t kSeedClasses = 8, kSeedCells = 6, kSeedHash = 7;
+uint32_t seed_class(uint64_t h) {  // sums, as the classes come in no order a branch could learn
+  return uint32_t(h > 768) + uint32_t(h > 1536) + uint32_t(h > 3072) + uint32_t(h > 6144) + uint32_t(h > 12288) +
+         uint32_t(h > 24576);
+}
+
+// Buckets a bin as a 32-bit fraction: umulhi(bin, f) < buckets for bin < nbins.
+uint32_t bucket_factor(uint32_t buckets, uint32_t nbins) {
+  return (uint32_t)std::min<uint64_t>(((uint64_t)buckets << 32) / nbins, 0xFFFFFFFFull);
+}
+template <int T, int HPT, int SPT>
+void launch_seed_sort(SelArgs a, uint64_t n, hipStream_t s) {
+  a.dbm = bucket_factor(T * SPT, a.nbins);
+  hipLaunchKernelGGL((k_seed_sort<T, HPT, SPT>), dim3((unsigned)n), dim3(T), 0, s, a);
 }
 
 // n / d for every 32-bit n as (t + ((n - t) >> s1)) >> s2 with t = umulhi(m, n)
@@ -1573,6 +2060,7 @@ int grim_seed_candidates(const grim_seeds* csd, const grim_reads* rd, uint32_t b
   // 1. hits per read
   int rc = grow_dev(&sd->hits, &sd->hits_cap, n);
   if (rc) return rc;
+  if ((rc = grow_dev(&sd->found, &sd->found_cap, rd->n_bases / sd->k + 1))) return rc;
   if (sd->hits_host_cap < n || !sd->hits_host) {
     if (sd->hits_host) (void)hipHostFree(sd->hits_host);
     sd->hits_host = nullptr;
@@ -1583,9 +2071,10 @@ int grim_seed_candidates(const grim_seeds* csd, const grim_reads* rd, uint32_t b
   if (!sd->words) GRIM_HIP_TRY(pool_alloc(&sd->words, 8 * sizeof(uint64_t)));
   uint32_t* bad = reinterpret_cast<uint32_t*>(sd->words + 2);
   uint32_t* n_redo = reinterpret_cast<uint32_t*>(sd->words + 3);
+  uint32_t* n_hash = reinterpret_cast<uint32_t*>(sd->words + 4);
   GRIM_HIP_TRY(launch_zero_words(reinterpret_cast<uint32_t*>(sd->words), 16, s));  // base, bad, n_redo
-  hipLaunchKernelGGL(k_seed_hits, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, sd->start, sd->k, bases,
-                     rd->n_bases, offsets, n, sd->hits, bad);
+  hipLaunchKernelGGL(k_seed_hits, dim3((unsigned)((n + 15) / 16)), dim3(256), 0, s, sd->start, sd->k, bases,
+                     rd->n_bases, offsets, n, sd->found, sd->hits, bad);
   GRIM_HIP_TRY(hipGetLastError());
   GRIM_HIP_TRY(hipMemcpyAsync(sd->hits_host, sd->hits, n * sizeof(uint64_t), hipMemcpyDeviceToHost, s));
   uint32_t* bad_host = reinterpret_cast<uint32_t*>(sd->total_host + 3);
@@ -1601,11 +2090,12 @@ int grim_seed_candidates(const grim_seeds* csd, const grim_reads* rd, uint32_t b
   uint32_t vb = 32u - key_bits;
   if (const char* e = std::getenv("GRIM_SEED_VOTE_BITS")) vb = std::min<uint32_t>(vb, (uint32_t)std::max(1, std::atoi(e)));
   const bool all_fallback = vb < 2 || env_flag("GRIM_SEED_FALLBACK_ALL");
-  const uint32_t class_min = (uint32_t)std::min((int)kSeedClasses - 1, std::max(0, env_int("GRIM_SEED_CLASS_MIN", 0)));
+  uint32_t class_min = (uint32_t)std::min((int)kSeedHash, std::max(0, env_int("GRIM_SEED_CLASS_MIN", 0)));
   SelArgs a{};
   a.start = sd->start;
   a.pos = sd->pos;
   a.k = sd->k;
+  a.found = sd->found;
   a.bases = bases;
   a.offsets = offsets;
   a.hits = sd->hits;
@@ -1616,7 +2106,9 @@ int grim_seed_candidates(const grim_seeds* csd, const grim_reads* rd, uint32_t b
   make_div(bin_size, &a.dm, &a.ds1, &a.ds2);
   a.range_hits = (uint32_t)std::max(1, env_int("GRIM_SEED_RANGE_HITS", 16384));
   a.force_ranges = env_flag("GRIM_SEED_FORCE_RANGES") ? 1u : 0u;
+  if (a.force_ranges || std::getenv("GRIM_SEED_VOTE_BITS")) class_min = kSeedHash;
   a.n_redo = n_redo;
+  a.n_hash = n_hash;
   // 2. batches of bounded staging (each read takes min(hits, cap) slots),
   // planned before anything is launched: every buffer is then allocated
   // once, each batch's host arrays have a region of their own, and batches
@@ -1664,6 +2156,7 @@ int grim_seed_candidates(const grim_seeds* csd, const grim_reads* rd, uint32_t b
   if ((rc = grow_dev(&sd->cnt, &sd->cnt_cap, nb_max))) return rc;
   if ((rc = grow_dev(&sd->list, &sd->list_cap, nb_max))) return rc;
   if ((rc = grow_dev(&sd->redo, &sd->redo_cap, nb_max))) return rc;
+  if ((rc = grow_dev(&sd->hash, &sd->hash_cap, nb_max))) return rc;
   if ((rc = grow_dev(&sd->slab, &sd->slab_cap, slab_words * fb_waves))) return rc;
   uint64_t nbatch = 0;
   for (const Batch& bt : plan) {
@@ -1703,28 +2196,47 @@ int grim_seed_candidates(const grim_seeds* csd, const grim_reads* rd, uint32_t b
     GRIM_HIP_TRY(launch_zero_words(sd->cnt, (uint32_t)nb, s));
     if (listed) GRIM_HIP_TRY(hipMemcpyAsync(all_fallback ? sd->redo : sd->list, list_h, listed * sizeof(uint32_t),
                                             hipMemcpyHostToDevice, s));
+    const uint64_t n_big = per_class[kSeedHash];
+    if (n_big) GRIM_HIP_TRY(hipMemcpyAsync(sd->hash, list_h + first[kSeedHash], n_big * sizeof(uint32_t),
+                                           hipMemcpyHostToDevice, s));
     GRIM_HIP_TRY(launch_fill_word(n_redo, all_fallback ? (uint32_t)n_fb : 0u, s));
+    GRIM_HIP_TRY(launch_fill_word(n_hash, (uint32_t)n_big, s));
     a.r0 = r0;
     a.tmp_off = sd->toff;
     a.tmp = sd->tmp;
     a.cnt = sd->cnt;
     a.redo = sd->redo;
+    a.hash = sd->hash;
     // 3. each read's kept bins, in LDS, one workgroup per read
     if (!all_fallback) {
-      for (uint32_t c = 0; c < kSeedClasses; ++c) {
+      // the largest first: the others fill the chip as they end
+      const uint64_t n_large = per_class[kSeedCells - 1] + per_class[kSeedCells];
+      if (n_large) {
+        SelArgs b = a;
+        b.list = sd->list + first[kSeedCells - 1];
+        b.dbm = bucket_factor(CellLds::S, a.nbins);
+        hipLaunchKernelGGL(k_seed_large, dim3((unsigned)n_large), dim3(1024), 0, s, b, (uint32_t)per_class[kSeedCells],
+                           bucket_factor(kCells, a.nbins));
+        GRIM_HIP_TRY(hipGetLastError());
+      }
+      for (int c = (int)kSeedCells - 2; c >= 0; --c) {
         if (!per_class[c]) continue;
         SelArgs b = a;
         b.list = sd->list + first[c];
-        b.n_list = (uint32_t)per_class[c];
-        const dim3 grid((unsigned)std::min<uint64_t>(per_class[c], 1u << 30));
+        const uint64_t m = per_class[c];
         switch (c) {
-          case 0: hipLaunchKernelGGL((k_seed_select<64, 1024>), grid, dim3(64), 0, s, b); break;
-          case 1: hipLaunchKernelGGL((k_seed_select<128, 2048>), grid, dim3(128), 0, s, b); break;
-          case 2: hipLaunchKernelGGL((k_seed_select<256, 4096>), grid, dim3(256), 0, s, b); break;
-          case 3: hipLaunchKernelGGL((k_seed_select<256, 8192>), grid, dim3(256), 0, s, b); break;
-          case 4: hipLaunchKernelGGL((k_seed_select<512, 16384>), grid, dim3(512), 0, s, b); break;
-          default: hipLaunchKernelGGL((k_seed_select<1024, 32768>), grid, dim3(1024), 0, s, b); break;
+          case 0: launch_seed_sort<64, 12, 8>(b, m, s); break;
+          case 1: launch_seed_sort<128, 12, 8>(b, m, s); break;
+          case 2: launch_seed_sort<256, 12, 8>(b, m, s); break;
+          case 3: launch_seed_sort<512, 12, 8>(b, m, s); break;
+          default: launch_seed_sort<1024, 12, 4>(b, m, s); break;
         }
+        GRIM_HIP_TRY(hipGetLastError());
+      }
+      // the reads they passed on, and those too large for them
+      if (listed) {
+        hipLaunchKernelGGL((k_seed_select<1024, 32768>), dim3((unsigned)std::min<uint64_t>(listed, std::max<uint64_t>(n_big, 256))),
+                           dim3(1024), 0, s, a);
         GRIM_HIP_TRY(hipGetLastError());
       }
     }
