@@ -1844,12 +1844,12 @@ int env_int(const char* name, int dflt) {
 bool env_flag(const char* name) { return env_int(name, 0) != 0; }
 
 // The kernel of a read with h hits: k_seed_sort of the fewest threads and LDS that
-// hold them, which leaves room for more workgroups per CU; k_seed_cells beyond. The
-// hash tables take what these pass on.
+// hold them, which leaves room for more workgroups per CU; by cells beyond, up to
+// where 32-bit hit numbers are safe. The hash tables take what these pass on.
 constexpr uint32_t kSeedClasses = 8, kSeedCells = 6, kSeedHash = 7;
 uint32_t seed_class(uint64_t h) {  // sums, as the classes come in no order a branch could learn
   return uint32_t(h > 768) + uint32_t(h > 1536) + uint32_t(h > 3072) + uint32_t(h > 6144) + uint32_t(h > 12288) +
-         uint32_t(h > 24576);
+         uint32_t(h > 24576) + uint32_t(h > (1ull << 31));
 }
 
 // Buckets a bin as a 32-bit fraction: umulhi(bin, f) < buckets for bin < nbins.
