@@ -1924,38 +1924,41 @@ int grim_seeds_build(const uint8_t* ref, uint64_t ref_len, uint32_t ref_on_devic
   }
   if ((e = pool_alloc(&sd->start, (sd->nk + 1) * sizeof(uint64_t))) != hipSuccess) return fail(e, "k-mer starts");
   const bool vec = ((uintptr_t)dref & 15u) == 0;
-  // positions per partition and stream; the scanned counts are the streams' places
   const uint32_t pb = part_bits(k), low = 2 * k - pb;
+  // The partitioned copy holds 8 bytes of position and code per base. Beyond
+  // kPartMost, or without the memory for it, the table is filled through its
+  // counters: 25 GB for 3.1 Gbp made the build 63 ms instead of 296, but hipFree
+  // then wiped them for 0.6 s, in which every other kernel ran 6% slower. (The
+  // switch is a test's.)
+  bool in_parts = low == 0 || (ref_len * sizeof(uint64_t) <= kPartMost && !env_flag("GRIM_SEED_BUILD_COUNTERS"));
+  // positions per partition and stream; the scanned counts are the streams' places
   const uint64_t np = 1ull << pb, tiles = (ref_len + kTile - 1) / kTile;
   const uint32_t streams = (uint32_t)std::min<uint64_t>(kStreams, tiles);
   const uint64_t cells = np * streams;
   const size_t part_lds = np * sizeof(uint32_t);
-  if ((e = pool_alloc(&counts, (cells + 1) * sizeof(uint32_t))) != hipSuccess) return fail(e, "partition counts");
-  if ((e = pool_alloc(&tmp, (cells + 1 + scan_blocks(cells + 1) + 1) * sizeof(uint64_t))) != hipSuccess)
-    return fail(e, "partition places");
-  uint64_t* place = static_cast<uint64_t*>(tmp);
-  if ((e = launch_zero_words(counts, (uint32_t)(cells + 1), s)) != hipSuccess) return fail(e, "zero counts");
-  hipLaunchKernelGGL(vec ? k_part_count<true> : k_part_count<false>, dim3(streams), dim3(kTileT), part_lds,
-                     s, dref, ref_len, k, pb, tiles, counts);
-  if ((e = hipGetLastError()) != hipSuccess) return fail(e, "k-mer count");
-  if ((e = launch_scan(counts, cells + 1, place, place + cells + 1, nullptr, nullptr, s)) != hipSuccess)
-    return fail(e, "partition scan");
+  uint64_t* place = nullptr;
   uint64_t n_pos = 0;
-  if ((e = hipMemcpyAsync(&n_pos, place + cells, sizeof n_pos, hipMemcpyDeviceToHost, s)) != hipSuccess)
-    return fail(e, "position count");
-  if ((e = hipStreamSynchronize(s)) != hipSuccess) return fail(e, "position count");
-  sd->n_pos = n_pos;
-  if ((e = pool_alloc(&sd->pos, std::max<uint64_t>(n_pos, 1) * sizeof(uint32_t))) != hipSuccess)
-    return fail(e, "positions");
-  // the partitioned copy: 8 bytes of position and code each. Beyond kPartMost, or
-  // without the memory for it, the table is filled through its counters: 25 GB
-  // for 3.1 Gbp made the build 63 ms instead of 296, but hipFree then wiped them
-  // for 0.6 s, in which every other kernel ran 6% slower. (The switch is a test's.)
-  bool in_parts = true;
-  if (low) {
-    in_parts = n_pos * sizeof(uint64_t) <= kPartMost && !env_flag("GRIM_SEED_BUILD_COUNTERS") &&
-               pool_alloc(&parts, std::max<uint64_t>(n_pos, 1) * sizeof(uint64_t)) == hipSuccess;
-    if (!in_parts) {
+  auto take_positions = [&](const uint64_t* total) -> hipError_t {  // their number is on the device
+    hipError_t err = hipMemcpyAsync(&n_pos, total, sizeof n_pos, hipMemcpyDeviceToHost, s);
+    if (err == hipSuccess) err = hipStreamSynchronize(s);
+    if (err != hipSuccess) return err;
+    sd->n_pos = n_pos;
+    return pool_alloc(&sd->pos, std::max<uint64_t>(n_pos, 1) * sizeof(uint32_t));
+  };
+  if (in_parts) {
+    if ((e = pool_alloc(&counts, (cells + 1) * sizeof(uint32_t))) != hipSuccess) return fail(e, "partition counts");
+    if ((e = pool_alloc(&tmp, (cells + 1 + scan_blocks(cells + 1) + 1) * sizeof(uint64_t))) != hipSuccess)
+      return fail(e, "partition places");
+    place = static_cast<uint64_t*>(tmp);
+    if ((e = launch_zero_words(counts, (uint32_t)(cells + 1), s)) != hipSuccess) return fail(e, "zero counts");
+    hipLaunchKernelGGL(vec ? k_part_count<true> : k_part_count<false>, dim3(streams), dim3(kTileT), part_lds,
+                       s, dref, ref_len, k, pb, tiles, counts);
+    if ((e = hipGetLastError()) != hipSuccess) return fail(e, "k-mer count");
+    if ((e = launch_scan(counts, cells + 1, place, place + cells + 1, nullptr, nullptr, s)) != hipSuccess)
+      return fail(e, "partition scan");
+    if ((e = take_positions(place + cells)) != hipSuccess) return fail(e, "positions");
+    if (low && pool_alloc(&parts, std::max<uint64_t>(n_pos, 1) * sizeof(uint64_t)) != hipSuccess) {
+      in_parts = false;
       parts = nullptr;
       (void)hipGetLastError();  // the failed allocation is not an error of the build
     }
@@ -1986,7 +1989,7 @@ int grim_seeds_build(const uint8_t* ref, uint64_t ref_len, uint32_t ref_on_devic
                          sd->start);
     if ((e = hipGetLastError()) != hipSuccess) return fail(e, "k-mer sort");
   } else {
-    for (void* p : {(void*)counts, tmp}) pool_free(p);  // the stream was waited for
+    for (void* p : {(void*)counts, tmp}) pool_free(p);  // null, or the stream was waited for
     counts = nullptr;
     tmp = nullptr;
     if ((e = pool_alloc(&counts, (sd->nk + 1) * sizeof(uint32_t))) != hipSuccess) return fail(e, "k-mer counts");
@@ -2000,6 +2003,7 @@ int grim_seeds_build(const uint8_t* ref, uint64_t ref_len, uint32_t ref_on_devic
     if ((e = launch_scan(counts, sd->nk + 1, sd->start, static_cast<uint64_t*>(tmp), nullptr, nullptr, s)) !=
         hipSuccess)
       return fail(e, "k-mer scan");
+    if (!sd->pos && (e = take_positions(sd->start + sd->nk)) != hipSuccess) return fail(e, "positions");
     hipLaunchKernelGGL(vec ? k_kmer_fill<true> : k_kmer_fill<false>, dim3((unsigned)blocks), dim3(256), 0, s, dref,
                        ref_len, k, sd->start, counts, sd->pos);
     if ((e = hipGetLastError()) != hipSuccess) return fail(e, "k-mer fill");
