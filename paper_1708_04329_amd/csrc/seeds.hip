@@ -47,12 +47,12 @@ struct grim_seeds {
   uint64_t n_pos = 0;
   std::mutex mu;
   // scratch of grim_seed_candidates (grown on demand)
-  uint64_t* hits = nullptr;       // [n_reads] hits per read
+  uint64_t* hits = nullptr;       // [n_reads + 1] hits per read, then whether offsets are bad
   uint64_t* hits_host = nullptr;  // pinned copy
   uint64_t hits_cap = 0, hits_host_cap = 0;
   uint2* found = nullptr;         // [n_bases / k + 1] seeds' table entries
   uint64_t found_cap = 0;
-  uint64_t* words = nullptr;      // [8]: CSR total so far (two words, by batch parity), bad offsets, fallback count
+  uint64_t* words = nullptr;      // [8]: CSR total so far (two words, by batch parity), -, reads for the fallback, for the hash tables
   uint32_t* tmp = nullptr;        // staging: kept bins per read
   uint64_t tmp_cap = 0;
   uint64_t* toff = nullptr;       // [batch reads] first staging slot
@@ -1763,6 +1763,7 @@ __global__ __launch_bounds__(256) void k_seed_place(const uint64_t* tmp_off, con
   const uint32_t K = cnt[i];
   const uint32_t* src = tmp + tmp_off[i];
   for (uint32_t j = lane; j < K; j += 64) cand_bin[o + j] = (int32_t)src[j];
+  if (lane == 0 && i + 1 == nb) cand_off[r0 + nb] = (int64_t)(o + K);  // the next batch's first offset, or the end
 }
 
 __global__ __launch_bounds__(256) void k_revcomp(const uint8_t* in, uint64_t n_bases, const int64_t* offsets, uint64_t n,
@@ -1794,11 +1795,19 @@ __global__ __launch_bounds__(256) void k_revcomp(const uint8_t* in, uint64_t n_b
   }
 }
 
-__global__ void k_fill_word(uint32_t* p, uint32_t v) { *p = v; }
-
-hipError_t launch_fill_word(uint32_t* p, uint32_t v, hipStream_t s) {
-  hipLaunchKernelGGL(k_fill_word, dim3(1), dim3(1), 0, s, p, v);
-  return hipGetLastError();
+// What a call's and a batch's kernels count in.
+__global__ void k_seed_call(uint64_t* words, uint64_t* bad) {
+  if (threadIdx.x < 8) words[threadIdx.x] = 0;
+  if (threadIdx.x == 8) *bad = 0;
+}
+__global__ __launch_bounds__(256) void k_seed_batch(uint32_t* cnt, uint32_t nb, uint32_t* n_redo, uint32_t redo,
+                                                    uint32_t* n_hash, uint32_t hash) {
+  const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+  if (i < nb) cnt[i] = 0;
+  if (i == 0) {
+    *n_redo = redo;
+    *n_hash = hash;
+  }
 }
 
 template <typename T>
@@ -2062,10 +2071,10 @@ int grim_seed_candidates(const grim_seeds* csd, const grim_reads* rd, uint32_t b
     offsets = reinterpret_cast<const int64_t*>(sd->staging + ob);
   }
   // 1. hits per read
-  int rc = grow_dev(&sd->hits, &sd->hits_cap, n);
+  int rc = grow_dev(&sd->hits, &sd->hits_cap, n + 1);  // and the word of bad offsets
   if (rc) return rc;
   if ((rc = grow_dev(&sd->found, &sd->found_cap, rd->n_bases / sd->k + 1))) return rc;
-  if (sd->hits_host_cap < n || !sd->hits_host) {
+  if (sd->hits_host_cap < n + 1 || !sd->hits_host) {
     if (sd->hits_host) (void)hipHostFree(sd->hits_host);
     sd->hits_host = nullptr;
     sd->hits_host_cap = 0;
@@ -2073,18 +2082,17 @@ int grim_seed_candidates(const grim_seeds* csd, const grim_reads* rd, uint32_t b
     sd->hits_host_cap = sd->hits_cap;
   }
   if (!sd->words) GRIM_HIP_TRY(pool_alloc(&sd->words, 8 * sizeof(uint64_t)));
-  uint32_t* bad = reinterpret_cast<uint32_t*>(sd->words + 2);
+  uint32_t* bad = reinterpret_cast<uint32_t*>(sd->hits + n);
   uint32_t* n_redo = reinterpret_cast<uint32_t*>(sd->words + 3);
   uint32_t* n_hash = reinterpret_cast<uint32_t*>(sd->words + 4);
-  GRIM_HIP_TRY(launch_zero_words(reinterpret_cast<uint32_t*>(sd->words), 16, s));  // base, bad, n_redo
+  hipLaunchKernelGGL(k_seed_call, dim3(1), dim3(64), 0, s, sd->words, sd->hits + n);
+  GRIM_HIP_TRY(hipGetLastError());
   hipLaunchKernelGGL(k_seed_hits, dim3((unsigned)((n + 15) / 16)), dim3(256), 0, s, sd->start, sd->k, bases,
                      rd->n_bases, offsets, n, sd->found, sd->hits, bad);
   GRIM_HIP_TRY(hipGetLastError());
-  GRIM_HIP_TRY(hipMemcpyAsync(sd->hits_host, sd->hits, n * sizeof(uint64_t), hipMemcpyDeviceToHost, s));
-  uint32_t* bad_host = reinterpret_cast<uint32_t*>(sd->total_host + 3);
-  GRIM_HIP_TRY(hipMemcpyAsync(bad_host, bad, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+  GRIM_HIP_TRY(hipMemcpyAsync(sd->hits_host, sd->hits, (n + 1) * sizeof(uint64_t), hipMemcpyDeviceToHost, s));
   GRIM_HIP_TRY(hipStreamSynchronize(s));
-  if (*bad_host) return set_error(GRIM_EINVAL, "read offsets out of order or outside [0, n_bases]");
+  if (sd->hits_host[n]) return set_error(GRIM_EINVAL, "read offsets out of order or outside [0, n_bases]");
   const uint64_t* H = sd->hits_host;
   // bins lie in [0, nbins): max(p - o, 0) / B <= (G - 1) / B
   const uint64_t max_bin = sd->G / bin_size;
@@ -2197,14 +2205,14 @@ int grim_seed_candidates(const grim_seeds* csd, const grim_reads* rd, uint32_t b
     }
     const uint64_t listed = all_fallback ? n_fb : first[kSeedClasses];
     GRIM_HIP_TRY(hipMemcpyAsync(sd->toff, toff_h, nb * sizeof(uint64_t), hipMemcpyHostToDevice, s));
-    GRIM_HIP_TRY(launch_zero_words(sd->cnt, (uint32_t)nb, s));
     if (listed) GRIM_HIP_TRY(hipMemcpyAsync(all_fallback ? sd->redo : sd->list, list_h, listed * sizeof(uint32_t),
                                             hipMemcpyHostToDevice, s));
     const uint64_t n_big = per_class[kSeedHash];
     if (n_big) GRIM_HIP_TRY(hipMemcpyAsync(sd->hash, list_h + first[kSeedHash], n_big * sizeof(uint32_t),
                                            hipMemcpyHostToDevice, s));
-    GRIM_HIP_TRY(launch_fill_word(n_redo, all_fallback ? (uint32_t)n_fb : 0u, s));
-    GRIM_HIP_TRY(launch_fill_word(n_hash, (uint32_t)n_big, s));
+    hipLaunchKernelGGL(k_seed_batch, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, s, sd->cnt, (uint32_t)nb, n_redo,
+                       all_fallback ? (uint32_t)n_fb : 0u, n_hash, (uint32_t)n_big);
+    GRIM_HIP_TRY(hipGetLastError());
     a.r0 = r0;
     a.tmp_off = sd->toff;
     a.tmp = sd->tmp;
@@ -2257,8 +2265,6 @@ int grim_seed_candidates(const grim_seeds* csd, const grim_reads* rd, uint32_t b
     ++nbatch;
   }
   GRIM_HIP_TRY(hipMemcpyAsync(sd->total_host + 2, sd->words + (nbatch & 1), sizeof(uint64_t), hipMemcpyDeviceToHost, s));
-  GRIM_HIP_TRY(hipStreamSynchronize(s));
-  GRIM_HIP_TRY(hipMemcpyAsync(cand_off + n, sd->total_host + 2, sizeof(int64_t), hipMemcpyHostToDevice, s));
   GRIM_HIP_TRY(hipStreamSynchronize(s));
   *n_cand_out = sd->total_host[2];
   return GRIM_OK;
