@@ -36,6 +36,7 @@
 #include <type_traits>
 
 #include "grim_internal.h"
+#include "verify_text.h"
 
 namespace grim {
 namespace {
@@ -530,7 +531,7 @@ __device__ __forceinline__ uint32_t piece_hash(uint32_t code) { return code * 0x
 // from its start, that an alignment within the budget lies in: what one that
 // touches a found piece can cover. Empty (0, 0) where none was found, and then
 // the pair's outputs are written here. Pairs the sift does not apply to get the
-// whole text, (0, 2^32 - 1).
+// whole text, (0, kWholeText).
 __global__ __launch_bounds__(256) void k_verify_sift(VerifyArgs a, uint64_t count) {
   __shared__ __attribute__((aligned(16))) SiftLds lds_all[4][4];
   const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, sub = lane >> 4, j = lane & 15u;
@@ -690,13 +691,13 @@ __global__ __launch_bounds__(256) void k_verify_sift(VerifyArgs a, uint64_t coun
     }
   }
   if (t >= count) return;
-  uint2 span = make_uint2(0, 0xFFFFFFFFu);
+  uint2 span = make_uint2(0, kWholeText);
   if (my_sift && my_lo > my_hi) {
     span = make_uint2(0, 0);
     write_distance(a, my_pair, 0xFFFE, mine.E);
   } else if (my_sift) {
     const int64_t reach = (int64_t)mine.L + mine.E, off = (int64_t)(mine.lo & 15u), len = (int64_t)(mine.hi - mine.lo);
-    if (len < 0xFFFFFFFFll)
+    if (len < (int64_t)kWholeText)
       span = make_uint2((uint32_t)max<int64_t>(0, 16 * ((int64_t)my_lo - 1) - off - reach),
                         (uint32_t)min<int64_t>(len, 16 * ((int64_t)my_hi + 1) - off + reach));
   }
@@ -717,7 +718,6 @@ __global__ __launch_bounds__(256) void k_verify_sift(VerifyArgs a, uint64_t coun
 // 0.96: more columns before the parts, fewer parts to order).
 constexpr uint32_t kMostLeft = 2048;
 constexpr uint32_t kMostParts = 4096;
-constexpr uint32_t kPart = 192;
 constexpr uint64_t kLeftBlocks = 2048;
 
 struct LeftLds {
@@ -738,20 +738,14 @@ __device__ __forceinline__ void left_items(const VerifyArgs& a, uint64_t t0, uin
   const uint32_t t = threadIdx.x;
   if (t < 64) cur[t] = 0;
   for (uint32_t i = t; i < n; i += 256) best_of[i] = 0xFFFFFFFFu;
-  // parts of a text: all but the last end kPart columns after the one before. A
-  // text is cut where that saves its length by half; whole bins that the sift
-  // could not look through are not.
+  // parts of an item's text; the read's length is looked up only where it may be cut
   auto parts_of = [&](uint2 sp, uint32_t item) -> uint32_t {
-    if (sp.x >= sp.y) return 0;
-    const uint32_t len = sp.y - sp.x;
-    if (sp.y == 0xFFFFFFFFu || len < 2 * kPart) return 1;
+    if (sp.y - sp.x < 2 * kPart) return sp.x < sp.y ? 1u : 0u;
     const uint32_t r = a.item_read[t0 + item];
-    const uint32_t reach = 2 * (uint32_t)(a.offsets[r + 1] - a.offsets[r]);  // L + E, E < L
-    if (len < 2 * (kPart + reach)) return 1;
-    return min((len + kPart - 1) / kPart, 64u);
+    return span_parts(sp.x, sp.y, (uint32_t)(a.offsets[r + 1] - a.offsets[r]));
   };
   auto bucket = [](uint2 sp, uint32_t np) {
-    const uint32_t len = np == 1 ? sp.y - sp.x : (sp.y - sp.x + np - 1) / np + kPart;
+    const uint32_t len = np == 1 ? sp.y - sp.x : part_step(sp.x, sp.y, np) + kPart;
     return 63u - min(len / 64u, 63u);
   };
   __syncthreads();
@@ -793,14 +787,12 @@ __device__ __forceinline__ void left_items(const VerifyArgs& a, uint64_t t0, uin
     const uint32_t np = whole ? 1u : parts_of(sp, item);
     int32_t best;
     // near an alignment most words are in play, and the full column is the
-    // faster; the cutoff serves the whole bins. Parts are widened to whole
-    // 16-byte loads.
-    if (BOUNDED && sp.y == 0xFFFFFFFFu) {
+    // faster; the cutoff serves the whole bins
+    if (BOUNDED && sp.y == kWholeText) {
       best = align_text<W, BOUNDED>(a, p, p.lo, p.hi);
     } else {
-      const uint32_t step = (sp.y - sp.x + np - 1) / np, back = p.L + (uint32_t)p.E;
-      const uint32_t from = sp.x + (u * step > back ? u * step - back : 0u), to = min(sp.y, sp.x + (u + 1) * step);
-      best = align_text<W, false>(a, p, max(p.lo, (p.lo + from) & ~15ull), min(p.hi, (p.lo + to + 15) & ~15ull));
+      const TextPart text = text_part(p.lo, p.hi, sp.x, sp.y, np, u, p.L + (uint32_t)p.E);
+      best = align_text<W, false>(a, p, text.lo, text.hi);
     }
     atomicMin(&best_of[item], (uint32_t)best);
   }
