@@ -204,37 +204,40 @@ __device__ __forceinline__ int64_t seed_code(const uint8_t* s, uint32_t k) {
 // reads share none of these), and the read's hits. Bound by the dependent
 // loads (offsets, bases, table): a thread per read, seed after seed, took 96 us
 // for 20011 reads of 100-250 bp, the lanes take 27.
-// A read whose offsets are out of order or outside [0, n_bases] gets no hits
-// and sets *bad; the call then fails before any later pass reads its bases.
+// A launch holds fewer than 2^32 threads, so kHitBlocks workgroups go over more
+// reads than they take at a time. A read whose offsets are out of order or
+// outside [0, n_bases] gets no hits and sets *bad; the call then fails before any
+// later pass reads its bases.
+constexpr uint64_t kHitBlocks = 1u << 20;
 __global__ __launch_bounds__(256) void k_seed_hits(const uint64_t* start, uint32_t k, const uint8_t* bases,
                                                    uint64_t n_bases, const int64_t* offsets, uint64_t n,
                                                    uint2* found, uint64_t* hits, uint32_t* bad) {
-  const uint64_t r = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 4;
   const uint32_t j = threadIdx.x & 15u;
-  if (r >= n) return;
-  const int64_t o0 = offsets[r], o1 = offsets[r + 1];
-  if (o0 < 0 || o1 < o0 || (uint64_t)o1 > n_bases) {
-    if (j == 0) {
-      hits[r] = 0;
-      atomicOr(bad, 1u);
+  for (uint64_t r = (uint64_t)blockIdx.x * 16 + (threadIdx.x >> 4); r < n; r += (uint64_t)gridDim.x * 16) {
+    const int64_t o0 = offsets[r], o1 = offsets[r + 1];
+    if (o0 < 0 || o1 < o0 || (uint64_t)o1 > n_bases) {
+      if (j == 0) {
+        hits[r] = 0;
+        atomicOr(bad, 1u);
+      }
+      continue;
     }
-    return;
-  }
-  const uint64_t n_seeds = (uint64_t)(o1 - o0) / k, at = (uint64_t)o0 / k;
-  uint64_t h = 0;
-  for (uint64_t i = j; i < n_seeds; i += 16) {
-    const int64_t c = seed_code(bases + o0 + i * k, k);
-    uint2 f = make_uint2(0, 0);
-    if (c >= 0) {
-      const uint64_t b = start[c];
-      f = make_uint2((uint32_t)b, (uint32_t)(start[c + 1] - b));
+    const uint64_t n_seeds = (uint64_t)(o1 - o0) / k, at = (uint64_t)o0 / k;
+    uint64_t h = 0;
+    for (uint64_t i = j; i < n_seeds; i += 16) {
+      const int64_t c = seed_code(bases + o0 + i * k, k);
+      uint2 f = make_uint2(0, 0);
+      if (c >= 0) {
+        const uint64_t b = start[c];
+        f = make_uint2((uint32_t)b, (uint32_t)(start[c + 1] - b));
+      }
+      found[at + i] = f;
+      h += f.y;
     }
-    found[at + i] = f;
-    h += f.y;
+    for (int d = 1; d < 16; d <<= 1)
+      h += ((uint64_t)(uint32_t)__shfl_xor((int)(uint32_t)(h >> 32), d) << 32) + (uint32_t)__shfl_xor((int)(uint32_t)h, d);
+    if (j == 0) hits[r] = h;
   }
-  for (int d = 1; d < 16; d <<= 1)
-    h += ((uint64_t)(uint32_t)__shfl_xor((int)(uint32_t)(h >> 32), d) << 32) + (uint32_t)__shfl_xor((int)(uint32_t)h, d);
-  if (j == 0) hits[r] = h;
 }
 
 // ---------------------------------------------------------------------------
@@ -2087,8 +2090,8 @@ int grim_seed_candidates(const grim_seeds* csd, const grim_reads* rd, uint32_t b
   uint32_t* n_hash = reinterpret_cast<uint32_t*>(sd->words + 4);
   hipLaunchKernelGGL(k_seed_call, dim3(1), dim3(64), 0, s, sd->words, sd->hits + n);
   GRIM_HIP_TRY(hipGetLastError());
-  hipLaunchKernelGGL(k_seed_hits, dim3((unsigned)((n + 15) / 16)), dim3(256), 0, s, sd->start, sd->k, bases,
-                     rd->n_bases, offsets, n, sd->found, sd->hits, bad);
+  hipLaunchKernelGGL(k_seed_hits, dim3((unsigned)std::min((n + 15) / 16, kHitBlocks)), dim3(256), 0, s, sd->start,
+                     sd->k, bases, rd->n_bases, offsets, n, sd->found, sd->hits, bad);
   GRIM_HIP_TRY(hipGetLastError());
   GRIM_HIP_TRY(hipMemcpyAsync(sd->hits_host, sd->hits, (n + 1) * sizeof(uint64_t), hipMemcpyDeviceToHost, s));
   GRIM_HIP_TRY(hipStreamSynchronize(s));
