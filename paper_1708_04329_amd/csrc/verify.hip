@@ -33,6 +33,7 @@
 // their bins only the stretch around the pieces found, are aligned.
 
 #include <algorithm>
+#include <cstdlib>
 #include <type_traits>
 
 #include "grim_internal.h"
@@ -897,11 +898,20 @@ hipError_t launch_verify_scatter(const VerifyArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_verify_sift(const VerifyArgs& a, uint64_t count, hipStream_t s) {
-  const uint64_t blocks = (count + 255) / 256;
-  if (blocks == 0) return hipSuccess;
-  if (blocks > 0x7FFFFFFFull) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL(k_verify_sift, dim3((unsigned)blocks), dim3(256), 0, s, a, count);
-  return hipGetLastError();
+  // one thread per item, and a launch holds fewer than 2^32 (GRIM_VERIFY_SLICE: fewer items, for tests)
+  uint64_t most = 1ull << 31;
+  if (const char* e = std::getenv("GRIM_VERIFY_SLICE")) most = std::min<uint64_t>(most, std::max(1ll, std::atoll(e)));
+  for (uint64_t at = 0; at < count; at += most) {
+    VerifyArgs b = a;
+    b.item_pair += at;
+    b.item_read += at;
+    b.item_span += at;
+    const uint64_t n = std::min(count - at, most);
+    hipLaunchKernelGGL(k_verify_sift, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, b, n);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_verify_left(const VerifyArgs& a, const uint64_t* first, const uint64_t* count, hipStream_t s) {
