@@ -106,7 +106,7 @@ int check_device(int dev) {
 template <typename T>
 int grow(T** p, uint64_t* cap, uint64_t need) {
   if (*cap >= need && *p) return GRIM_OK;
-  pool_free(*p);  // calls wait for their work: the last one's is complete
+  pool_free(*p);  // calls wait for their work, also when they fail (StreamWait)
   *p = nullptr;
   *cap = 0;
   uint64_t n = need + need / 4 + 256;
@@ -604,6 +604,7 @@ int grim_filter_scan(const grim_index* cidx, const grim_reads* rd, uint32_t* mas
   DeviceGuard dg(idx->device);
   apply_cached_config(idx, GRIM_MODE_SCAN, rd->n_reads, rd->n_bases, 0);
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
+  StreamWait wait(s);
   ReadView v;
   rc = stage_reads(idx, rd, s, &v);
   if (rc) return rc;
@@ -640,6 +641,7 @@ int grim_filter_scan(const grim_index* cidx, const grim_reads* rd, uint32_t* mas
   GRIM_HIP_TRY(launch_scan_allbins(a, cfg, s));
   ps.stop(s);
   rc = finish_status(idx, s);
+  if (rc == GRIM_OK) wait.done();
   pt.collect();
   ps.collect();
   return rc;
@@ -660,6 +662,7 @@ int grim_filter_candidates(const grim_index* cidx, const grim_reads* rd, const i
   DeviceGuard dg(idx->device);
   apply_cached_config(idx, GRIM_MODE_CANDIDATES, rd->n_reads, rd->n_bases, n_cand);
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
+  StreamWait wait(s);
   CandArgs a;
   rc = prepare_candidates(idx, rd, cand_off, cand_bin, n_cand, count_out, pass_out, s, &a);
   if (rc) return rc;
@@ -668,6 +671,7 @@ int grim_filter_candidates(const grim_index* cidx, const grim_reads* rd, const i
   GRIM_HIP_TRY(launch_scan_candidates(a, cand_config_from_env(idx->cand_cfg), s));
   ps.stop(s);
   GRIM_HIP_TRY(hipStreamSynchronize(s));
+  wait.done();
   ps.collect();
   return status_to_error(flags_to_status(a.flags));
 }
@@ -691,6 +695,7 @@ int verify_impl(const grim_index* cidx, const grim_reads* rd, const int64_t* can
   std::lock_guard<std::mutex> lk(idx->mu);
   DeviceGuard dg(idx->device);
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
+  StreamWait wait(s);
   ReadView v;
   rc = stage_reads(idx, rd, s, &v);
   if (rc) return rc;
@@ -741,7 +746,10 @@ int verify_impl(const grim_index* cidx, const grim_reads* rd, const int64_t* can
     first[w] = total;
     total += counts[w];
   }
-  if (total == 0) return GRIM_OK;
+  if (total == 0) {
+    wait.done();
+    return GRIM_OK;
+  }
   rc = grow(&ws.vitem_pair, &ws.vitem_cap, total);
   if (rc) return rc;
   rc = grow(&ws.vitem_read, &ws.vitem_read_cap, total);
@@ -764,6 +772,7 @@ int verify_impl(const grim_index* cidx, const grim_reads* rd, const int64_t* can
   }
   pv.stop(s);
   GRIM_HIP_TRY(hipStreamSynchronize(s));  // the inputs' status is known: nothing after the count sets it
+  wait.done();
   pv.collect();
   return GRIM_OK;
 }

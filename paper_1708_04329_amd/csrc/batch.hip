@@ -193,6 +193,7 @@ extern "C" int grim_tune(grim_index* idx, const grim_reads* rd, const int64_t* c
   CandArgs ca{};
   DevBuf<uint16_t> cnt;
   DevBuf<uint8_t> pas;
+  StreamWait wait(s);
   if (mode == GRIM_MODE_SCAN) {
     rc = prepare_reads(idx, rd, 65535u, scan_token_shift(idx->q), s, &offs);
     if (rc) return rc;

@@ -36,6 +36,22 @@ hipError_t pool_alloc(T** out, size_t bytes) {
   return pool_alloc(reinterpret_cast<void**>(out), bytes);
 }
 
+// Waits for the stream at the end of its scope unless done() was called: a call
+// that fails after its first copy or launch leaves no work behind that still
+// uses its workspace, which the next call may grow (the old block then goes to
+// another handle, on another stream) or clear.
+struct StreamWait {
+  hipStream_t s;
+  bool armed = true;
+  explicit StreamWait(hipStream_t st) : s(st) {}
+  StreamWait(const StreamWait&) = delete;
+  StreamWait& operator=(const StreamWait&) = delete;
+  void done() { armed = false; }
+  ~StreamWait() {
+    if (armed) (void)hipStreamSynchronize(s);
+  }
+};
+
 // Device status words written by kernels (status[0] holds error bits).
 enum : uint32_t {
   ST_BAD_LENGTH = 1u,      // L < q or offsets out of order / out of range

@@ -104,6 +104,8 @@ extern "C" int grim_filter_candidates_static(const grim_index* cidx, const grim_
   }
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   uint32_t* flags = reinterpret_cast<uint32_t*>(base);
+  uint32_t st[kFlagWords];
+  StreamWait wait(s);
   // the array keeps the previous call's contents: clear the flags
   GRIM_HIP_TRY(launch_zero_words(flags, 2 * kFlagWords, s));
   CandArgs a{};
@@ -129,8 +131,8 @@ extern "C" int grim_filter_candidates_static(const grim_index* cidx, const grim_
   a.flags = flags;
   a.work = flags + kFlagWords;
   GRIM_HIP_TRY(launch_scan_candidates(a, cfg, s));
-  uint32_t st[kFlagWords];
   GRIM_HIP_TRY(hipMemcpyAsync(st, flags, sizeof st, hipMemcpyDeviceToHost, s));
   GRIM_HIP_TRY(hipStreamSynchronize(s));
+  wait.done();
   return status_to_error(flags_to_status(st));
 }

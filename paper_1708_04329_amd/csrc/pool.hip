@@ -18,6 +18,7 @@
 // device by itself).
 
 #include <chrono>
+#include <cstdlib>
 #include <mutex>
 #include <unordered_map>
 #include <vector>
@@ -76,6 +77,7 @@ void release(const std::vector<Block>& blocks) {
 }
 
 hipError_t allocate(void** out, size_t bytes) {
+  if (std::getenv("GRIM_POOL_TEST_FAIL")) return hipErrorOutOfMemory;  // tests: no memory for what a call still needs
   int device = 0;
   hipError_t e = hipGetDevice(&device);
   if (e != hipSuccess) return e;

@@ -1816,7 +1816,7 @@ __global__ __launch_bounds__(256) void k_seed_batch(uint32_t* cnt, uint32_t nb, 
 template <typename T>
 int grow_dev(T** p, uint64_t* cap, uint64_t need) {
   if (*cap >= need && *p) return GRIM_OK;
-  pool_free(*p);  // calls wait for their work: the last one's is complete
+  pool_free(*p);  // calls wait for their work, also when they fail (StreamWait)
   *p = nullptr;
   *cap = 0;
   const uint64_t n = need + need / 8 + 64;
@@ -2052,6 +2052,7 @@ int grim_seed_candidates(const grim_seeds* csd, const grim_reads* rd, uint32_t b
   std::lock_guard<std::mutex> lk(sd->mu);
   SeedGuard g(sd->device);
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
+  StreamWait wait(s);
   const uint64_t n = rd->n_reads;
   if (!sd->total_host) GRIM_HIP_TRY(hipHostMalloc(&sd->total_host, 4 * sizeof(uint64_t), hipHostMallocDefault));
   *n_cand_out = 0;
@@ -2269,6 +2270,7 @@ int grim_seed_candidates(const grim_seeds* csd, const grim_reads* rd, uint32_t b
   }
   GRIM_HIP_TRY(hipMemcpyAsync(sd->total_host + 2, sd->words + (nbatch & 1), sizeof(uint64_t), hipMemcpyDeviceToHost, s));
   GRIM_HIP_TRY(hipStreamSynchronize(s));
+  wait.done();
   *n_cand_out = sd->total_host[2];
   return GRIM_OK;
 }
