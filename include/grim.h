@@ -15,9 +15,9 @@
  *     grim_index handles and frees them in grim_index_free.
  *   - Device memory freed within 2 s of its allocation (a loop that builds, uses
  *     and frees handles; a build's temporaries) is kept for the next handles, at
- *     most 12 GiB per device; blocks idle for 10 s go back to the driver at the
- *     next call that allocates or frees, all of them when an allocation of the
- *     library fails or a server or batcher is created.
+ *     most 12 GiB per device and a sixteenth of its free memory; blocks idle for
+ *     2 s go back to the driver, all of them when an allocation of the library
+ *     fails, a server or batcher is created, or grim_trim_memory is called.
  *   - "device" buffers are HIP device memory on the device that holds the
  *     index; "host" buffers are ordinary process memory.
  *   - hip_stream is a hipStream_t passed as void* (NULL = the null stream).
@@ -108,6 +108,12 @@ int grim_abi_version(void);
 /* Message for the last failed call on this thread ("" if none). The pointer
  * stays valid until the next call on this thread. */
 const char* grim_last_error(void);
+
+/* Gives the device memory that the library keeps for its next handles back to
+ * the driver at once, on every device (it goes by itself when it has been idle
+ * for 2 s): for a program that is about to need nearly all of a device's memory
+ * itself. Returns GRIM_OK. */
+int grim_trim_memory(void);
 
 /* Build the bit vectors of a reference (Section 3, bit vector generation):
  * bin x = [x*B, x*B + B) extended by O bases; bit t of bin x is set when a

@@ -30,7 +30,7 @@ void clear_error();
 // pool_free: after every use of the block on any stream is complete.
 hipError_t pool_alloc(void** out, size_t bytes);
 void pool_free(void* p);
-void pool_trim();  // idle blocks of the current device back to the driver
+void pool_trim();      // idle blocks of the current device back to the driver
 template <typename T>
 hipError_t pool_alloc(T** out, size_t bytes) {
   return pool_alloc(reinterpret_cast<void**>(out), bytes);

@@ -5,117 +5,144 @@
 // loop over bin sizes that builds, uses and frees a 100 Mbp seed table and
 // index (1.4 GB with the build's temporaries) spent 10 to 50 of its 12 to 60 ms
 // a round there, against 2 ms in kernels. A block that is freed within
-// kPoolShort seconds of its allocation, as in such a loop, therefore stays in a
-// list per device, at most kPoolMost bytes (the 10 GB index of a q = 6 round of
-// the study over bin sizes fits) and kPoolSeconds long (older ones go at the next
-// call that allocates or frees); what lived longer goes back at once, and all of
-// the list does when an allocation of this library fails or a server or batcher
-// is about to size itself by the free memory.
+// kBrief seconds of its allocation, as in such a loop, therefore stays in a
+// list per device, at most kMost bytes (the 10 GB index of a q = 6 round of
+// the study over bin sizes fits) and no more than a sixteenth of the memory that
+// is free; what lived longer goes back at once. A thread gives blocks back
+// that have been idle for kIdle seconds, whether or not the library is called
+// again; it runs only while some are. All of the list goes back when an allocation
+// of this library fails, when a server or batcher is about to size itself by
+// the free memory, and by grim_trim_memory.
 //
 // A block is reused by whichever thread and stream asks next, so it may only be
 // given back when no work that touches it is left: pool_free is called after the
 // owner's stream or the device has been waited for (hipFree waited for the
 // device by itself).
 
+#include <algorithm>
 #include <chrono>
+#include <condition_variable>
 #include <cstdlib>
-#include <mutex>
-#include <unordered_map>
-#include <vector>
+#include <thread>
+
+#include <unistd.h>
 
 #include "grim_internal.h"
+#include "pool_core.h"
 
 namespace grim {
 namespace {
 
-constexpr size_t kPoolMost = size_t(12) << 30;
-constexpr double kPoolSeconds = 10.0, kPoolShort = 2.0;
+constexpr size_t kMost = size_t(12) << 30;
+constexpr size_t kLook = size_t(64) << 20;  // smaller blocks are kept without a look at the free memory
+constexpr double kIdle = 2.0, kBrief = 2.0;
 
-using Clock = std::chrono::steady_clock;
-
-struct Block {
-  void* p;
-  size_t bytes;
-  int device;
-  Clock::time_point since;  // of its allocation, or since it is idle
-};
-
-struct Pool {
+// The thread that gives idle blocks back, and what it shares with the process's end.
+struct Watch {
   std::mutex mu;
-  std::unordered_map<void*, Block> live;
-  std::vector<Block> idle;  // oldest first
+  std::condition_variable cv;
+  bool running = false, stop = false;
+  std::thread* thread = nullptr;
+  pid_t pid = 0;  // of the process that started it: a child of fork has no such thread
+};
+// never destroyed, nor is the pool: handles may be freed while the process ends
+Watch& watch() {
+  static Watch* w = new Watch;
+  return *w;
+}
+void watch_idle();
+void end_watch() {
+  Watch& w = watch();
+  {
+    std::lock_guard<std::mutex> lk(w.mu);
+    w.stop = true;
+    w.cv.notify_all();
+    if (!w.thread || w.pid != getpid()) return;
+  }
+  w.thread->join();
+}
+
+// The device made current for a scope.
+struct OnDevice {
+  int before = -1, device;
+  explicit OnDevice(int d) : device(d) {
+    if (hipGetDevice(&before) != hipSuccess) before = device;
+    if (before != device) (void)hipSetDevice(device);
+  }
+  ~OnDevice() {
+    if (before != device) (void)hipSetDevice(before);
+  }
 };
 
-// never destroyed: handles may be freed while the process ends
-Pool& pool() {
-  static Pool* p = new Pool;
+struct HipDriver {
+  bool alloc(void** out, size_t bytes, int) {
+    if (hipMalloc(out, bytes) == hipSuccess) return true;
+    (void)hipGetLastError();  // reported by the result alone
+    return false;
+  }
+  void free(void* p, int device) {
+    OnDevice on(device);
+    (void)hipFree(p);
+  }
+  double now() {
+    return std::chrono::duration<double>(std::chrono::steady_clock::now().time_since_epoch()).count();
+  }
+  size_t spare(int device, size_t bytes) {
+    if (bytes < kLook) return kMost;
+    OnDevice on(device);
+    size_t fr = 0, total = 0;
+    return hipMemGetInfo(&fr, &total) == hipSuccess ? fr / 16 : 0;
+  }
+  bool watch() try {
+    Watch& w = grim::watch();
+    std::lock_guard<std::mutex> lk(w.mu);
+    if (w.stop) return false;
+    const bool mine = w.pid == getpid();
+    if (w.running && mine) return true;
+    // its frees go through the runtime, which ends after what is registered here
+    static const int at_end = std::atexit(end_watch);
+    if (at_end != 0) return false;
+    if (w.thread && mine) {
+      w.thread->join();  // it has left its loop
+      delete w.thread;
+    }
+    w.thread = nullptr;
+    w.thread = new std::thread(watch_idle);
+    w.running = true;
+    w.pid = getpid();
+    return true;
+  } catch (...) {
+    return false;
+  }
+};
+
+pool::Pool<HipDriver>& blocks() {
+  static HipDriver drv;
+  static auto* p = new pool::Pool<HipDriver>(drv, pool::Limits{kMost, kIdle, kBrief});
   return *p;
 }
 
-// Takes idle blocks of the device out of the list: all, or those too old, then
-// the oldest until at most `most` bytes are left.
-void take_out(Pool& P, int device, bool all, size_t most, std::vector<Block>* out) {
-  const auto now = Clock::now();
-  size_t kept = 0;
-  for (const Block& b : P.idle)
-    if (b.device == device) kept += b.bytes;
-  for (size_t i = 0; i < P.idle.size();) {
-    const Block b = P.idle[i];
-    const bool old = std::chrono::duration<double>(now - b.since).count() > kPoolSeconds;
-    if (b.device == device && (all || old || kept > most)) {
-      kept -= b.bytes;
-      out->push_back(b);
-      P.idle.erase(P.idle.begin() + (long)i);
-    } else {
-      ++i;
+void watch_idle() {
+  Watch& w = watch();
+  // its frees belong to no other thread's graph capture
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  std::unique_lock<std::mutex> lk(w.mu);
+  while (!w.stop) {
+    lk.unlock();
+    double next = -1.0;
+    try {
+      next = blocks().expire();
+    } catch (...) {
+      next = kIdle;  // no memory for its list: later
     }
+    lk.lock();
+    // a block that became idle after the look sees `running` under the lock, so
+    // look once more before leaving
+    if (next < 0 && blocks().idle_bytes(-1) == 0) break;
+    if (!w.stop) w.cv.wait_for(lk, std::chrono::duration<double>(std::max(next, 0.001)));
   }
-}
-
-void release(const std::vector<Block>& blocks) {
-  for (const Block& b : blocks) (void)hipFree(b.p);
-}
-
-hipError_t allocate(void** out, size_t bytes) {
-  if (std::getenv("GRIM_POOL_TEST_FAIL")) return hipErrorOutOfMemory;  // tests: no memory for what a call still needs
-  int device = 0;
-  hipError_t e = hipGetDevice(&device);
-  if (e != hipSuccess) return e;
-  const size_t step = bytes >= (size_t(1) << 20) ? size_t(2) << 20 : 4096;
-  const size_t need = (bytes + step - 1) / step * step + (bytes == 0 ? step : 0);
-  Pool& P = pool();
-  std::vector<Block> old;
-  {
-    std::lock_guard<std::mutex> lk(P.mu);
-    size_t best = P.idle.size();
-    for (size_t i = 0; i < P.idle.size(); ++i) {
-      const Block& b = P.idle[i];
-      // the smallest that fits, but no block much larger than asked for
-      if (b.device == device && b.bytes >= need && b.bytes <= need + need / 4 &&
-          (best == P.idle.size() || b.bytes < P.idle[best].bytes))
-        best = i;
-    }
-    if (best < P.idle.size()) {
-      Block b = P.idle[best];
-      P.idle.erase(P.idle.begin() + (long)best);
-      b.since = Clock::now();
-      P.live[b.p] = b;
-      *out = b.p;
-    }
-    take_out(P, device, false, kPoolMost, &old);
-  }
-  release(old);
-  if (*out) return hipSuccess;
-  e = hipMalloc(out, need);
-  if (e != hipSuccess) {
-    pool_trim();
-    (void)hipGetLastError();
-    e = hipMalloc(out, need);
-  }
-  if (e != hipSuccess) return e;
-  std::lock_guard<std::mutex> lk(P.mu);
-  P.live[*out] = Block{*out, need, device, Clock::now()};
-  return hipSuccess;
+  w.running = false;
 }
 
 }  // namespace
@@ -123,50 +150,38 @@ hipError_t allocate(void** out, size_t bytes) {
 // No exception of the lists' own memory leaves these: the C entry points call them.
 hipError_t pool_alloc(void** out, size_t bytes) {
   *out = nullptr;
-  hipError_t e;
+  // tests: no memory for what a call still needs
+  if (std::getenv("GRIM_POOL_TEST_FAIL")) return hipErrorOutOfMemory;
+  int device = 0;
+  const hipError_t e = hipGetDevice(&device);
+  if (e != hipSuccess) return e;
   try {
-    e = allocate(out, bytes);
+    return blocks().alloc(out, bytes, device) ? hipSuccess : hipErrorOutOfMemory;
   } catch (...) {
-    if (*out) (void)hipFree(*out);
-    e = hipErrorOutOfMemory;
+    *out = nullptr;
+    return hipErrorOutOfMemory;
   }
-  if (e != hipSuccess) *out = nullptr;
-  return e;
 }
 
 void pool_free(void* p) try {
-  if (!p) return;
-  Pool& P = pool();
-  std::vector<Block> old;
-  {
-    std::lock_guard<std::mutex> lk(P.mu);
-    auto it = P.live.find(p);
-    if (it == P.live.end()) return;
-    Block b = it->second;
-    P.live.erase(it);
-    const auto now = Clock::now();
-    const bool brief = std::chrono::duration<double>(now - b.since).count() < kPoolShort;
-    b.since = now;
-    (brief ? P.idle : old).push_back(b);
-    take_out(P, b.device, false, kPoolMost, &old);
-  }
-  release(old);
+  blocks().free(p);
 } catch (...) {
   // the block stays with the process
 }
 
 void pool_trim() try {
   int device = 0;
-  if (hipGetDevice(&device) != hipSuccess) return;
-  std::vector<Block> old;
-  Pool& P = pool();
-  {
-    std::lock_guard<std::mutex> lk(P.mu);
-    take_out(P, device, true, 0, &old);
-  }
-  release(old);
+  if (hipGetDevice(&device) == hipSuccess) blocks().trim(device);
 } catch (...) {
-  // idle blocks stay for the next call
+  // idle blocks stay until the thread looks
 }
 
 }  // namespace grim
+
+extern "C" int grim_trim_memory(void) try {
+  grim::clear_error();
+  grim::blocks().trim(-1);
+  return GRIM_OK;
+} catch (...) {
+  return grim::set_error(GRIM_ENOMEM, "no host memory for the list of blocks");
+}

@@ -140,7 +140,7 @@ EXPORTS = ["grim_abi_version", "grim_last_error", "grim_build_index", "grim_inde
            "grim_serve_stats", "grim_serve_reset_stats", "grim_serve_destroy", "grim_verify_candidates",
            "grim_seeds_build", "grim_seeds_info", "grim_seeds_free", "grim_seed_candidates",
            "grim_reverse_complement", "grim_mask_summary", "grim_verify_candidates_bounded",
-           "grim_filter_candidates_static"]
+           "grim_filter_candidates_static", "grim_trim_memory"]
 
 _lib = None
 
@@ -158,6 +158,7 @@ def lib(path: str = LIB_PATH):
     sig = {
         "grim_abi_version": ([], I),
         "grim_last_error": ([], ctypes.c_char_p),
+        "grim_trim_memory": ([], I),
         "grim_build_index": ([P, U64, U32, U32, U32, U32, U32, P, PP], I),
         "grim_index_info": ([P, ctypes.POINTER(IndexInfo)], I),
         "grim_index_read": ([P, U32, U64, U64, P], I),
@@ -520,6 +521,11 @@ def grim_profile_read(reset: bool = False) -> dict:
     _check(lib().grim_profile_read(ctypes.byref(p), 1 if reset else 0))
     return {k: {"launches": getattr(p, k).launches, "total_ms": getattr(p, k).total_ms,
                 "last_ms": getattr(p, k).last_ms} for k, _ in Profile._fields_}
+
+
+def grim_trim_memory():
+    """Give device memory that the library keeps for its next handles back to the driver."""
+    _check(lib().grim_trim_memory())
 
 
 def grim_abi_version() -> int:
