@@ -298,9 +298,8 @@ int grim_seed_candidates(const grim_seeds* seeds, const grim_reads* reads, uint3
  * E_r + 1 (at most 0xFFFE) when it is larger; match_out[k] is unchanged
  * (dist <= E_r). A mapper's verification only needs to know whether a
  * location maps within E_r (Section 1, seed-and-extend step 5), and the
- * bound lets each lane advance only the 32-row words of the dynamic program
- * that can still hold a distance <= E_r (Myers 1999, Section 4: the block
- * form with Ukkonen's cutoff), which at most locations is the first one.
+ * bound lets a bin that holds none of E_r + 1 disjoint pieces of the read be
+ * settled without an alignment, and the others be aligned only around them.
  * Arguments, requirements and errors as for grim_verify_candidates. */
 int grim_verify_candidates_bounded(const grim_index* idx, const grim_reads* reads, const int64_t* cand_off,
                                    const int32_t* cand_bin, uint64_t n_cand, const uint8_t* verify_mask,

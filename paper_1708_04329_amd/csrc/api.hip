@@ -742,7 +742,7 @@ int verify_impl(const grim_index* cidx, const grim_reads* rd, const int64_t* can
   pt.collect();
   if (rc) return rc;
   uint64_t total = 0;
-  for (uint32_t w = 0; w < kVerifyBuckets; ++w) {
+  for (uint32_t w = 0; w < verify_classes(bounded); ++w) {
     first[w] = total;
     total += counts[w];
   }
@@ -765,11 +765,12 @@ int verify_impl(const grim_index* cidx, const grim_reads* rd, const int64_t* can
   ProfSpan pv(PROF_VERIFY);
   pv.start(s);
   if (bounded) {
-    GRIM_HIP_TRY(launch_verify_sift(a, total, s));
+    GRIM_HIP_TRY(launch_verify_sift(a, first[kVerifyWords + 1], s));
     GRIM_HIP_TRY(launch_verify_left(a, first, counts, s));
-  } else {
-    for (uint32_t w = 1; w < kVerifyBuckets; ++w) GRIM_HIP_TRY(launch_verify_align(a, w, first[w], counts[w], s));
   }
+  const uint32_t whole = bounded ? kVerifyWords : 0;  // classes whose texts are aligned whole
+  for (uint32_t w = 1; w <= kVerifyWords; ++w)
+    GRIM_HIP_TRY(launch_verify_align(a, w, first[whole + w], counts[whole + w], s));
   pv.stop(s);
   GRIM_HIP_TRY(hipStreamSynchronize(s));  // the inputs' status is known: nothing after the count sets it
   wait.done();

@@ -171,7 +171,11 @@ hipError_t launch_ref_codes(const uint8_t* ref, uint64_t G, uint8_t* codes, hipS
 // Verification of (read, bin) pairs: bit-parallel semi-global edit distance
 // of the read against the bases of the bin's extent.
 constexpr uint32_t kVerifyMaxLen = 512;   // bases per read: 16 words of 32 rows
-constexpr uint32_t kVerifyBuckets = 17;   // work lists by words per read, 1..16
+constexpr uint32_t kVerifyWords = 16;
+// Work lists by words per read, 1..16; in the bounded form those of the reads that
+// the sift cannot look through follow, 17..32.
+constexpr uint32_t kVerifyBuckets = 1 + 2 * kVerifyWords;
+inline uint32_t verify_classes(bool bounded) { return bounded ? kVerifyBuckets : 1 + kVerifyWords; }
 struct VerifyArgs {
   const uint8_t* ref;        // base codes, G bytes
   uint64_t G;
@@ -189,9 +193,9 @@ struct VerifyArgs {
   uint8_t* match_out;
   uint32_t* status;
   uint64_t* bucket;          // [kVerifyBuckets] pairs to align per class
-  uint32_t* read_sel;        // [n_reads] pairs selected per read (first pass)
+  uint2* read_sel;           // [n_reads] pairs selected per read and its class (first pass)
   uint32_t chunk;            // reads per chunk: verify_chunk_reads(n_reads)
-  uint64_t* chunk_sum;       // [chunks][kVerifyBuckets] pair counts, then first slots
+  uint64_t* chunk_sum;       // [kVerifyBuckets][chunks] pair counts, then first slots
   uint64_t* item_pair;       // work list: pair index
   uint32_t* item_read;       //            and its read
   uint2* item_span;          // bounded: where an alignment within E_r may lie, per work item
@@ -205,15 +209,15 @@ uint64_t verify_chunks(uint64_t n_reads);
 hipError_t launch_verify_count(const VerifyArgs& a, hipStream_t s);
 // Fill the work list from the counts and positions of launch_verify_count.
 hipError_t launch_verify_scatter(const VerifyArgs& a, hipStream_t s);
-// Bounded form: find the items (of all `count`) that can be within their budget
-// (item_span) and write the outputs of the others.
+// Bounded form: find which of the items [0, count), of classes 1..16, can be within
+// their budget (item_span) and write the outputs of the others.
 hipError_t launch_verify_sift(const VerifyArgs& a, uint64_t count, hipStream_t s);
 constexpr uint64_t kRefTail = 64;  // bytes past the reference copy that the sift may read
 // Bounded form: align what the sift left; reads of w words are the items
-// [first[w], first[w] + count[w]), w = 1 .. kVerifyBuckets - 1.
+// [first[w], first[w] + count[w]), w = 1 .. kVerifyWords.
 hipError_t launch_verify_left(const VerifyArgs& a, const uint64_t* first, const uint64_t* count, hipStream_t s);
-// Exact form: align work items [first, first + count), all of whose reads have
-// `words` 32-base words.
+// Align the whole text of work items [first, first + count), all of whose reads
+// have `words` 32-base words.
 hipError_t launch_verify_align(const VerifyArgs& a, uint32_t words, uint64_t first, uint64_t count,
                                hipStream_t s);
 
@@ -366,7 +370,7 @@ struct grim_workspace {
   uint64_t vitem_cap = 0, vitem_read_cap = 0;
   uint2* vitem_span = nullptr;       // bounded verification: where to align
   uint64_t vitem_span_cap = 0;
-  uint32_t* vread_sel = nullptr;     // pairs selected per read
+  uint2* vread_sel = nullptr;        // pairs selected per read, and its class
   uint64_t vread_sel_cap = 0;
   uint64_t* vchunk_sum = nullptr;    // per-chunk class counts / first slots
   uint64_t vchunk_sum_cap = 0;

@@ -21,20 +21,21 @@
 // runs) take a checked step that masks it out.
 //
 // Work split: one lane per pair. A first pass counts the pairs to align per
-// read length class (words per read, 1..16) and writes the outputs of the
-// pairs it skips; a prefix over chunks of reads turns the counts into list
-// positions (no global atomics, which would serialise on a few class
-// counters); a second pass lists the pairs class by class, so that one
-// launch per class runs lanes with equal word counts in lock step.
+// class (words per read, 1..16) and writes the outputs of the pairs it skips; a
+// prefix over chunks of reads turns the counts into list positions (no global
+// atomics, which would serialise on a few class counters); a second pass lists
+// the pairs class by class, so that one launch per class runs lanes with equal
+// word counts in lock step.
 //
 // The bounded form first looks for the pairs that can map at all (k_verify_sift):
 // of E + 1 disjoint pieces of a read, E edits leave one untouched, so a bin
 // that holds none of them exactly is further than E. Only the others, and of
-// their bins only the stretch around the pieces found, are aligned.
+// their bins only the stretch around the pieces found, are aligned. Reads whose
+// pieces would be too short have classes of their own, and their bins are aligned
+// whole as in the exact form.
 
 #include <algorithm>
 #include <cstdlib>
-#include <type_traits>
 
 #include "grim_internal.h"
 #include "verify_text.h"
@@ -66,14 +67,28 @@ __device__ __forceinline__ void load_groups(const VerifyArgs& a, int64_t k0, int
   }
 }
 
-__device__ __forceinline__ uint32_t length_class(const VerifyArgs& a, uint64_t r) {
+// Pieces of a read of L bases that the sift looks for, of which E edits leave one
+// untouched (see k_verify_sift); 0 where it cannot.
+constexpr uint32_t kMinPiece = 13;
+constexpr uint32_t kMaxPieces = 32;
+__device__ __forceinline__ uint32_t sift_pieces(int64_t E, uint32_t L) {
+  return E >= 0 && E < (int64_t)kMaxPieces && L / (uint32_t)(E + 1) >= kMinPiece ? (uint32_t)E + 1 : 0u;
+}
+
+// Work list of read r; 0: it has no bases or too many.
+__device__ __forceinline__ uint32_t list_class(const VerifyArgs& a, uint64_t r) {
   const uint64_t L = (uint64_t)(a.offsets[r + 1] - a.offsets[r]);
-  return (L == 0 || L > kVerifyMaxLen) ? 0u : (uint32_t)((L + 31) / 32);
+  if (L == 0 || L > kVerifyMaxLen) return 0u;
+  const uint32_t words = (uint32_t)((L + 31) / 32);
+  if (!a.bounded) return words;
+  // E_r from the threshold, which is at least -2^30
+  const int32_t E = ((int32_t)L - (int32_t)a.q + 1 - a.thr[r]) / (int32_t)a.q;
+  return sift_pieces(E, (uint32_t)L) ? words : words + kVerifyWords;
 }
 
 // First pass, one workgroup of 16 wavefronts per chunk of reads, a wavefront
-// per read: count the read's selected pairs (read_sel), write the outputs of the
-// pairs it skips, and sum the counts per length class for the chunk
+// per read: count the read's selected pairs (read_sel, with its class), write the outputs of the
+// pairs it skips, and sum the counts per class (list_class) for the chunk
 // (chunk_sum[class][chunk]). No global atomics: the list positions come from
 // a prefix over chunks. Bound by the lists' bytes (5 in, 3 out per pair).
 __global__ __launch_bounds__(1024) void k_verify_count(VerifyArgs a) {
@@ -89,10 +104,11 @@ __global__ __launch_bounds__(1024) void k_verify_count(VerifyArgs a) {
     if (c0 < 0 || c1 < c0 || (uint64_t)c1 > a.n_cand || c1 - c0 > 0xFFFFFFFFll) {
       if (lane == 0) {
         atomicOr(a.status, ST_BAD_CAND_OFF);
-        a.read_sel[r] = 0;
+        a.read_sel[r] = make_uint2(0, 0);
       }
       continue;
     }
+    const uint32_t cls = list_class(a, r);
     uint32_t n_sel = 0;
     for (int64_t k0 = c0; k0 < c1; k0 += kGroups * 64) {
       int32_t x[kGroups];
@@ -114,9 +130,8 @@ __global__ __launch_bounds__(1024) void k_verify_count(VerifyArgs a) {
       }
     }
     if (lane == 0) {
-      a.read_sel[r] = n_sel;
+      a.read_sel[r] = make_uint2(n_sel, cls);
       if (n_sel) {
-        const uint32_t cls = length_class(a, r);
         if (cls == 0) atomicOr(a.status, ST_VERIFY_LONG);
         else atomicAdd(&csum[cls], (unsigned long long)n_sel);
       }
@@ -126,7 +141,7 @@ __global__ __launch_bounds__(1024) void k_verify_count(VerifyArgs a) {
   if (threadIdx.x < kVerifyBuckets) a.chunk_sum[(uint64_t)threadIdx.x * gridDim.x + blockIdx.x] = csum[threadIdx.x];
 }
 
-// One wavefront per length class 1..16 (class 0 holds no pairs): a scan over
+// One wavefront per class, 16 to a workgroup (class 0 holds no pairs): a scan over
 // the chunks, 512 at a time (8 per lane, loaded together), turns
 // chunk_sum[class][chunk] into the pairs of that class in the chunks before;
 // bucket[class] gets the class's pair count (the host launches one alignment per
@@ -138,7 +153,7 @@ __device__ __forceinline__ uint64_t shfl_up64(uint64_t v, uint32_t d) {
 
 __global__ __launch_bounds__(1024) void k_verify_prefix(VerifyArgs a, uint64_t n_chunks) {
   constexpr uint32_t kPer = 8;
-  const uint32_t lane = threadIdx.x & 63u, c = 1 + (threadIdx.x >> 6);  // classes 1..16
+  const uint32_t lane = threadIdx.x & 63u, c = 1 + kVerifyWords * blockIdx.x + (threadIdx.x >> 6);
   uint64_t* sums = a.chunk_sum + (uint64_t)c * n_chunks;
   unsigned long long acc = 0;
   for (uint64_t k0 = 0; k0 < n_chunks; k0 += 64 * kPer) {
@@ -163,7 +178,7 @@ __global__ __launch_bounds__(1024) void k_verify_prefix(VerifyArgs a, uint64_t n
     acc += ((uint64_t)(uint32_t)__shfl((int)(incl >> 32), 63) << 32) | (uint32_t)__shfl((int)(uint32_t)incl, 63);
   }
   if (lane == 0) a.bucket[c] = acc;
-  if (threadIdx.x == 0) a.bucket[0] = 0;
+  if (c == 1 && lane == 0) a.bucket[0] = 0;
 }
 
 // Second pass, same chunks: each wavefront claims its read's slots in the
@@ -183,7 +198,7 @@ __global__ __launch_bounds__(1024) void k_verify_scatter(VerifyArgs a) {
   }
   __syncthreads();
   for (uint64_t r = r_lo + wave; r < r_hi; r += 16) {
-    const uint32_t n_sel = a.read_sel[r], cls = length_class(a, r);
+    const uint32_t n_sel = a.read_sel[r].x, cls = a.read_sel[r].y;
     if (n_sel == 0 || cls == 0) continue;
     const int64_t c0 = a.cand_off[r], c1 = a.cand_off[r + 1];
     unsigned long long claim = 0;
@@ -294,72 +309,6 @@ struct Column {
   }
 };
 
-// Bounded form of the same step (Myers 1999, Section 4: the block-based
-// algorithm with Ukkonen's cutoff): only words 0..y advance, y being the last
-// word that can hold a distance <= k in this column; every cell below it is
-// known to exceed k. sc[w] is the distance at word w's last row (row `top`
-// for word W - 1). Word y + 1 joins when its first row can reach k: the last
-// active word's bottom was <= k in the previous column and either the text
-// base matches that first row or the bottom decreased. It joins as if its
-// previous column rose by one per row (Myers' initialisation; cells whose
-// true distance is <= k still come out exact). A last active word leaves once
-// its last row's distance minus its +1 bits exceeds k (no cell of it can then
-// be <= k). Distances <= k are exact; larger ones are reported as k + 1.
-template <int W>
-struct ColumnB {
-  uint32_t r0[W], r1[W], va[W];
-  uint32_t pv[W], mv[W];
-  int32_t sc[W];
-  uint32_t top, lastmask;  // lastmask: rows 0..top of word W - 1
-  int32_t k, y, best;
-
-  template <bool CHECKED>
-  __device__ __forceinline__ void step(uint32_t c) {
-    const uint32_t c0 = 0u - (c & 1u), c1 = 0u - ((c >> 1) & 1u);
-    const uint32_t valid = (!CHECKED || c < 4u) ? 0xFFFFFFFFu : 0u;
-    uint32_t php = 0, mhp = 0;
-    int32_t hprev = 0;  // horizontal difference out of the previous word's last row
-    int32_t yn = y;
-#pragma unroll
-    for (int w = 0; w < W; ++w) {
-      uint32_t eq = __builtin_amdgcn_bitop3_b32(va[w], r0[w], c0, 0x90);
-      eq = __builtin_amdgcn_bitop3_b32(eq, r1[w], c1, 0x90);
-      if (CHECKED) eq &= valid;
-      if (w > 0 && w == yn + 1 && sc[w - 1] - hprev <= k && ((eq & 1u) || hprev < 0)) {
-        pv[w] = 0xFFFFFFFFu;
-        mv[w] = 0;
-        sc[w] = sc[w - 1] - hprev + (w == W - 1 ? (int32_t)top + 1 : 32);
-        yn = w;
-      }
-      if (w <= yn) {
-        const uint32_t xv = eq | mv[w];
-        eq |= mhp >> 31;
-        const uint32_t sum = (eq & pv[w]) + pv[w];
-        const uint32_t xh = __builtin_amdgcn_bitop3_b32(sum, pv[w], eq, 0xBE);  // (sum ^ pv) | eq
-        const uint32_t ph = mv[w] | ~(xh | pv[w]);
-        const uint32_t mh = pv[w] & xh;
-        const uint32_t bit = w == W - 1 ? top : 31u;
-        hprev = (int32_t)((ph >> bit) & 1u) - (int32_t)((mh >> bit) & 1u);
-        sc[w] += hprev;
-        const uint32_t phs = __builtin_amdgcn_alignbit(ph, php, 31);
-        const uint32_t mhs = __builtin_amdgcn_alignbit(mh, mhp, 31);
-        pv[w] = mhs | ~(xv | phs);
-        mv[w] = phs & xv;
-        php = ph;
-        mhp = mh;
-      }
-    }
-    y = yn;
-    if (y == W - 1) best = min(best, sc[W - 1]);
-    // going up from a word's last row the distance falls by at most one per
-    // +1 bit, so a last active word whose last row minus its +1 bits exceeds
-    // k holds no cell <= k and leaves
-#pragma unroll
-    for (int w = W - 1; w >= 1; --w)
-      if (y == w && sc[w] - (int32_t)__popc(w == W - 1 ? pv[w] & lastmask : pv[w]) > k) y = w - 1;
-  }
-};
-
 // A pair's read and bin: the read's bases and budget, the bases bin x's tokens
 // cover, text [lo, hi).
 struct Pair {
@@ -385,10 +334,9 @@ __device__ __forceinline__ Pair pair_of(const VerifyArgs& a, uint32_t r, uint32_
 }
 
 // The smallest distance of pair p's read to a part of text [lo, hi) within its bin.
-template <int W, bool BOUNDED>
+template <int W>
 __device__ __forceinline__ int32_t align_text(const VerifyArgs& a, const Pair& p, uint64_t lo, uint64_t hi) {
-  using Col = typename std::conditional<BOUNDED, ColumnB<W>, Column<W>>::type;
-  Col col;
+  Column<W> col;
   const uint32_t L = p.L;
 #pragma unroll
   for (int w = 0; w < W; ++w) {
@@ -412,18 +360,7 @@ __device__ __forceinline__ int32_t align_text(const VerifyArgs& a, const Pair& p
     col.mv[w] = 0;
   }
   col.top = (L - 1) & 31u;
-  col.best = (int32_t)L;
-  if constexpr (BOUNDED) {
-    // column 0: row i holds distance i + 1, so the words up to the one holding
-    // row k - 1 start active (word 0 always)
-    col.k = (int32_t)min<int64_t>(p.E, 1 << 20);
-    col.lastmask = col.top == 31u ? 0xFFFFFFFFu : (2u << col.top) - 1u;
-    col.y = col.k >= 1 ? min((int32_t)W - 1, (col.k - 1) / 32) : 0;
-#pragma unroll
-    for (int w = 0; w < W; ++w) col.sc[w] = w == W - 1 ? (int32_t)L : 32 * (w + 1);
-  } else {
-    col.score = (int32_t)L;
-  }
+  col.best = col.score = (int32_t)L;
 
   const uint8_t* txt = a.ref;
   uint64_t j = lo;
@@ -458,14 +395,19 @@ __device__ __forceinline__ void write_distance(const VerifyArgs& a, uint64_t k, 
   a.match_out[k] = (int64_t)d <= E ? 1 : 0;
 }
 
-// Exact distances, one lane per listed pair.
+// The whole text of every listed pair, a lane each: all pairs in the exact form, in
+// the bounded form those of reads that the sift cannot look through. These have
+// lists of their own: cut to a workgroup of k_verify_left they ended unevenly (2M
+// pairs of 100 bp reads at E = 10: 8.7 ms for the call). The full column serves
+// them too: with Ukkonen's cutoff, which the add with carry does not allow, 200000
+// such pairs took 1.43 ms, with it 1.10.
 template <int W>
 __global__ __launch_bounds__(256) void k_verify_align(VerifyArgs a, uint64_t first, uint64_t count) {
   const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= count) return;
   const uint64_t k = a.item_pair[first + t];
   const Pair p = pair_of(a, a.item_read[first + t], (uint32_t)a.cand_bin[k]);
-  write_distance(a, k, align_text<W, false>(a, p, p.lo, p.hi), p.E);
+  write_distance(a, k, align_text<W>(a, p, p.lo, p.hi), p.E);
 }
 
 // ---------------------------------------------------------------------------
@@ -491,8 +433,6 @@ __global__ __launch_bounds__(256) void k_verify_align(VerifyArgs a, uint64_t fir
 // bp) take 0.61 ms, 2.8 TB/s, and the alignments of what is left 0.94 ms; without
 // the sift the alignments took 5.1 ms.
 // ---------------------------------------------------------------------------
-constexpr uint32_t kMinPiece = 13;
-constexpr uint32_t kMaxPieces = 32;
 constexpr uint32_t kMapBits = 13, kMapWords = (1u << kMapBits) / 32;
 
 // 16 text or read bases of code bytes (bits 0-1), the first most significant.
@@ -531,8 +471,8 @@ __device__ __forceinline__ uint32_t piece_hash(uint32_t code) { return code * 0x
 // Sifts items [0, count): item_span[t] = the part of the pair's text, as offsets
 // from its start, that an alignment within the budget lies in: what one that
 // touches a found piece can cover. Empty (0, 0) where none was found, and then
-// the pair's outputs are written here. Pairs the sift does not apply to get the
-// whole text, (0, kWholeText).
+// the pair's outputs are written here. Texts too long for the offsets get all of
+// theirs, (0, kWholeText).
 __global__ __launch_bounds__(256) void k_verify_sift(VerifyArgs a, uint64_t count) {
   __shared__ __attribute__((aligned(16))) SiftLds lds_all[4][4];
   const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, sub = lane >> 4, j = lane & 15u;
@@ -549,8 +489,7 @@ __global__ __launch_bounds__(256) void k_verify_sift(VerifyArgs a, uint64_t coun
     my_pair = a.item_pair[t];
     my_read = a.item_read[t];
     mine = pair_of(a, my_read, (uint32_t)a.cand_bin[my_pair]);
-    if (mine.E >= 0 && mine.E < (int64_t)kMaxPieces && mine.L / (uint32_t)(mine.E + 1) >= kMinPiece)
-      my_np = (uint32_t)mine.E + 1;
+    my_np = sift_pieces(mine.E, mine.L);
     my_L = mine.L;
     my_rd = (uint64_t)(mine.rd - a.bases);
     my_txt = mine.lo & ~15ull;
@@ -730,7 +669,7 @@ struct LeftLds {
 static_assert(kMostLeft == 1u << 11, "item bits of a part");
 
 // Items [t0, t0 + n), reads of W words, by one workgroup.
-template <int W, bool BOUNDED>
+template <int W>
 __device__ __forceinline__ void left_items(const VerifyArgs& a, uint64_t t0, uint32_t n, LeftLds& lds) {
   uint32_t* const part = lds.part;
   uint32_t* const best_of = lds.best_of;
@@ -786,16 +725,8 @@ __device__ __forceinline__ void left_items(const VerifyArgs& a, uint64_t t0, uin
     const Pair p = pair_of(a, a.item_read[t0 + item], (uint32_t)a.cand_bin[a.item_pair[t0 + item]]);
     const uint2 sp = a.item_span[t0 + item];
     const uint32_t np = whole ? 1u : parts_of(sp, item);
-    int32_t best;
-    // near an alignment most words are in play, and the full column is the
-    // faster; the cutoff serves the whole bins
-    if (BOUNDED && sp.y == kWholeText) {
-      best = align_text<W, BOUNDED>(a, p, p.lo, p.hi);
-    } else {
-      const TextPart text = text_part(p.lo, p.hi, sp.x, sp.y, np, u, p.L + (uint32_t)p.E);
-      best = align_text<W, false>(a, p, text.lo, text.hi);
-    }
-    atomicMin(&best_of[item], (uint32_t)best);
+    const TextPart text = text_part(p.lo, p.hi, sp.x, sp.y, np, u, p.L + (uint32_t)p.E);
+    atomicMin(&best_of[item], (uint32_t)align_text<W>(a, p, text.lo, text.hi));
   }
   __syncthreads();
   for (uint32_t i = t; i < n; i += 256) {
@@ -814,9 +745,6 @@ struct LeftPlan {
   uint64_t first[8], count[8];
 };
 
-// the cutoff pays off for reads of up to 6 words (measured: 1.3x at 4 and 5
-// words, 0.86x at 8, where lanes diverge over more words); longer reads run
-// the full column and cap the distance
 template <int W0>
 __global__ __launch_bounds__(256) void k_verify_left(VerifyArgs a, LeftPlan plan) {
   __shared__ LeftLds lds;
@@ -825,14 +753,14 @@ __global__ __launch_bounds__(256) void k_verify_left(VerifyArgs a, LeftPlan plan
   const uint64_t at = (uint64_t)(blockIdx.x - plan.block[c]) * plan.per, t0 = plan.first[c] + at;
   const uint32_t n = (uint32_t)min<uint64_t>(plan.per, plan.count[c] - at);
   switch (c) {
-    case 0: left_items<W0 + 7, (W0 + 7 <= 6)>(a, t0, n, lds); break;
-    case 1: left_items<W0 + 6, (W0 + 6 <= 6)>(a, t0, n, lds); break;
-    case 2: left_items<W0 + 5, (W0 + 5 <= 6)>(a, t0, n, lds); break;
-    case 3: left_items<W0 + 4, (W0 + 4 <= 6)>(a, t0, n, lds); break;
-    case 4: left_items<W0 + 3, (W0 + 3 <= 6)>(a, t0, n, lds); break;
-    case 5: left_items<W0 + 2, (W0 + 2 <= 6)>(a, t0, n, lds); break;
-    case 6: left_items<W0 + 1, (W0 + 1 <= 6)>(a, t0, n, lds); break;
-    default: left_items<W0, (W0 <= 6)>(a, t0, n, lds); break;
+    case 0: left_items<W0 + 7>(a, t0, n, lds); break;
+    case 1: left_items<W0 + 6>(a, t0, n, lds); break;
+    case 2: left_items<W0 + 5>(a, t0, n, lds); break;
+    case 3: left_items<W0 + 4>(a, t0, n, lds); break;
+    case 4: left_items<W0 + 3>(a, t0, n, lds); break;
+    case 5: left_items<W0 + 2>(a, t0, n, lds); break;
+    case 6: left_items<W0 + 1>(a, t0, n, lds); break;
+    default: left_items<W0>(a, t0, n, lds); break;
   }
 }
 
@@ -886,7 +814,7 @@ hipError_t launch_verify_count(const VerifyArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(k_verify_count, dim3((unsigned)chunks), dim3(1024), 0, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_verify_prefix, dim3(1), dim3(1024), 0, s, a, chunks);
+  hipLaunchKernelGGL(k_verify_prefix, dim3(a.bounded ? 2 : 1), dim3(1024), 0, s, a, chunks);
   return hipGetLastError();
 }
 
