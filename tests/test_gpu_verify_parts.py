@@ -1,8 +1,11 @@
-"""Bounded verification of lists whose workgroups take several pairs for each lane,
-of reads that the sift can look through and others. Against the oracle's dynamic
-program, on a sample of the pairs."""
+"""Bounded verification of long bins: texts cut into up to 64 parts, more parts in a
+workgroup than its table holds (texts are then taken as they are), and lists whose
+workgroups take several pairs for each lane. Against the oracle's dynamic program,
+on every pair or a sample of them."""
 
 from __future__ import annotations
+
+import random
 
 import numpy as np
 import pytest
@@ -11,6 +14,7 @@ import synth
 from gpu_util import dev
 from paper_1708_04329_amd import grim
 from test_gpu_verify import run_verify
+from test_gpu_verify_sift import edited
 
 pytestmark = pytest.mark.gpu
 
@@ -19,6 +23,38 @@ def listed(cand):
     co = np.zeros(len(cand) + 1, np.int64)
     co[1:] = np.cumsum([len(c) for c in cand])
     return co, np.concatenate([np.array(c, np.int32) for c in cand])
+
+
+@pytest.mark.parametrize("B,step,n_reads", [(4_000, 700, 12), (9_000, 1_500, 60), (20_000, 3_000, 60)])
+def test_texts_of_many_parts(oracle, B, step, n_reads):
+    """Copies of one unit all along the reference, reads of it: every bin is left by
+    the sift and its pieces lie from end to end (9 and 20 kbp: 48 and 64 parts, so
+    256 pairs make three and four times the 4096 parts of a workgroup's table)."""
+    rng = random.Random(B)
+    G, O, q = 12 * B + 77, 300, 5
+    unit = rng.choices(b"ACGT", k=300)
+    ref = bytearray(rng.choices(b"ACGT", k=G))
+    for p in range(0, G - 300, step):
+        ref[p:p + 300] = bytes(unit)
+        ref[p + rng.randrange(300)] = rng.choice(b"ACGT")
+    nb = -(-G // B)
+    seqs, budget, cand = [], [], []
+    for i in range(n_reads):
+        L = rng.choice([30, 100, 190, 193, 250])
+        E = rng.choice([0, 1, L // 30, L // 20])
+        s = edited(rng, bytes(unit[7:7 + L]), E, rng.randrange(E + 1))
+        seqs.append(s + b"ACGTA"[:max(0, 5 - len(s))])
+        budget.append(E)
+        cand.append(list(range(nb)))
+    ref = np.frombuffer(bytes(ref), np.uint8).copy()
+    rd = synth.reads_from_strings(seqs)
+    co, cb = listed(cand)
+    budget = np.array(budget, np.uint16)
+    idx = grim.grim_build_index(dev(ref), B, O, q, grim.LAYOUT_REF)
+    got_d, got_m = run_verify(idx, rd, co, cb, bounded=True, max_edits=budget)
+    want_d, want_m = oracle.verify_bounded(ref, B, O, q, rd.bases, rd.offsets, co, cb, max_edits=budget)
+    assert np.array_equal(got_d, want_d) and np.array_equal(got_m, want_m)
+    assert want_m.any()
 
 
 @pytest.mark.parametrize("n_pairs", [8192 * 256 + 1, 3 * 8192 * 256 + 513])
