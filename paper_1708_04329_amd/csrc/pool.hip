@@ -34,7 +34,8 @@ namespace grim {
 namespace {
 
 constexpr size_t kMost = size_t(12) << 30;
-constexpr size_t kLook = size_t(64) << 20;  // smaller blocks are kept without a look at the free memory
+constexpr size_t kLook = size_t(64) << 20;  // smaller blocks are kept without a look at the free memory,
+constexpr double kLookAgain = 0.1;          // which a loop takes this often at most (10 us each)
 constexpr double kIdle = 2.0, kBrief = 2.0;
 
 // The thread that gives idle blocks back, and what it shares with the process's end.
@@ -75,6 +76,15 @@ struct OnDevice {
 };
 
 struct HipDriver {
+  struct Look {
+    int device = -1;
+    double at = 0;
+    size_t spare = 0;
+  };
+  static constexpr size_t kDevices = 16;
+  std::mutex mu;
+  Look seen[kDevices];  // the last look at each device's free memory
+
   bool alloc(void** out, size_t bytes, int) {
     if (hipMalloc(out, bytes) == hipSuccess) return true;
     (void)hipGetLastError();  // reported by the result alone
@@ -89,9 +99,15 @@ struct HipDriver {
   }
   size_t spare(int device, size_t bytes) {
     if (bytes < kLook) return kMost;
-    OnDevice on(device);
-    size_t fr = 0, total = 0;
-    return hipMemGetInfo(&fr, &total) == hipSuccess ? fr / 16 : 0;
+    std::lock_guard<std::mutex> lk(mu);
+    Look& l = seen[(size_t)device % kDevices];
+    const double t = now();
+    if (l.device != device || t - l.at > kLookAgain) {
+      OnDevice on(device);
+      size_t fr = 0, total = 0;
+      l = {device, t, hipMemGetInfo(&fr, &total) == hipSuccess ? fr / 16 : 0};
+    }
+    return l.spare;
   }
   bool watch() try {
     Watch& w = grim::watch();
@@ -117,8 +133,8 @@ struct HipDriver {
 };
 
 pool::Pool<HipDriver>& blocks() {
-  static HipDriver drv;
-  static auto* p = new pool::Pool<HipDriver>(drv, pool::Limits{kMost, kIdle, kBrief});
+  static auto* drv = new HipDriver;
+  static auto* p = new pool::Pool<HipDriver>(*drv, pool::Limits{kMost, kIdle, kBrief});
   return *p;
 }
 

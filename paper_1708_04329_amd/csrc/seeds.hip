@@ -639,6 +639,7 @@ struct SelArgs {
   const uint64_t* start;
   const uint32_t* pos;
   uint32_t k;
+  uint32_t most_seeds;       // of a read whose seeds' offsets are below 2^32: the hash tables take longer ones
   const uint2* found;        // the seeds' first places in pos[] and hits (k_seed_hits)
   const uint8_t* bases;
   const int64_t* offsets;
@@ -1195,8 +1196,7 @@ __global__ __launch_bounds__(T) void k_seed_select(SelArgs a) {
 // dependent loads that start a read (a third of its 25 us), which the other
 // workgroups of a CU hide: 19241 reads of up to 24576 hits on the 3.1 Gbp reference
 // (77 M hits) take 0.57 ms, the hash tables took 1.7.
-// A read with more than kSeedBucket hits in one bucket, or more seeds than the
-// lists hold, goes on to the hash tables.
+// A read with more than kSeedBucket hits in one bucket goes on to the hash tables.
 constexpr uint32_t kSeedBucket = 255;
 
 template <int T, int HPT, int SPT>
@@ -1210,20 +1210,26 @@ struct SortLds {
   uint32_t s_pre[kSeeds + 1];      // hits of the seeds before it
   uint32_t ws[T / 64 + 1];
   uint32_t sh[4];
+  // cnt, hist and sh to zero; the barriers of take_seeds follow
+  __device__ __forceinline__ void clear(uint32_t t) {
+#pragma unroll
+    for (uint32_t u = 0; u < SPT; u += 4) *reinterpret_cast<uint4*>(cnt + SPT * t + u) = make_uint4(0, 0, 0, 0);
+    for (uint32_t v = t; v <= kSeedBucket; v += T) hist[v] = 0;
+    if (t < 4) sh[t] = 0;
+  }
 };
 
-// Takes the read's n_seeds <= kSeeds seeds; returns its hits. Clears hist and sh.
+// Takes seeds [s0, s0 + kSeeds) of a read's n_seeds; returns their hits. Every thread
+// is done with the ones before.
 template <int T, typename Lds>
-__device__ __forceinline__ uint32_t sort_seeds(const uint2* found, uint32_t n_seeds, Lds& m) {
+__device__ __forceinline__ uint32_t take_seeds(const uint2* found, uint32_t n_seeds, uint32_t s0, Lds& m) {
   const uint32_t t = threadIdx.x;
   uint32_t h0 = 0, c = 0;
-  if (t < n_seeds) {
-    const uint2 f = found[t];
+  if (t < Lds::kSeeds && t < n_seeds - s0) {
+    const uint2 f = found[s0 + t];
     h0 = f.x;
     c = f.y;
   }
-  for (uint32_t v = t; v <= kSeedBucket; v += T) m.hist[v] = 0;
-  if (t < 4) m.sh[t] = 0;
   uint32_t H;
   const uint32_t ex = block_excl_scan<T, uint32_t>(c, m.ws, &H);
   if (t < Lds::kSeeds) {
@@ -1235,11 +1241,12 @@ __device__ __forceinline__ uint32_t sort_seeds(const uint2* found, uint32_t n_se
   return H;
 }
 
-// Bins of hits f0 + h T, h < N, below H (the seed of the first is s or later);
-// the positions are all loaded before the first is used.
+// Bins of hits f0 + h T, h < N, of the H hits of the seeds taken, the first of which
+// starts at base o0 of its read (the seed of the first hit is s or later); the
+// positions are all loaded before the first is used.
 template <int T, int N, typename Lds>
-__device__ __forceinline__ void hit_bins(const SelArgs& a, const Lds& m, uint32_t f0, uint32_t H, uint32_t& s,
-                                         uint32_t (&bin)[N]) {
+__device__ __forceinline__ void hit_bins(const SelArgs& a, const Lds& m, uint32_t f0, uint32_t H, uint32_t o0,
+                                         uint32_t& s, uint32_t (&bin)[N]) {
   uint32_t o[N];
 #pragma unroll
   for (int h = 0; h < N; ++h) {
@@ -1249,7 +1256,7 @@ __device__ __forceinline__ void hit_bins(const SelArgs& a, const Lds& m, uint32_
     if (f < H) {
       while (m.s_pre[s + 1] <= f) ++s;
       bin[h] = a.pos[m.s_h0[s] + (f - m.s_pre[s])];
-      o[h] = s * a.k;
+      o[h] = o0 + s * a.k;
     }
   }
 #pragma unroll
@@ -1261,6 +1268,39 @@ __device__ __forceinline__ void hit_bins(const SelArgs& a, const Lds& m, uint32_
 __device__ __forceinline__ uint32_t afresh(uint32_t x) {
   asm volatile("" : "+v"(x));
   return x;
+}
+
+// The bins of a read's hits, HPT or fewer to a thread: hit f goes to thread f % T.
+// Returns the hits (the host chose T by their number). More seeds than the lists hold
+// are taken in turn; few hits then come with each.
+template <int T, int HPT, int N, typename Lds>
+__device__ __forceinline__ uint32_t all_bins(const SelArgs& a, const uint2* found, uint32_t n_seeds, Lds& m,
+                                             uint32_t (&bin)[HPT]) {
+  static_assert(HPT % N == 0, "groups of hits");
+  const uint32_t t = threadIdx.x;
+  uint32_t H = take_seeds<T>(found, n_seeds, 0, m), s = 0;
+#pragma unroll
+  for (int h0 = 0; h0 < HPT; h0 += N) {
+    uint32_t some[N];
+    hit_bins<T, N>(a, m, afresh(t) + h0 * T, H, 0, s, some);
+#pragma unroll
+    for (int h = 0; h < N; ++h) bin[h0 + h] = some[h];
+  }
+  for (uint32_t s0 = Lds::kSeeds; s0 < n_seeds; s0 += Lds::kSeeds) {
+    __syncthreads();
+    const uint32_t more = take_seeds<T>(found, n_seeds, s0, m);
+    s = 0;
+#pragma unroll
+    for (int h = 0; h < HPT; ++h) {
+      const uint32_t f = afresh(t) + h * T - H;  // wraps for hits of seeds before
+      if (f < more) {
+        while (m.s_pre[s + 1] <= f) ++s;
+        bin[h] = hit_bin(a.pos[m.s_h0[s] + (f - m.s_pre[s])], (uint64_t)(s0 + s) * a.k, a);
+      }
+    }
+    H += more;
+  }
+  return H;
 }
 
 // Thread t's hits are those numbered t + h T < H. cnt and hist are zero. Writes
@@ -1450,26 +1490,16 @@ template <int T, int HPT, int SPT>
 __global__ __launch_bounds__(T) void k_seed_sort(SelArgs a) {
   __shared__ __attribute__((aligned(16))) SortLds<T, HPT, SPT> m;
   const uint32_t t = threadIdx.x;
-  constexpr int N = 6;
   const uint32_t i = a.list[blockIdx.x];
   const int64_t o0 = a.offsets[a.r0 + i];
   const uint64_t n_seeds = (uint64_t)(a.offsets[a.r0 + i + 1] - o0) / a.k;
-  if (n_seeds > m.kSeeds) {
+  if (n_seeds > a.most_seeds) {
     to_hash(a, i);
     return;
   }
-#pragma unroll
-  for (uint32_t u = 0; u < SPT; u += 4) *reinterpret_cast<uint4*>(m.cnt + SPT * t + u) = make_uint4(0, 0, 0, 0);
-  // H <= HMAX: the host chose T by the same counts
-  const uint32_t H = sort_seeds<T>(a.found + (uint64_t)o0 / a.k, (uint32_t)n_seeds, m);
-  uint32_t bin[HPT], s = 0;
-#pragma unroll
-  for (int h0 = 0; h0 < HPT; h0 += N) {
-    uint32_t some[N];
-    hit_bins<T, N>(a, m, afresh(t) + h0 * T, H, s, some);
-#pragma unroll
-    for (int h = 0; h < N; ++h) bin[h0 + h] = some[h];
-  }
+  m.clear(t);
+  uint32_t bin[HPT];
+  const uint32_t H = all_bins<T, HPT, 6>(a, a.found + (uint64_t)o0 / a.k, (uint32_t)n_seeds, m, bin);
   if (!sort_select<T, HPT, SPT>(a, i, H, bin, 0, m)) to_hash(a, i);
 }
 
@@ -1490,8 +1520,8 @@ using CellLds = SortLds<1024, 24, 8>;
 
 // The hits to select from to out, their number to sh[2]; returns `least`, or 0 where
 // the cells cannot tell.
-__device__ __forceinline__ uint32_t cells_of(const SelArgs& a, uint32_t H, uint32_t cell_f, CellLds& m,
-                                             uint32_t (&many)[2][kCells / 32]) {
+__device__ __forceinline__ uint32_t cells_of(const SelArgs& a, const uint2* found, uint32_t n_seeds, uint32_t cell_f,
+                                             CellLds& m, uint32_t (&many)[2][kCells / 32]) {
   constexpr uint32_t T = 1024, SPT = 8, kWords = kCells / 2, kPer = kWords / 4 / T;
   uint32_t* const cells = m.cnt;  // two to a word, over cnt and out
   static_assert(offsetof(CellLds, out) == sizeof m.cnt && sizeof m.cnt + sizeof m.out >= 4 * kWords, "cells");
@@ -1510,6 +1540,23 @@ __device__ __forceinline__ uint32_t cells_of(const SelArgs& a, uint32_t H, uint3
 #pragma unroll
     for (uint32_t j = 0; j < 8; ++j) f(j, (w[j >> 1] >> (16 * (j & 1u))) & 0xFFFFu);
   };
+  // f(bin of a hit, whether there is one) for every hit, in step over the workgroup;
+  // seeds that all fit the lists are taken once
+  uint32_t H = take_seeds<T>(found, n_seeds, 0, m);
+  auto walk = [&](auto f) {
+    for (uint32_t s0 = 0; s0 < n_seeds; s0 += CellLds::kSeeds) {
+      if (n_seeds > CellLds::kSeeds) {
+        __syncthreads();  // the seeds before have been read
+        H = take_seeds<T>(found, n_seeds, s0, m);
+      }
+      for (uint32_t b0 = 0, s = 0; b0 < H; b0 += N * T) {
+        uint32_t bin[N];
+        hit_bins<T, N>(a, m, b0 + t, H, s0 * a.k, s, bin);
+#pragma unroll
+        for (int h = 0; h < N; ++h) f(bin[h], b0 + t + h * T < H);
+      }
+    }
+  };
   uint32_t least = 0, round = 0;
   for (;; ++round) {
 #pragma unroll
@@ -1517,16 +1564,12 @@ __device__ __forceinline__ uint32_t cells_of(const SelArgs& a, uint32_t H, uint3
     for (uint32_t w = t; w <= kSeedBucket; w += T) m.hist[w] = 0;
     if (t == 0) m.sh[1] = 0;
     __syncthreads();
-    for (uint32_t f0 = t, s = 0; f0 < H; f0 += N * T) {
-      uint32_t bin[N];
-      hit_bins<T, N>(a, m, f0, H, s, bin);
-#pragma unroll
-      for (int h = 0; h < N; ++h)
-        if (f0 + h * T < H && (round == 0 || listed(bin[h], 0))) {
-          const uint32_t c = cell(bin[h], round), shift = 16 * (c & 1u);
-          if (((atomicAdd(&cells[c >> 1], 1u << shift) >> shift) & 0xFFFFu) == 0xFFFFu) m.sh[0] = 1;
-        }
-    }
+    walk([&](uint32_t bin, bool in) {
+      if (in && (round == 0 || listed(bin, 0))) {
+        const uint32_t c = cell(bin, round), shift = 16 * (c & 1u);
+        if (((atomicAdd(&cells[c >> 1], 1u << shift) >> shift) & 0xFFFFu) == 0xFFFFu) m.sh[0] = 1;
+      }
+    });
     __syncthreads();
     if (m.sh[0]) return 0;  // a cell's count ran over
     // hits by the count of their cell, 255 or more together
@@ -1576,19 +1619,14 @@ __device__ __forceinline__ uint32_t cells_of(const SelArgs& a, uint32_t H, uint3
   __syncthreads();  // the threshold has been read from hist
   for (uint32_t w = t; w <= kSeedBucket; w += T) m.hist[w] = 0;
   // the hits in those cells, in any order, to out
-  for (uint32_t b0 = 0, s = 0; b0 < H; b0 += N * T) {
-    uint32_t bin[N];
-    hit_bins<T, N>(a, m, b0 + t, H, s, bin);
-#pragma unroll
-    for (int h = 0; h < N; ++h) {
-      const bool in = b0 + t + h * T < H && listed(bin[h], 0) && (round == 0 || listed(bin[h], 1));
-      const uint64_t who = __ballot(in);
-      uint32_t at = 0;
-      if (lane == 0 && who) at = atomicAdd(&m.sh[2], (uint32_t)__popcll(who));
-      at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
-      if (in) m.out[at + (uint32_t)__popcll(who & ((1ull << lane) - 1ull))] = bin[h];
-    }
-  }
+  walk([&](uint32_t bin, bool there) {
+    const bool in = there && listed(bin, 0) && (round == 0 || listed(bin, 1));
+    const uint64_t who = __ballot(in);
+    uint32_t at = 0;
+    if (lane == 0 && who) at = atomicAdd(&m.sh[2], (uint32_t)__popcll(who));
+    at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+    if (in) m.out[at + (uint32_t)__popcll(who & ((1ull << lane) - 1ull))] = bin;
+  });
   __syncthreads();
   return least;
 }
@@ -1604,16 +1642,15 @@ __global__ __launch_bounds__(1024) void k_seed_large(SelArgs a, uint32_t n_cells
   const uint32_t i = a.list[gridDim.x - 1 - blockIdx.x];
   const int64_t o0 = a.offsets[a.r0 + i];
   const uint64_t n_seeds = (uint64_t)(a.offsets[a.r0 + i + 1] - o0) / a.k;
-  if (n_seeds > CellLds::kSeeds) {
+  if (n_seeds > a.most_seeds) {
     to_hash(a, i);
     return;
   }
-#pragma unroll
-  for (uint32_t u = 0; u < SPT; u += 4) *reinterpret_cast<uint4*>(m.cnt + SPT * t + u) = make_uint4(0, 0, 0, 0);
-  const uint32_t H = sort_seeds<T>(a.found + (uint64_t)o0 / a.k, (uint32_t)n_seeds, m);
-  uint32_t bin[HPT], left = H, least = 0;
+  m.clear(t);
+  const uint2* found = a.found + (uint64_t)o0 / a.k;
+  uint32_t bin[HPT], left, least = 0;
   if (blockIdx.x < n_cells) {
-    least = cells_of(a, H, cell_f, m, many);
+    least = cells_of(a, found, (uint32_t)n_seeds, cell_f, m, many);
     if (least == 0) {
       to_hash(a, i);
       return;
@@ -1623,14 +1660,7 @@ __global__ __launch_bounds__(1024) void k_seed_large(SelArgs a, uint32_t n_cells
     for (int h = 0; h < HPT; ++h) bin[h] = t + h * T < left ? m.out[t + h * T] : 0u;
     __syncthreads();
   } else {
-    uint32_t s = 0;
-#pragma unroll
-    for (int h0 = 0; h0 < HPT; h0 += N) {
-      uint32_t some[N];
-      hit_bins<T, N>(a, m, afresh(t) + h0 * T, H, s, some);
-#pragma unroll
-      for (int h = 0; h < N; ++h) bin[h0 + h] = some[h];
-    }
+    left = all_bins<T, HPT, N>(a, found, (uint32_t)n_seeds, m, bin);
   }
   if (!sort_select<T, HPT, SPT>(a, i, left, bin, least, m)) to_hash(a, i);
 }
@@ -2111,6 +2141,7 @@ int grim_seed_candidates(const grim_seeds* csd, const grim_reads* rd, uint32_t b
   a.start = sd->start;
   a.pos = sd->pos;
   a.k = sd->k;
+  a.most_seeds = 0xFFFFFFFFu / sd->k;
   a.found = sd->found;
   a.bases = bases;
   a.offsets = offsets;
