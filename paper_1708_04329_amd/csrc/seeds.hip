@@ -21,8 +21,8 @@
 //   3. a workgroup per read sorts its hits into buckets of bins in LDS, counts
 //      votes and places there, and writes the kept bins in order to its staging
 //      slots; reads of more hits than fit are thinned out first;
-//   4. the reads that does not suit take LDS hash tables, and the few a table
-//      cannot describe exactly a slower path in device memory (sort, runs, exact
+//   4. the reads that does not suit take LDS hash tables of four sizes, and the few a
+//      table cannot describe exactly a slower path in device memory (sort, runs, exact
 //      selection);
 //   5. a scan of the kept counts gives the CSR offsets, and the lists move
 //      from staging to their place.
@@ -33,6 +33,7 @@
 #include <cstring>
 #include <memory>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "grim_internal.h"
@@ -67,7 +68,7 @@ struct grim_seeds {
   uint64_t list_cap = 0;
   uint32_t* redo = nullptr;       // [batch reads] reads for the fallback
   uint64_t redo_cap = 0;
-  uint32_t* hash = nullptr;       // [batch reads] reads for the hash tables
+  uint32_t* hash = nullptr;       // [batch reads] reads for the hash tables, by table
   uint64_t hash_cap = 0;
   uint32_t* slab = nullptr;       // fallback work space
   uint64_t slab_cap = 0;
@@ -610,7 +611,7 @@ __global__ __launch_bounds__(256) void k_part_starts(const uint64_t* place, uint
 
 // ---------------------------------------------------------------------------
 // Candidate selection by hash tables, one workgroup per read, in LDS: the reads that
-// k_seed_sort and k_seed_large pass on.
+// k_seed_sort and k_seed_large pass on, and those of many hits a bin (seed_class).
 //
 // Each hit's bin goes into an open-addressing hash table of packed entries
 // (bin << vb | votes, linear probing, atomic compare-and-swap to claim a
@@ -634,6 +635,23 @@ __global__ __launch_bounds__(256) void k_part_starts(const uint64_t* place, uint
 // ---------------------------------------------------------------------------
 constexpr uint32_t kEmpty = 0xFFFFFFFFu;
 constexpr uint32_t kVoteHist = 256;  // votes counted exactly below this
+// Hits a bin from which runs of hits are put into the table together: 500 reads of
+// 97000 hits in 6 bins 0.50 -> 0.32 ms, in 489 bins 0.30 -> 0.35.
+constexpr uint32_t kCrowdedRuns = 512;
+
+// The hash tables' sizes: reads of up to kHashHits[c] hits fit table c (three
+// quarters of its slots), the last takes the rest. Reads that are passed on, of which
+// few come as a rule, take tables 1 and 3 (every launch more that finds none costs a
+// call 4 us); the others are for reads that go there at once.
+constexpr uint32_t kHashTables = 4;
+constexpr uint32_t kHashHits[kHashTables - 1] = {1536, 6144, 12288};
+__host__ __device__ constexpr uint32_t hash_table(uint64_t h) {
+  return uint32_t(h > kHashHits[0]) + uint32_t(h > kHashHits[1]) + uint32_t(h > kHashHits[2]);
+}
+
+// The tables' lists share an array of a word per read: 0, 1, the free words between,
+// 3 and 2. Lists 1 and 3 grow into the free words, 3 downwards.
+__host__ __device__ constexpr int hash_step(uint32_t table) { return table == 3 ? -1 : 1; }
 
 struct SelArgs {
   const uint64_t* start;
@@ -650,8 +668,9 @@ struct SelArgs {
   uint32_t* cnt;             // [batch reads] bins kept
   uint32_t* redo;            // [batch reads] reads handed to the fallback
   uint32_t* n_redo;          // their number
-  uint32_t* hash;            // [batch reads] reads for the hash tables
-  uint32_t* n_hash;          // their number
+  uint32_t* hash[4];         // reads for each hash table: read j of table c is hash[c][j * hash_step(c)]
+  uint32_t* n_hash;          // [4] their numbers
+  uint32_t table;            // k_seed_select's own
   const uint32_t* list;      // batch-relative reads of a k_seed_sort launch, a workgroup each
   uint32_t cap;
   uint32_t nbins;            // bins are below nbins
@@ -753,9 +772,9 @@ __global__ __launch_bounds__(T) void k_seed_select(SelArgs a) {
   __shared__ uint32_t sh[9];
   const uint32_t t = threadIdx.x, lane = t & 63u;
   const uint32_t vmask = (1u << a.vb) - 1u;
-  const uint32_t n_hash = *a.n_hash;
+  const uint32_t n_hash = a.n_hash[a.table];
   for (uint32_t li = blockIdx.x; li < n_hash; li += gridDim.x) {
-    const uint32_t i = a.hash[li];
+    const uint32_t i = a.hash[a.table][(int64_t)li * hash_step(a.table)];
     const uint64_t r = a.r0 + i;
     const uint64_t H = a.hits[r];
     if (t == 0) sh[2] = 0;  // read by no thread before the first clear()'s barrier
@@ -861,8 +880,11 @@ __global__ __launch_bounds__(T) void k_seed_select(SelArgs a) {
     // table's room (counted), the slots claimed are counted, one atomic per
     // wavefront and step, and once the count reaches the limit no lane starts
     // another hit (at most T more slots are claimed, which leaves the table a
-    // free slot, so every probe ends); sh[1] then tells the caller.
-    auto walk_all = [&](bool counted) {
+    // free slot, so every probe ends); sh[1] then tells the caller. kRuns: a lane
+    // takes HB hits in a row, and those of one bin go in together: a k-mer's positions
+    // are in order, so where hundreds share a bin all lanes would add to one word.
+    auto walk_all = [&](bool counted, auto runs) {
+      constexpr bool kRuns = decltype(runs)::value;
       for (uint32_t sc = 0; sc < n_seeds; sc += T) {
         const uint32_t ns = min((uint32_t)T, n_seeds - sc);
         uint32_t h0 = 0, c = 0;
@@ -882,12 +904,13 @@ __global__ __launch_bounds__(T) void k_seed_select(SelArgs a) {
         __syncthreads();
         constexpr uint32_t HB = 8;
         uint32_t s = 0;
-        for (uint32_t f0 = t; f0 < total; f0 += HB * T) {
+        constexpr uint32_t kStep = kRuns ? 1 : T;
+        for (uint32_t f0 = kRuns ? t * HB : t; f0 < total; f0 += HB * T) {
           uint32_t bins[HB];
           uint32_t nh = 0;  // this lane's hits in the batch: bins[0 .. nh)
 #pragma unroll
           for (uint32_t h = 0; h < HB; ++h) {
-            const uint32_t f = f0 + h * T;
+            const uint32_t f = f0 + h * kStep;
             bins[h] = 0;
             if (f < total) {
               while (s_pre[s + 1] <= f) ++s;
@@ -896,17 +919,25 @@ __global__ __launch_bounds__(T) void k_seed_select(SelArgs a) {
             }
           }
           if (counted && sh[1]) nh = 0;
-          uint32_t bin = bins[0];
+          uint32_t bin = bins[0], votes = 1;
           uint32_t sl = (bin * 0x9E3779B1u) >> (32u - logS);
           while (nh) {
-            const uint32_t old = atomicCAS(&tab[sl], kEmpty, (bin << a.vb) | 1u);
+            if (kRuns && nh > 1 && bins[1] == bin) {
+              ++votes;
+              --nh;
+#pragma unroll
+              for (uint32_t h = 0; h + 1 < HB; ++h) bins[h] = bins[h + 1];
+              continue;
+            }
+            const uint32_t old = atomicCAS(&tab[sl], kEmpty, (bin << a.vb) | votes);
             const bool claimed = old == kEmpty;
             bool placed = claimed;
             if (!placed && (old >> a.vb) == bin) {
-              const uint32_t o2 = atomicAdd(&tab[sl], 1u);
-              if ((o2 & vmask) + 1u >= vmask) sh[2] = 1u;
+              const uint32_t o2 = atomicAdd(&tab[sl], votes);
+              if ((o2 & vmask) + votes >= vmask) sh[2] = 1u;
               placed = true;
             }
+            if (kRuns && claimed && votes >= vmask) sh[2] = 1u;
             if (counted) {
               const uint64_t m = __ballot(claimed);
               if (m && lane == (uint32_t)__builtin_ctzll(m)) {
@@ -919,6 +950,7 @@ __global__ __launch_bounds__(T) void k_seed_select(SelArgs a) {
 #pragma unroll
               for (uint32_t h = 0; h + 1 < HB; ++h) bins[h] = bins[h + 1];
               bin = bins[0];
+              votes = 1;
               sl = (bin * 0x9E3779B1u) >> (32u - logS);
               if (counted && sh[1]) nh = 0;
             } else {
@@ -1089,7 +1121,8 @@ __global__ __launch_bounds__(T) void k_seed_select(SelArgs a) {
     uint32_t kept = 0;
     if (R == 1) {
       clear();
-      walk_all(counted);
+      if (H > (uint64_t)kCrowdedRuns * a.nbins) walk_all(counted, std::true_type{});
+      else walk_all(counted, std::false_type{});
       if (sh[1]) {
         R = ranges_for();  // its distinct bins overflowed the table
       } else if (sh[2]) {
@@ -1196,8 +1229,11 @@ __global__ __launch_bounds__(T) void k_seed_select(SelArgs a) {
 // dependent loads that start a read (a third of its 25 us), which the other
 // workgroups of a CU hide: 19241 reads of up to 24576 hits on the 3.1 Gbp reference
 // (77 M hits) take 0.57 ms, the hash tables took 1.7.
-// A read with more than kSeedBucket hits in one bucket goes on to the hash tables.
-constexpr uint32_t kSeedBucket = 255;
+// A read with more than kSeedBucket hits in one bucket goes on to the hash tables, and
+// so does one of more than 6144 hits whose looks at buckets of more than kLongBucket,
+// as many as the squares of their sizes, would take longer than the tables: 5000
+// reads of 24000 hits at 96 a bin took 2.70 ms by buckets alone, 1.40 so.
+constexpr uint32_t kSeedBucket = 255, kLongBucket = 32;
 
 template <int T, int HPT, int SPT>
 struct SortLds {
@@ -1310,6 +1346,7 @@ template <int T, int HPT, int SPT>
 __device__ __forceinline__ bool sort_select(const SelArgs& a, uint32_t i, uint32_t H, uint32_t (&bin)[HPT],
                                             uint32_t least, SortLds<T, HPT, SPT>& m) {
   constexpr uint32_t S = SPT * T, HMAX = HPT * T;
+  constexpr bool kLooks = T == 1024;
   uint32_t* const cnt = m.cnt;
   uint32_t* const out = m.out;
   const uint32_t t = threadIdx.x, lane = t & 63u;
@@ -1319,7 +1356,7 @@ __device__ __forceinline__ bool sort_select(const SelArgs& a, uint32_t i, uint32
     if (t + h * T < H) rank[h] = atomicAdd(&cnt[__umulhi(bin[h], a.dbm)], 1u);
   __syncthreads();
   {
-    uint32_t v[SPT], sum = 0, most = 0;
+    uint32_t v[SPT], sum = 0, most = 0, long_looks = 0;
 #pragma unroll
     for (uint32_t u = 0; u < SPT; u += 4) {
       const uint4 q = *reinterpret_cast<const uint4*>(cnt + SPT * t + u);
@@ -1329,10 +1366,12 @@ __device__ __forceinline__ bool sort_select(const SelArgs& a, uint32_t i, uint32
     for (uint32_t u = 0; u < SPT; ++u) {
       const uint32_t x = v[u];
       most = max(most, x);
+      if (kLooks) long_looks += x > kLongBucket ? x * x : 0u;
       v[u] = sum;
       sum += x;
     }
     if (most > kSeedBucket) m.sh[0] = 1;
+    if (kLooks && most > kLongBucket) atomicAdd(&m.sh[3], long_looks);  // at most H * H
     uint32_t all;
     const uint32_t at = block_excl_scan<T, uint32_t>(sum, m.ws, &all);
 #pragma unroll
@@ -1341,7 +1380,7 @@ __device__ __forceinline__ bool sort_select(const SelArgs& a, uint32_t i, uint32
     if (t == 0) cnt[S] = H;
   }
   __syncthreads();
-  if (m.sh[0]) return false;
+  if (m.sh[0] || (kLooks && m.sh[3] > 32 * H + 1024 * T)) return false;
 #pragma unroll
   for (int h = 0; h < HPT; ++h)
     if (afresh(t) + h * T < H) out[cnt[__umulhi(bin[h], a.dbm)] + rank[h]] = bin[h];
@@ -1482,8 +1521,10 @@ __device__ __forceinline__ bool sort_select(const SelArgs& a, uint32_t i, uint32
   return true;
 }
 
-__device__ __forceinline__ void to_hash(const SelArgs& a, uint32_t i) {
-  if (threadIdx.x == 0) a.hash[atomicAdd(a.n_hash, 1u)] = i;
+// Read i of H hits goes on to the hash tables.
+__device__ __forceinline__ void to_hash(const SelArgs& a, uint32_t i, uint64_t H) {
+  const uint32_t c = H <= kHashHits[1] ? 1u : 3u;
+  if (threadIdx.x == 0) a.hash[c][(int64_t)atomicAdd(a.n_hash + c, 1u) * hash_step(c)] = i;
 }
 
 template <int T, int HPT, int SPT>
@@ -1494,13 +1535,13 @@ __global__ __launch_bounds__(T) void k_seed_sort(SelArgs a) {
   const int64_t o0 = a.offsets[a.r0 + i];
   const uint64_t n_seeds = (uint64_t)(a.offsets[a.r0 + i + 1] - o0) / a.k;
   if (n_seeds > a.most_seeds) {
-    to_hash(a, i);
+    to_hash(a, i, a.hits[a.r0 + i]);
     return;
   }
   m.clear(t);
   uint32_t bin[HPT];
   const uint32_t H = all_bins<T, HPT, 6>(a, a.found + (uint64_t)o0 / a.k, (uint32_t)n_seeds, m, bin);
-  if (!sort_select<T, HPT, SPT>(a, i, H, bin, 0, m)) to_hash(a, i);
+  if (!sort_select<T, HPT, SPT>(a, i, H, bin, 0, m)) to_hash(a, i, H);
 }
 
 // Reads of more hits than that: the hits are first counted by cell, the bins
@@ -1642,8 +1683,9 @@ __global__ __launch_bounds__(1024) void k_seed_large(SelArgs a, uint32_t n_cells
   const uint32_t i = a.list[gridDim.x - 1 - blockIdx.x];
   const int64_t o0 = a.offsets[a.r0 + i];
   const uint64_t n_seeds = (uint64_t)(a.offsets[a.r0 + i + 1] - o0) / a.k;
+  const uint64_t H = a.hits[a.r0 + i];
   if (n_seeds > a.most_seeds) {
-    to_hash(a, i);
+    to_hash(a, i, H);
     return;
   }
   m.clear(t);
@@ -1652,7 +1694,7 @@ __global__ __launch_bounds__(1024) void k_seed_large(SelArgs a, uint32_t n_cells
   if (blockIdx.x < n_cells) {
     least = cells_of(a, found, (uint32_t)n_seeds, cell_f, m, many);
     if (least == 0) {
-      to_hash(a, i);
+      to_hash(a, i, H);
       return;
     }
     left = m.sh[2];
@@ -1662,7 +1704,7 @@ __global__ __launch_bounds__(1024) void k_seed_large(SelArgs a, uint32_t n_cells
   } else {
     left = all_bins<T, HPT, N>(a, found, (uint32_t)n_seeds, m, bin);
   }
-  if (!sort_select<T, HPT, SPT>(a, i, left, bin, least, m)) to_hash(a, i);
+  if (!sort_select<T, HPT, SPT>(a, i, left, bin, least, m)) to_hash(a, i, H);
 }
 
 // ---------------------------------------------------------------------------
@@ -1834,12 +1876,15 @@ __global__ void k_seed_call(uint64_t* words, uint64_t* bad) {
   if (threadIdx.x == 8) *bad = 0;
 }
 __global__ __launch_bounds__(256) void k_seed_batch(uint32_t* cnt, uint32_t nb, uint32_t* n_redo, uint32_t redo,
-                                                    uint32_t* n_hash, uint32_t hash) {
+                                                    uint32_t* n_hash, uint4 hash) {
   const uint32_t i = blockIdx.x * 256 + threadIdx.x;
   if (i < nb) cnt[i] = 0;
   if (i == 0) {
     *n_redo = redo;
-    *n_hash = hash;
+    n_hash[0] = hash.x;
+    n_hash[1] = hash.y;
+    n_hash[2] = hash.z;
+    n_hash[3] = hash.w;
   }
 }
 
@@ -1887,9 +1932,21 @@ bool env_flag(const char* name) { return env_int(name, 0) != 0; }
 
 // The kernel of a read with h hits: k_seed_sort of the fewest threads and LDS that
 // hold them, which leaves room for more workgroups per CU; by cells beyond, up to
-// where 32-bit hit numbers are safe. The hash tables take what these pass on.
-constexpr uint32_t kSeedClasses = 8, kSeedCells = 6, kSeedHash = 7;
-uint32_t seed_class(uint64_t h) {  // sums, as the classes come in no order a branch could learn
+// where 32-bit hit numbers are safe. The hash tables take what these pass on, and at
+// once
+//   - reads of kCrowded hits a bin and more, whose buckets would be long (2000 reads of
+//     3900 hits: 196 us by buckets and 172 by tables at 39 a bin, 147 and 210 at 8);
+//   - reads for the cells where all bins fit the largest table: a table filled in one
+//     walk over the hits is the faster (500 reads of 97000 hits in 3334 bins 0.46 ms by
+//     cells, 0.29 by tables).
+constexpr uint32_t kSeedClasses = 11, kSeedCells = 6, kSeedHash = 7;  // 7: the largest table, 8 .. 10 the smaller
+constexpr uint64_t kCrowded = 32;
+// Classes kHashFrom[c] .. kHashFrom[c + 1] - 1 pass reads on to table c, to kHashGroups[c] workgroups.
+constexpr uint32_t kHashFrom[kHashTables + 1] = {0, 0, 4, 4, kSeedHash};
+constexpr uint32_t kHashGroups[kHashTables] = {0, 1024, 0, 256};  // what the CUs hold at a time
+uint32_t hash_class(uint32_t table) { return kSeedHash + (table + 1) % kHashTables; }
+uint32_t seed_class(uint64_t h, uint64_t hashed) {  // sums, as the classes come in no order a branch could learn
+  if (h > hashed) return hash_class(hash_table(h));
   return uint32_t(h > 768) + uint32_t(h > 1536) + uint32_t(h > 3072) + uint32_t(h > 6144) + uint32_t(h > 12288) +
          uint32_t(h > 24576) + uint32_t(h > (1ull << 31));
 }
@@ -2118,7 +2175,7 @@ int grim_seed_candidates(const grim_seeds* csd, const grim_reads* rd, uint32_t b
   if (!sd->words) GRIM_HIP_TRY(pool_alloc(&sd->words, 8 * sizeof(uint64_t)));
   uint32_t* bad = reinterpret_cast<uint32_t*>(sd->hits + n);
   uint32_t* n_redo = reinterpret_cast<uint32_t*>(sd->words + 3);
-  uint32_t* n_hash = reinterpret_cast<uint32_t*>(sd->words + 4);
+  uint32_t* n_hash = reinterpret_cast<uint32_t*>(sd->words + 4);  // a word per table
   hipLaunchKernelGGL(k_seed_call, dim3(1), dim3(64), 0, s, sd->words, sd->hits + n);
   GRIM_HIP_TRY(hipGetLastError());
   hipLaunchKernelGGL(k_seed_hits, dim3((unsigned)std::min((n + 15) / 16, kHitBlocks)), dim3(256), 0, s, sd->start,
@@ -2154,6 +2211,9 @@ int grim_seed_candidates(const grim_seeds* csd, const grim_reads* rd, uint32_t b
   a.range_hits = (uint32_t)std::max(1, env_int("GRIM_SEED_RANGE_HITS", 16384));
   a.force_ranges = env_flag("GRIM_SEED_FORCE_RANGES") ? 1u : 0u;
   if (a.force_ranges || std::getenv("GRIM_SEED_VOTE_BITS")) class_min = kSeedHash;
+  // more hits than this go to the hash tables at once
+  uint64_t hashed = (uint64_t)nbins * kCrowded;
+  if (nbins <= 24576) hashed = std::min<uint64_t>(hashed, 24576);
   a.n_redo = n_redo;
   a.n_hash = n_hash;
   // 2. batches of bounded staging (each read takes min(hits, cap) slots),
@@ -2223,7 +2283,7 @@ int grim_seed_candidates(const grim_seeds* csd, const grim_reads* rd, uint32_t b
         ++n_fb;
         continue;
       }
-      ++per_class[std::max(class_min, seed_class(h))];
+      ++per_class[std::max(class_min, seed_class(h, hashed))];
     }
     uint64_t first[kSeedClasses + 1] = {};
     for (uint32_t c = 0; c < kSeedClasses; ++c) first[c + 1] = first[c] + per_class[c];
@@ -2235,25 +2295,33 @@ int grim_seed_candidates(const grim_seeds* csd, const grim_reads* rd, uint32_t b
         const uint64_t h = H[r0 + i];
         if (h == 0) continue;
         if (all_fallback) list_h[fb++] = (uint32_t)i;
-        else list_h[at[std::max(class_min, seed_class(h))]++] = (uint32_t)i;
+        else list_h[at[std::max(class_min, seed_class(h, hashed))]++] = (uint32_t)i;
       }
     }
     const uint64_t listed = all_fallback ? n_fb : first[kSeedClasses];
     GRIM_HIP_TRY(hipMemcpyAsync(sd->toff, toff_h, nb * sizeof(uint64_t), hipMemcpyHostToDevice, s));
     if (listed) GRIM_HIP_TRY(hipMemcpyAsync(all_fallback ? sd->redo : sd->list, list_h, listed * sizeof(uint32_t),
                                             hipMemcpyHostToDevice, s));
-    const uint64_t n_big = per_class[kSeedHash];
-    if (n_big) GRIM_HIP_TRY(hipMemcpyAsync(sd->hash, list_h + first[kSeedHash], n_big * sizeof(uint32_t),
-                                           hipMemcpyHostToDevice, s));
+    uint32_t n_hashed[kHashTables];  // reads that start there
+    for (uint32_t c = 0; c < kHashTables; ++c) n_hashed[c] = (uint32_t)per_class[hash_class(c)];
+    a.hash[0] = sd->hash;
+    a.hash[1] = a.hash[0] + n_hashed[0];
+    a.hash[2] = sd->hash + nb - n_hashed[2];
+    a.hash[3] = a.hash[2] - 1;
+    for (uint32_t c = 0; c < kHashTables; ++c)
+      if (n_hashed[c])
+        GRIM_HIP_TRY(hipMemcpyAsync(hash_step(c) > 0 ? a.hash[c] : a.hash[c] + 1 - n_hashed[c],
+                                    list_h + first[hash_class(c)], n_hashed[c] * sizeof(uint32_t),
+                                    hipMemcpyHostToDevice, s));
     hipLaunchKernelGGL(k_seed_batch, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, s, sd->cnt, (uint32_t)nb, n_redo,
-                       all_fallback ? (uint32_t)n_fb : 0u, n_hash, (uint32_t)n_big);
+                       all_fallback ? (uint32_t)n_fb : 0u, n_hash,
+                       make_uint4(n_hashed[0], n_hashed[1], n_hashed[2], n_hashed[3]));
     GRIM_HIP_TRY(hipGetLastError());
     a.r0 = r0;
     a.tmp_off = sd->toff;
     a.tmp = sd->tmp;
     a.cnt = sd->cnt;
     a.redo = sd->redo;
-    a.hash = sd->hash;
     // 3. each read's kept bins, in LDS, one workgroup per read
     if (!all_fallback) {
       // the largest first: the others fill the chip as they end
@@ -2280,10 +2348,22 @@ int grim_seed_candidates(const grim_seeds* csd, const grim_reads* rd, uint32_t b
         }
         GRIM_HIP_TRY(hipGetLastError());
       }
-      // the reads they passed on, and those too large for them
-      if (listed) {
-        hipLaunchKernelGGL((k_seed_select<1024, 32768>), dim3((unsigned)std::min<uint64_t>(listed, std::max<uint64_t>(n_big, 256))),
-                           dim3(1024), 0, s, a);
+      // the reads they passed on, and those not for them: a launch per table that one
+      // of the classes may have passed a read to
+      for (uint32_t c = 0; c < kHashTables; ++c) {
+        uint64_t may = n_hashed[c];
+        const bool any = class_min && kHashGroups[c];  // tests: classes do not tell the hits
+        for (uint32_t of = any ? 0 : kHashFrom[c]; of < (any ? kSeedHash : kHashFrom[c + 1]); ++of) may += per_class[of];
+        if (!may) continue;
+        SelArgs b = a;
+        b.table = c;
+        const dim3 grid((unsigned)std::min<uint64_t>(may, std::max(n_hashed[c], kHashGroups[c])));
+        switch (c) {
+          case 0: hipLaunchKernelGGL((k_seed_select<128, 2048>), grid, dim3(128), 0, s, b); break;
+          case 1: hipLaunchKernelGGL((k_seed_select<256, 8192>), grid, dim3(256), 0, s, b); break;
+          case 2: hipLaunchKernelGGL((k_seed_select<512, 16384>), grid, dim3(512), 0, s, b); break;
+          default: hipLaunchKernelGGL((k_seed_select<1024, 32768>), grid, dim3(1024), 0, s, b); break;
+        }
         GRIM_HIP_TRY(hipGetLastError());
       }
     }

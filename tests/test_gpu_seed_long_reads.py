@@ -1,5 +1,6 @@
 """Seed candidates of reads with more seeds than a workgroup's lists hold (taken in
-turn by every launch shape). Bit-exact against the oracle."""
+turn by every launch shape), and of reads of many hits a bin, which the hash tables
+take at once, by their size. Bit-exact against the oracle."""
 
 from __future__ import annotations
 
@@ -42,3 +43,21 @@ def test_cells_of_many_seeds(oracle, cell_read):
     seqs = reads_of(ref, rng, 5, [cell_read, 255, 256, 257])
     for B in (1, 12):
         check(oracle, ref, seqs, 5, B, (3, 2000, 30_000))
+
+
+@pytest.mark.parametrize("hits", [767, 1536, 1537, 6144, 6145, 12288, 12289, 40000])
+@pytest.mark.parametrize("vote_bits", [None, "2"])
+def test_few_bins(oracle, monkeypatch, hits, vote_bits):
+    """One to thirty bins: runs of hits in one bin are put into the table together (votes
+    beyond a narrow vote field go to the fallback)."""
+    if vote_bits:
+        monkeypatch.setenv("GRIM_SEED_VOTE_BITS", vote_bits)
+    rng = np.random.default_rng(hits)
+    k, G = 12, 24 * 40_100
+    ref = BASES[rng.integers(0, 2, G)]
+    seed = np.frombuffer(b"GTTGACGTTGCA", np.uint8)
+    for cell in rng.choice(G // 24, hits, replace=False):
+        ref[24 * cell + 5:24 * cell + 17] = seed
+    seqs = [seed.tobytes(), b"TTTTTTTTTTTT" + seed.tobytes() * 2]
+    for B in (G, G // 6, G // 29):
+        check(oracle, ref, seqs, k, B, (1, 4, 60))
