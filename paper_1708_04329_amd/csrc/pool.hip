@@ -35,7 +35,7 @@ namespace {
 
 constexpr size_t kMost = size_t(12) << 30;
 constexpr size_t kLook = size_t(64) << 20;  // smaller blocks are kept without a look at the free memory,
-constexpr double kLookAgain = 0.1;          // which a loop takes this often at most (10 us each)
+constexpr double kLookAgain = 0.1;          // which a loop takes this often at most (3 us each)
 constexpr double kIdle = 2.0, kBrief = 2.0;
 
 // The thread that gives idle blocks back, and what it shares with the process's end.
@@ -113,8 +113,8 @@ struct HipDriver {
     Watch& w = grim::watch();
     std::lock_guard<std::mutex> lk(w.mu);
     if (w.stop) return false;
+    if (w.running) return true;
     const bool mine = w.pid == getpid();
-    if (w.running && mine) return true;
     // its frees go through the runtime, which ends after what is registered here
     static const int at_end = std::atexit(end_watch);
     if (at_end != 0) return false;
