@@ -201,12 +201,13 @@ int grim_filter_candidates(const grim_index* idx, const grim_reads* reads,
  * harnesses that forbid hipMalloc. Same arguments, results and errors as
  * grim_filter_candidates, with two differences:
  *   - the reads must be in device memory (on_device = 1);
- *   - the call's size is limited as if its thresholds and token lists took
- *     256 + (n_reads + 1) * 4 (rounded up to 256) + 4 * (n_bases + 64 *
- *     n_reads + 128) of GRIM_STATIC_SCRATCH_BYTES, about 10 MB per 100K reads
- *     of 100 bases; larger calls fail with GRIM_EINVAL (split them, or use
- *     grim_filter_candidates). What scratch a call uses is a fixed device
- *     array that each GPU the library runs on holds until the process ends.
+ *   - the call's size is limited: 256 + (n_reads + 1) * 4 (rounded up to 256)
+ *     + 4 * (n_bases + 64 * n_reads + 128), what thresholds and token lists of
+ *     the reads would take, may not exceed GRIM_STATIC_SCRATCH_BYTES (about
+ *     10 MB per 100K reads of 100 bases); larger calls fail with GRIM_EINVAL
+ *     (split them, or use grim_filter_candidates). The scratch that calls do
+ *     use, flags and a counter, is a fixed device array of 256 bytes that each
+ *     GPU the library runs on holds until the process ends.
  * Every call on one GPU shares that GPU's array. The library runs such calls
  * one at a time per GPU within a process, and a call returns only after its
  * work on hip_stream is complete, so calls cannot overlap; the array keeps

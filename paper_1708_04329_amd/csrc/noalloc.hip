@@ -85,8 +85,9 @@ extern "C" int grim_filter_candidates_static(const grim_index* cidx, const grim_
   const uint64_t off_tok = 256 + up256((rd->n_reads + 1) * 4);
   if (rd->n_reads > most || rd->n_bases > most || off_tok + token_capacity(rd->n_bases, rd->n_reads) * 4 > most)
     return set_error(GRIM_EINVAL,
-                     "%llu reads of %llu bases need %llu scratch bytes, above the fixed %llu "
-                     "(GRIM_STATIC_SCRATCH_BYTES); split the call or use grim_filter_candidates",
+                     "%llu reads of %llu bases are beyond the size limit of this call: their token lists would take "
+                     "%llu scratch bytes, more than %llu (GRIM_STATIC_SCRATCH_BYTES); split the call or use "
+                     "grim_filter_candidates",
                      (unsigned long long)rd->n_reads, (unsigned long long)rd->n_bases,
                      (unsigned long long)(off_tok + token_capacity(rd->n_bases, rd->n_reads) * 4),
                      (unsigned long long)most);
