@@ -19,8 +19,9 @@
 // streams its token list against the LDS rows: G = TW/LW lanes share a read,
 // each lane owns LW words (32*LW bins) and reads them with LW/4 16-byte LDS
 // loads per token. Tokens arrive pre-scaled to the LDS byte offset of their
-// row, so a row address costs one add per token. All CUs work on the tiles of
-// one read chunk at a time, whose tokens then stay in the XCDs' L2s.
+// row, so a row address costs one add per token. The CUs of an XCD work on the
+// tiles of one read chunk at a time, whose tokens then stay in its L2: from eight
+// chunks on each XCD has a chunk of its own, with fewer all share one.
 //
 // Full 32-token blocks go through the Harley-Seal tree, two blocks per step
 // so that only every other block's carry ripples through the upper planes;
@@ -530,7 +531,7 @@ hipError_t launch_t(ScanArgs a, uint64_t reads_per_chunk, hipStream_t s) {
   a.n_rchunks = (uint32_t)chunks;
   const uint64_t blocks = chunks * a.n_tiles;
   // the per-bin count output is compiled only into its own instance: without
-  // it the kernel fits 126 registers with no spills (1.5% faster on the
+  // it the kernel fits 118 registers with no spills (1.5% faster on the
   // human-scale scan, and 36 GB less of scratch traffic per launch)
   if (a.counts_out)
     hipLaunchKernelGGL((k_scan_allbins<TW, LW, NT, true>), dim3((unsigned)blocks), dim3(NT), 0, s, a);

@@ -364,9 +364,10 @@ hipError_t launch_scan(const uint32_t* in, uint64_t n, uint64_t* out, uint64_t* 
 //      table's starts), and the positions to their places, through LDS where
 //      the partition fits.
 // Bound by the partial lines of step 3's runs and, where a partition does not
-// fit in LDS, of step 4's stores. 100 Mbp: 0.11 + 0.62 + 0.40 ms (every position
-// to its slot by itself: 2.5 ms in step 3; slots reserved with an atomic per tile
-// and partition: 0.90).
+// fit in LDS, of step 4's stores; step 3's kernel, which keeps a thread's 48 codes
+// over its two passes, also spills (128 VGPRs, 96 bytes of scratch a lane). 100
+// Mbp: 0.11 + 0.62 + 0.40 ms (every position to its slot by itself: 2.5 ms in step
+// 3; slots reserved with an atomic per tile and partition: 0.90).
 // ---------------------------------------------------------------------------
 constexpr uint32_t kTileT = 1024;  // threads per tile
 constexpr uint32_t kTileSpan = 32;

@@ -69,13 +69,11 @@ __device__ __forceinline__ uint32_t check_read(const TokArgs& a, uint64_t r, uin
   return err;
 }
 
-// The checks and thresholds alone, a thread per read.
+// The checks and thresholds alone, a thread per read (verification: no captured form).
 __global__ __launch_bounds__(256) void k_thresholds(TokArgs a) {
   const uint64_t r = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const uint64_t n_reads = a.dyn ? min(a.dyn->n_reads, a.n_reads) : a.n_reads;
-  const uint64_t n_bases = a.dyn ? min(a.dyn->n_bases, a.n_bases) : a.n_bases;
   int64_t o0, ntok;
-  if (r < n_reads) (void)check_read(a, r, n_bases, (int64_t)a.q, &o0, &ntok);
+  if (r < a.n_reads) (void)check_read(a, r, a.n_bases, (int64_t)a.q, &o0, &ntok);
 }
 
 template <int Q>
