@@ -191,10 +191,17 @@ __global__ __launch_bounds__(1024) void k_verify_scatter(VerifyArgs a) {
   const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
   const uint64_t r_lo = (uint64_t)blockIdx.x * a.chunk;
   const uint64_t r_hi = min(a.n_reads, r_lo + a.chunk);
-  if (threadIdx.x >= 1 && threadIdx.x < kVerifyBuckets) {
-    unsigned long long first = a.chunk_sum[(uint64_t)threadIdx.x * gridDim.x + blockIdx.x];
-    for (uint32_t c = 1; c < threadIdx.x; ++c) first += a.bucket[c];
-    cur[threadIdx.x] = first;
+  if (wave == 0) {  // the pairs of the classes before, and of the class in the chunks before
+    const bool used = lane >= 1 && lane <= (a.bounded ? 2 * kVerifyWords : kVerifyWords);
+    const uint64_t pairs = used ? a.bucket[lane] : 0;
+    const uint64_t before = used ? a.chunk_sum[(uint64_t)lane * gridDim.x + blockIdx.x] : 0;
+    uint64_t incl = pairs;
+#pragma unroll
+    for (uint32_t d = 1; d < 64; d <<= 1) {
+      const uint64_t t = shfl_up64(incl, d);
+      if (lane >= d) incl += t;
+    }
+    if (used) cur[lane] = incl - pairs + before;
   }
   __syncthreads();
   for (uint64_t r = r_lo + wave; r < r_hi; r += 16) {
