@@ -646,10 +646,6 @@ constexpr uint32_t kCrowdedRuns = 512;
 // call 4 us); the others are for reads that go there at once.
 constexpr uint32_t kHashTables = 4;
 constexpr uint32_t kHashHits[kHashTables - 1] = {1536, 6144, 12288};
-__host__ __device__ constexpr uint32_t hash_table(uint64_t h) {
-  return uint32_t(h > kHashHits[0]) + uint32_t(h > kHashHits[1]) + uint32_t(h > kHashHits[2]);
-}
-
 // The tables' lists share an array of a word per read: 0, 1, the free words between,
 // 3 and 2. Lists 1 and 3 grow into the free words, 3 downwards.
 __host__ __device__ constexpr int hash_step(uint32_t table) { return table == 3 ? -1 : 1; }
@@ -1945,9 +1941,11 @@ constexpr uint64_t kCrowded = 32;
 // Classes kHashFrom[c] .. kHashFrom[c + 1] - 1 pass reads on to table c, to kHashGroups[c] workgroups.
 constexpr uint32_t kHashFrom[kHashTables + 1] = {0, 0, 4, 4, kSeedHash};
 constexpr uint32_t kHashGroups[kHashTables] = {0, 1024, 0, 256};  // what the CUs hold at a time
-uint32_t hash_class(uint32_t table) { return kSeedHash + (table + 1) % kHashTables; }
-uint32_t seed_class(uint64_t h, uint64_t hashed) {  // sums, as the classes come in no order a branch could learn
-  if (h > hashed) return hash_class(hash_table(h));
+uint32_t table_class(uint32_t table) { return kSeedHash + (table + 1) % kHashTables; }
+uint32_t hash_class(uint64_t h) {
+  return table_class(uint32_t(h > kHashHits[0]) + uint32_t(h > kHashHits[1]) + uint32_t(h > kHashHits[2]));
+}
+uint32_t seed_class(uint64_t h) {  // sums, as the classes come in no order a branch could learn
   return uint32_t(h > 768) + uint32_t(h > 1536) + uint32_t(h > 3072) + uint32_t(h > 6144) + uint32_t(h > 12288) +
          uint32_t(h > 24576) + uint32_t(h > (1ull << 31));
 }
@@ -2274,21 +2272,21 @@ int grim_seed_candidates(const grim_seeds* csd, const grim_reads* rd, uint32_t b
     uint64_t* toff_h = sd->toff_host + r0;
     uint32_t* list_h = sd->list_host + r0;
     uint64_t per_class[kSeedClasses] = {}, n_fb = 0;
-    uint64_t run = 0;
-    for (uint64_t i = 0; i < nb; ++i) {
-      const uint64_t h = H[r0 + i];
-      toff_h[i] = run;
-      run += std::min<uint64_t>(h, cap);
-      if (h == 0) continue;
-      if (all_fallback) {
-        ++n_fb;
-        continue;
-      }
-      ++per_class[std::max(class_min, seed_class(h, hashed))];
-    }
     uint64_t first[kSeedClasses + 1] = {};
-    for (uint32_t c = 0; c < kSeedClasses; ++c) first[c + 1] = first[c] + per_class[c];
-    {
+    auto group = [&](auto class_of) {
+      uint64_t run = 0;
+      for (uint64_t i = 0; i < nb; ++i) {
+        const uint64_t h = H[r0 + i];
+        toff_h[i] = run;
+        run += std::min<uint64_t>(h, cap);
+        if (h == 0) continue;
+        if (all_fallback) {
+          ++n_fb;
+          continue;
+        }
+        ++per_class[class_of(h)];
+      }
+      for (uint32_t c = 0; c < kSeedClasses; ++c) first[c + 1] = first[c] + per_class[c];
       uint64_t at[kSeedClasses];
       for (uint32_t c = 0; c < kSeedClasses; ++c) at[c] = first[c];
       uint64_t fb = 0;
@@ -2296,15 +2294,17 @@ int grim_seed_candidates(const grim_seeds* csd, const grim_reads* rd, uint32_t b
         const uint64_t h = H[r0 + i];
         if (h == 0) continue;
         if (all_fallback) list_h[fb++] = (uint32_t)i;
-        else list_h[at[std::max(class_min, seed_class(h, hashed))]++] = (uint32_t)i;
+        else list_h[at[class_of(h)]++] = (uint32_t)i;
       }
-    }
+    };
+    if (bt.max_h <= hashed) group([class_min](uint64_t h) { return std::max(class_min, seed_class(h)); });
+    else group([class_min, hashed](uint64_t h) { return std::max(class_min, h > hashed ? hash_class(h) : seed_class(h)); });
     const uint64_t listed = all_fallback ? n_fb : first[kSeedClasses];
     GRIM_HIP_TRY(hipMemcpyAsync(sd->toff, toff_h, nb * sizeof(uint64_t), hipMemcpyHostToDevice, s));
     if (listed) GRIM_HIP_TRY(hipMemcpyAsync(all_fallback ? sd->redo : sd->list, list_h, listed * sizeof(uint32_t),
                                             hipMemcpyHostToDevice, s));
     uint32_t n_hashed[kHashTables];  // reads that start there
-    for (uint32_t c = 0; c < kHashTables; ++c) n_hashed[c] = (uint32_t)per_class[hash_class(c)];
+    for (uint32_t c = 0; c < kHashTables; ++c) n_hashed[c] = (uint32_t)per_class[table_class(c)];
     a.hash[0] = sd->hash;
     a.hash[1] = a.hash[0] + n_hashed[0];
     a.hash[2] = sd->hash + nb - n_hashed[2];
@@ -2312,7 +2312,7 @@ int grim_seed_candidates(const grim_seeds* csd, const grim_reads* rd, uint32_t b
     for (uint32_t c = 0; c < kHashTables; ++c)
       if (n_hashed[c])
         GRIM_HIP_TRY(hipMemcpyAsync(hash_step(c) > 0 ? a.hash[c] : a.hash[c] + 1 - n_hashed[c],
-                                    list_h + first[hash_class(c)], n_hashed[c] * sizeof(uint32_t),
+                                    list_h + first[table_class(c)], n_hashed[c] * sizeof(uint32_t),
                                     hipMemcpyHostToDevice, s));
     hipLaunchKernelGGL(k_seed_batch, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, s, sd->cnt, (uint32_t)nb, n_redo,
                        all_fallback ? (uint32_t)n_fb : 0u, n_hash,
