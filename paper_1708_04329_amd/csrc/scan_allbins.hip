@@ -410,8 +410,14 @@ __global__ __launch_bounds__(NT) void k_scan_allbins(ScanArgs a) {
   // step). Chunks that run side by side, `width` of them, take the groups of a
   // stretch in turn, so that they hold the same mix of lengths and the XCDs the
   // same work (with a run of reads each, the longest reads' chunk held its XCD
-  // up: 28000 mixed reads in 8 chunks 17.7 ms, 12.3 ms with equal shares).
-  const uint32_t width = a.n_rchunks % 8u == 0 ? 8u : a.n_rchunks;
+  // up: 28000 mixed reads in 8 chunks 17.7 ms, 12.3 ms with equal shares; 150000
+  // in 40 69.6 and 66.3 ms). With twelve and more chunks to an XCD their lengths
+  // hardly differ, and a chunk (of enough reads) takes a run of them, whose rows of
+  // the mask lie together: 1M of 150 bp 401.0 against 402.7 ms, 379.0 against 380.6
+  // and 373.2 against 375.0 on three cards; 1M mixed 0.8% either way.
+  constexpr uint32_t kRuns = 96, kRunReads = 512;
+  const bool runs = a.n_rchunks >= kRuns && n_reads >= (uint64_t)kRunReads * a.n_rchunks;
+  const uint32_t width = a.n_rchunks % 8u != 0 ? a.n_rchunks : (runs ? 1u : 8u);
   const uint64_t n_all = (n_reads + RPW - 1) / RPW;
   const uint64_t n_rows = (n_all + width - 1) / width, stretches = a.n_rchunks / width;
   const uint64_t per = n_rows / stretches, extra = n_rows % stretches, mine = rchunk / width;
