@@ -51,22 +51,22 @@ MALL_BYTES = 256 << 20  # Infinity Cache
 # they were taken on; reported as null once the source has changed since.
 MEASURED_TRAFFIC = {
     ("c3_allbins_3.1Gbp_q5", "scan_allbins.hip"): {
-        "sha256": "677b3ca8d1abe2a7620437dd65688d1c9b251ecf6e8ae2ce5aa4a0356e67ba4a",
-        "fetch_bytes": 83.10e9, "write_bytes": 192.09e9, "profile": "profiles/k_scan_allbins_c3_3.1Gbp_q5.md"},
+        "sha256": "7669cd92dbd9e8de6aed1f80755309b8fce5b56b2ee7390ce06e01eac53a41a5",
+        "fetch_bytes": 83.15e9, "write_bytes": 192.34e9, "profile": "profiles/k_scan_allbins_c3_3.1Gbp_q5.md"},
     ("c4_candidates_uneven_3.1Gbp_q6", "scan_candidates.hip"): {
-        "sha256": "63aa277896ac3793519d0fbd88ea3460caa1ebcb205e7cd64ee2b6448591baa3",
-        "fetch_bytes": 1051.7e9, "write_bytes": 13.4e9, "profile": "profiles/k_scan_cand_c4_3.1Gbp_q6.md"},
+        "sha256": "0b6be4bdcc1b9a2411801edc2329db55a3db00221e73bf4c8d58f9bd21eb1b51",
+        "fetch_bytes": 1050.7e9, "write_bytes": 13.3e9, "profile": "profiles/k_scan_cand_c4_3.1Gbp_q6.md"},
     ("c2_candidates_100Mbp_q5", "scan_candidates.hip"): {
-        "sha256": "63aa277896ac3793519d0fbd88ea3460caa1ebcb205e7cd64ee2b6448591baa3",
-        "fetch_bytes": 14.64e9, "write_bytes": 1.50e9, "profile": "profiles/k_scan_cand_c2_100Mbp_q5.md"},
+        "sha256": "0b6be4bdcc1b9a2411801edc2329db55a3db00221e73bf4c8d58f9bd21eb1b51",
+        "fetch_bytes": 12.80e9, "write_bytes": 1.34e9, "profile": "profiles/k_scan_cand_c2_100Mbp_q5.md"},
 }
 
 
 # VALU wavefront instructions per launch from rocprofv3 SQ_INSTS_VALU, keyed like the traffic.
 MEASURED_VALU = {
     ("c2_candidates_100Mbp_q5", "scan_candidates.hip"): {
-        "sha256": "63aa277896ac3793519d0fbd88ea3460caa1ebcb205e7cd64ee2b6448591baa3",
-        "valu_wave_insts": 1.0101e9, "profile": "profiles/k_scan_cand_c2_100Mbp_q5.md"},
+        "sha256": "0b6be4bdcc1b9a2411801edc2329db55a3db00221e73bf4c8d58f9bd21eb1b51",
+        "valu_wave_insts": 1.1581e9, "profile": "profiles/k_scan_cand_c2_100Mbp_q5.md"},
 }
 
 
