@@ -204,7 +204,7 @@ int grim_filter_candidates(const grim_index* idx, const grim_reads* reads,
  *   - the call's size is limited: 256 + (n_reads + 1) * 4 (rounded up to 256)
  *     + 4 * (n_bases + 64 * n_reads + 128), what thresholds and token lists of
  *     the reads would take, may not exceed GRIM_STATIC_SCRATCH_BYTES (about
- *     10 MB per 100K reads of 100 bases); larger calls fail with GRIM_EINVAL
+ *     66 MB per 100K reads of 100 bases); larger calls fail with GRIM_EINVAL
  *     (split them, or use grim_filter_candidates). The scratch that calls do
  *     use, flags and a counter, is a fixed device array of 256 bytes that each
  *     GPU the library runs on holds until the process ends.

@@ -471,8 +471,8 @@ STATIC_SCRATCH_BYTES = 64 << 20
 
 def grim_filter_candidates_static(index: Index, reads: ReadSet, cand_off, cand_bin, count_out=None, pass_out=None,
                                   stream=None):
-    """grim_filter_candidates with no device allocation (fixed per-GPU scratch of
-    STATIC_SCRATCH_BYTES); the reads must be device tensors."""
+    """grim_filter_candidates with no device allocation (its flags live in a fixed
+    array per GPU), for reads whose token lists would take at most STATIC_SCRATCH_BYTES; the reads must be device tensors."""
     _check_dtype(cand_off, "cand_off", np.int64)
     _check_dtype(cand_bin, "cand_bin", np.int32)
     _check_dtype(count_out, "count_out", np.uint16)
