@@ -85,9 +85,16 @@ struct HipDriver {
   std::mutex mu;
   Look seen[kDevices];  // the last look at each device's free memory
 
+  // Of this thread's last failed allocation: no memory, or a device in error.
+  static hipError_t& failure() {
+    static thread_local hipError_t e = hipErrorOutOfMemory;
+    return e;
+  }
   bool alloc(void** out, size_t bytes, int) {
-    if (hipMalloc(out, bytes) == hipSuccess) return true;
+    const hipError_t e = hipMalloc(out, bytes);
+    if (e == hipSuccess) return true;
     (void)hipGetLastError();  // reported by the result alone
+    failure() = e;
     return false;
   }
   void free(void* p, int device) {
@@ -172,7 +179,8 @@ hipError_t pool_alloc(void** out, size_t bytes) {
   const hipError_t e = hipGetDevice(&device);
   if (e != hipSuccess) return e;
   try {
-    return blocks().alloc(out, bytes, device) ? hipSuccess : hipErrorOutOfMemory;
+    HipDriver::failure() = hipErrorOutOfMemory;  // also where the lists find no host memory
+    return blocks().alloc(out, bytes, device) ? hipSuccess : HipDriver::failure();
   } catch (...) {
     *out = nullptr;
     return hipErrorOutOfMemory;
